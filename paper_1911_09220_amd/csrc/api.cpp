@@ -61,7 +61,7 @@ namespace {
 
 namespace pafem {
 // One application of the operator; `work` must hold op_work_bytes(op).  dotp (may be
-// null): pa_apply_blocks partial element energies for launch_cg_alpha.
+// null): pa_apply_blocks partial element energies for the update kernels.
 void apply_op(const Op& op, const void* x, void* y, void* work, hipStream_t st, double* dotp,
               bool y_ready) {
   const Space& s = *op.space;
@@ -623,7 +623,7 @@ pafem_status pafem_pcg_workspace_bytes(pafem_op op, int32_t max_iter, size_t* nb
     require(op->op.qdtype == PAFEM_F64, PAFEM_EUNSUPPORTED, "PCG needs an f64 operator");
     require(max_iter >= 0, PAFEM_EINVAL, "negative max_iter");
     const size_t n = size_t(op->op.space->ndofs);
-    *nbytes = align256(sizeof(CGState)) + align256(3 * kCGBlocks * sizeof(double)) +
+    *nbytes = align256(sizeof(CGState)) + align256(kPartials * kCGBlocks * sizeof(double)) +
               align256((size_t(max_iter) + 1) * sizeof(double)) + 3 * align256(n * 8) +
               align256(size_t(pa_apply_blocks(op->op.space->dev)) * sizeof(double)) +
               op_work_bytes(op->op);
@@ -659,7 +659,7 @@ pafem_status pafem_pcg_solve(pafem_op op, const double* diag, const double* b, d
     auto* state = reinterpret_cast<CGState*>(w);
     w += align256(sizeof(CGState));
     auto* partials = reinterpret_cast<double*>(w);
-    w += align256(3 * kCGBlocks * sizeof(double));
+    w += align256(kPartials * kCGBlocks * sizeof(double));
     auto* hist = reinterpret_cast<double*>(w);
     w += align256((size_t(opts->max_iter) + 1) * sizeof(double));
     auto* r = reinterpret_cast<double*>(w);
@@ -676,22 +676,17 @@ pafem_status pafem_pcg_solve(pafem_op op, const double* diag, const double* b, d
     const int check = std::max(1, opts->check_every);
     const uint8_t* ess = (o.flags & PAFEM_OP_CONSTRAINED) ? s.dev.bmask : nullptr;
 
-    launch_cg_reset(state, opts->max_iter + 1, st);
     if (!opts->zero_guess) apply_op(o, x, q, opwork, st);
-    launch_cg_init<double, double>(state, partials, b, 1.0, opts->zero_guess ? nullptr : q, dg,
-                                   x, r, d, opts->zero_guess, opts->rel_tol, hist, n, st);
     // the atomic scatter's y-init of each apply is written by the preceding kernel
     const bool evec = o.flags & PAFEM_OP_SCATTER_EVEC;
-    if (!evec) launch_scatter_init(s.dev, d, ess != nullptr, q, st);
+    double* const qi = evec ? nullptr : q;
+    launch_cg_init(state, partials, b, opts->zero_guess ? nullptr : q, dg, x, r, d, qi, ess,
+                   opts->zero_guess, opts->rel_tol, opts->max_iter + 1, hist, n, st);
     auto iterations = [&](hipStream_t s2, int count) {
       for (int k = 0; k < count; ++k) {
         apply_op(o, d, q, opwork, s2, dotp, !evec);
-        launch_cg_alpha(state, partials, dotp, nap, ess, d, n, s2);
-        launch_cg_update(state, partials, x, r, d, q, dg, hist, n, s2);
-        if (evec)
-          launch_cg_direction(state, r, dg, d, n, s2);
-        else
-          launch_cg_direction_init(state, r, dg, d, q, ess, n, s2);
+        launch_cg_update(state, partials, dotp, nap, ess != nullptr, x, r, d, q, dg, n, s2);
+        launch_cg_direction(state, partials, r, dg, d, qi, ess, hist, n, s2);
       }
     };
     CapturedGraph graph;
@@ -761,7 +756,7 @@ IRLayout ir_layout(const Op& hi, const Op& lo) {
   size_t o = 0;
   L.state_hi = o; o += align256(sizeof(CGState));
   L.state_lo = o; o += align256(sizeof(CGState));
-  L.partials = o; o += align256(4 * kCGBlocks * sizeof(double));
+  L.partials = o; o += align256(kPartials * kCGBlocks * sizeof(double));
   L.r64 = o; o += align256(n * 8);
   L.q64 = o; o += align256(n * 8);
   L.d32 = o; o += align256(n * 4);
@@ -832,8 +827,6 @@ pafem_status pafem_ir_solve(pafem_op a_hi, pafem_op a_lo, const double* diag, co
     const int check = std::max(1, opts->check_every);
     if (dinv) launch_ir_dinv(diag, dinv, n, st);
     hip_check(hipMemsetAsync(x, 0, size_t(n) * 8, st), "zero x");
-    launch_cg_reset(st_hi, 0, st);
-    launch_cg_reset(st_lo, 0, st);
     // r = b, ||b||
     hip_check(hipMemsetAsync(q64, 0, size_t(n) * 8, st), "zero q");
     launch_residual(st_hi, partials, b, q64, r64, n, st);
@@ -861,9 +854,9 @@ pafem_status pafem_ir_solve(pafem_op a_hi, pafem_op a_lo, const double* diag, co
         const int batch = std::min(check, opts->max_inner - launched);
         for (int k = 0; k < batch; ++k) {
           apply_op(lo, d32, q32, opwork, st, dotp, /*y_ready=*/true);
-          launch_cg_alpha<float>(st_lo, partials, dotp, nap, ess, d32, n, st);
-          launch_ir_update(st_lo, partials, x, s, r64, d32, q32, dinv, n, st);
-          launch_ir_direction(st_lo, r64, dinv, d32, q32, ess, n, st);
+          launch_ir_update(st_lo, partials, dotp, nap, ess != nullptr, x, s, r64, d32, q32, dinv,
+                           n, st);
+          launch_ir_direction(st_lo, partials, false, r64, dinv, d32, q32, ess, n, st);
         }
         launched += batch;
       }
@@ -886,7 +879,7 @@ pafem_status pafem_ir_solve(pafem_op a_hi, pafem_op a_lo, const double* diag, co
       restart = !(opts->keep_direction && hl.done == 1);
       if (!restart) {
         launch_ir_replace(st_lo, partials, r64, s_new, dinv, d32, q32, opts->inner_rel_tol, n, st);
-        launch_ir_direction(st_lo, r64, dinv, d32, q32, ess, n, st);
+        launch_ir_direction(st_lo, partials, true, r64, dinv, d32, q32, ess, n, st);
       }
       s = s_new;
     }

@@ -108,6 +108,26 @@ __device__ __forceinline__ double block_sum(double v, double* scratch) {
   return t;
 }
 
+// Two block sums at once; `scratch` holds 2 * blockDim.x / 64 doubles.  Totals in every
+// thread.  Contains __syncthreads().
+__device__ __forceinline__ void block_sum2(double& a, double& b, double* scratch) {
+  const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
+  const int nw = (blockDim.x + kWave - 1) / kWave;
+  a = wave_sum(a);
+  b = wave_sum(b);
+  if (lane == 0) {
+    scratch[2 * wid] = a;
+    scratch[2 * wid + 1] = b;
+  }
+  __syncthreads();
+  a = b = 0.0;
+  for (int w = 0; w < nw; ++w) {
+    a += scratch[2 * w];
+    b += scratch[2 * w + 1];
+  }
+  __syncthreads();
+}
+
 // ---- deterministic grid reductions -------------------------------------------
 // Each block stores one partial per quantity; the last block to arrive (atomic
 // ticket) sums all partials in index order.

@@ -3,11 +3,18 @@
 // run on the device because they are written with Vector operations, "GPU
 // Acceleration").
 //
-// Each kernel is a fixed grid of kCGBlocks x kCGThreads threads (one workgroup per
-// compute unit, so the last-block ticket sees few same-address atomics) striding over
-// the vectors.  Dot products: wave64 butterfly -> per-wave LDS -> per-block
-// partial; the last block to arrive (atomic ticket) sums the partials in index
-// order and updates the scalars, so results do not depend on scheduling.
+// Each kernel is a grid of at most kCGBlocks x kCGThreads threads (one workgroup per
+// compute unit) striding over the vectors.  Dot products: wave64 butterfly -> per-wave
+// LDS -> one partial per workgroup, stored plainly; every workgroup of the next kernel
+// of the iteration sums the (at most kCGBlocks) partials itself, in the same order, and
+// so knows alpha, beta and convergence without another launch.  The first workgroup
+// writes the scalars that the host or a later kernel reads.  Results do not depend on
+// scheduling.  (A last-arriver reduction inside the kernel cost more than the vectors:
+// its ticket and the device-wide fences, which write back the L2 of each die, took 10 us
+// of a 14 us update on 4913 dofs, and the separate step-length kernel 12 us; with three
+// kernels instead of four the iteration there went from 40 to 23 us, and at 1.3M dofs in
+// 2D from 75 to 57 us.)
+#include <algorithm>
 #include <cmath>
 
 #include "device.hpp"
@@ -29,195 +36,265 @@ __device__ __forceinline__ bool state_done(const CGState* st) {
   for (int64_t i = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; i < (n);    \
        i += int64_t(gridDim.x) * blockDim.x)
 
-__global__ void cg_reset_kernel(CGState* st, int32_t max_hist) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    st->rz = st->alpha = st->beta = st->rr = st->bb = st->tol2 = st->res2 = 0.0;
-    st->iter = 0;
-    st->done = 0;
-    st->max_hist = max_hist;
-    for (int i = 0; i < 8; ++i) st->ticket[i] = 0u;
-  }
+// Sum of a[0], a[stride], ... (n of them) over this thread's share; the block sum of it
+// has a fixed order.
+__device__ __forceinline__ double strided_share(const double* a, int n, int stride) {
+  double v = 0.0;
+#pragma unroll 4
+  for (int i = threadIdx.x; i < n; i += kCGThreads) v += a[size_t(i) * stride];
+  return v;
 }
 
-template <typename TB, typename TV>
+__device__ __forceinline__ void finish_done(CGState* st, int done) {
+  __hip_atomic_store(&st->done, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// ---- one-workgroup kernels that turn partials into state --------------------
+// (a solve's start and end; inside an iteration every workgroup of the next vector
+// kernel sums the partials itself)
+
+// p0 rz, p1 rr, p3 bb: start of a solve
 __global__ void __launch_bounds__(kCGThreads)
-    cg_init_kernel(CGState* st, double* partials, const TB* __restrict__ b, double bscale,
-                   const TV* __restrict__ q, const TV* __restrict__ diag, TV* __restrict__ x,
-                   TV* __restrict__ r, TV* __restrict__ d, int zero_guess, double rel_tol,
-                   double* hist, int64_t n) {
-  __shared__ double scratch[kCGThreads / kWave];
-  double rz = 0.0, rr = 0.0, bb = 0.0;
-  GRID_LOOP(i, n) {
-    const double bi = double(b[i]) * bscale;
-    const TV ri = TV(q ? bi - double(q[i]) : bi);
-    if (zero_guess) x[i] = TV(0);
-    const TV zi = diag ? ri / diag[i] : ri;
-    r[i] = ri;
-    d[i] = zi;
-    rz += double(ri) * double(zi);
-    rr += double(ri) * double(ri);
-    bb += bi * bi;
-  }
-  double* p0 = partials;
-  double* p1 = partials + kCGBlocks;
-  double* p2 = partials + 2 * kCGBlocks;
+    cg_start_finish_kernel(CGState* st, const double* partials, int nb, double rel_tol,
+                           int32_t max_hist, double* hist, int flexible) {
+  __shared__ double scratch[2 * kCGThreads / kWave];
+  double rr = strided_share(partials + kCGBlocks, nb, 1);
+  double bb = strided_share(partials + 3 * kCGBlocks, nb, 1);
+  block_sum2(rr, bb, scratch);
+  double rz = flexible ? 0.0 : strided_share(partials, nb, 1);
   rz = block_sum(rz, scratch);
-  rr = block_sum(rr, scratch);
-  bb = block_sum(bb, scratch);
   if (threadIdx.x == 0) {
-    store_partial(p0, rz);
-    store_partial(p1, rr);
-    store_partial(p2, bb);
-  }
-  if (!arrive_last(&st->ticket[0])) return;
-  const double trz = sum_partials(p0, scratch);
-  const double trr = sum_partials(p1, scratch);
-  const double tbb = sum_partials(p2, scratch);
-  if (threadIdx.x == 0) {
-    st->rz = trz;
-    st->rr = trr;
     // reference of the relative stop: ||b||^2, or ||r_0||^2 when b = 0 (the answer is
     // then x = 0 and the iteration reduces the initial residual; both 0: done)
-    const double ref = tbb > 0.0 ? tbb : trr;
+    const double ref = bb > 0.0 ? bb : rr;
+    st->rr = rr;
     st->bb = ref;
     st->tol2 = rel_tol * rel_tol * ref;
+    if (!flexible) {
+      st->rz = rz;
+      st->alpha = st->beta = 0.0;
+      st->res2 = 0.0;
+    }
+    if (max_hist >= 0) {  // negative: keep counting (restart inside a solve)
+      st->iter = 0;
+      st->max_hist = max_hist;
+    }
+    if (hist && st->max_hist > 0) hist[0] = ref > 0.0 ? sqrt(rr / ref) : 0.0;
+    finish_done(st, rr <= st->tol2 ? 1 : 0);
+  }
+}
+
+// p0 rz of the first preconditioned residual of flexible CG: must be > 0
+__global__ void __launch_bounds__(kCGThreads)
+    fcg_start_finish_kernel(CGState* st, const double* partials, int nb) {
+  __shared__ double scratch[kCGThreads / kWave];
+  if (state_done(st)) return;
+  const double rz = block_sum(strided_share(partials, nb, 1), scratch);
+  if (threadIdx.x == 0) {
+    st->rz = rz;
+    if (!(rz > 0.0) || !isfinite(rz)) finish_done(st, 3);
+  }
+}
+
+__global__ void __launch_bounds__(kCGThreads)
+    residual_finish_kernel(CGState* st, const double* partials, int nb) {
+  __shared__ double scratch[kCGThreads / kWave];
+  const double s = block_sum(strided_share(partials, nb, 1), scratch);
+  if (threadIdx.x == 0) st->res2 = s;
+}
+
+// p0 rz, p1 rr of the (re)started inner PCG
+__global__ void __launch_bounds__(kCGThreads)
+    ir_start_finish_kernel(CGState* st, const double* partials, int nb, double inner_rel_tol) {
+  __shared__ double scratch[2 * kCGThreads / kWave];
+  double rz = strided_share(partials, nb, 1), rr = strided_share(partials + kCGBlocks, nb, 1);
+  block_sum2(rz, rr, scratch);
+  if (threadIdx.x == 0) {
+    st->rz = rz;
+    st->rr = rr;
+    st->bb = rr;
+    st->tol2 = inner_rel_tol * inner_rel_tol * rr;
     st->iter = 0;
     st->alpha = st->beta = 0.0;
-    st->res2 = 0.0;
-    const int conv = trr <= st->tol2;
-    if (hist && st->max_hist > 0) hist[0] = ref > 0.0 ? sqrt(trr / ref) : 0.0;
-    __hip_atomic_store(&st->done, conv ? 1 : 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&st->ticket[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    finish_done(st, rr > 0.0 ? 0 : 1);
   }
 }
 
-// alpha = rz / (d . q) with d . q assembled from the apply's per-workgroup element
-// energies plus, for a constrained operator, the essential rows (q_b = d_b there):
-// d . q = sum(epart) + sum over essential b of d_b^2.  The mask is read eight
-// entries at a time; entries at or beyond n are never used.
-template <typename TV>
+// p0 rz, p1 rr, p2 z.q, p3 d.q after a residual replacement
 __global__ void __launch_bounds__(kCGThreads)
-    cg_alpha_kernel(CGState* st, double* partials, const double* __restrict__ epart,
-                    int nepart, const uint8_t* __restrict__ bmask, const TV* __restrict__ d,
-                    int64_t n) {
-  __shared__ double scratch[kCGThreads / kWave];
-  if (state_done(st)) return;
-  const int64_t tid = blockIdx.x * int64_t(blockDim.x) + threadIdx.x;
-  const int64_t nthr = int64_t(gridDim.x) * blockDim.x;
-  double s = 0.0;
-  for (int64_t i = tid; i < nepart; i += nthr) s += epart[i];
-  if (bmask) {
-    const int64_t nw = n / 8;
-    const uint64_t* mw = reinterpret_cast<const uint64_t*>(bmask);
-    for (int64_t w = tid; w < nw; w += nthr) {
-      uint64_t m = mw[w];
-      while (m) {
-        const int b = __builtin_ctzll(m) >> 3;
-        const double v = double(d[w * 8 + b]);
-        s += v * v;
-        m &= ~(uint64_t(0xff) << (8 * b));
-      }
-    }
-    for (int64_t i = nw * 8 + tid; i < n; i += nthr)
-      if (bmask[i]) {
-        const double v = double(d[i]);
-        s += v * v;
-      }
-  }
-  s = block_sum(s, scratch);
-  if (threadIdx.x == 0) store_partial(partials, s);
-  if (!arrive_last(&st->ticket[1])) return;
-  const double pq = sum_partials(partials, scratch);
+    ir_replace_finish_kernel(CGState* st, const double* partials, int nb, double inner_rel_tol) {
+  __shared__ double scratch[2 * kCGThreads / kWave];
+  double rz = strided_share(partials, nb, 1), rr = strided_share(partials + kCGBlocks, nb, 1);
+  block_sum2(rz, rr, scratch);
+  double zq = strided_share(partials + 2 * kCGBlocks, nb, 1);
+  double dq = strided_share(partials + 3 * kCGBlocks, nb, 1);
+  block_sum2(zq, dq, scratch);
   if (threadIdx.x == 0) {
-    const double alpha = st->rz / pq;
-    if (!(pq > 0.0) || !isfinite(alpha))
-      __hip_atomic_store(&st->done, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    st->alpha = alpha;
-    __hip_atomic_store(&st->ticket[1], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-}
-
-template <typename TV>
-__global__ void __launch_bounds__(kCGThreads)
-    cg_update_kernel(CGState* st, double* partials, TV* __restrict__ x, TV* __restrict__ r,
-                     const TV* __restrict__ d, const TV* __restrict__ q,
-                     const TV* __restrict__ diag, double* hist, int64_t n) {
-  __shared__ double scratch[kCGThreads / kWave];
-  if (state_done(st)) return;
-  const TV alpha = TV(st->alpha);
-  double rz = 0.0, rr = 0.0;
-  GRID_LOOP(i, n) {
-    const TV di = d[i];
-    x[i] += alpha * di;
-    const TV ri = r[i] - alpha * q[i];
-    r[i] = ri;
-    const TV zi = diag ? ri / diag[i] : ri;
-    rz += double(ri) * double(zi);
-    rr += double(ri) * double(ri);
-  }
-  double* p0 = partials;
-  double* p1 = partials + kCGBlocks;
-  rz = block_sum(rz, scratch);
-  rr = block_sum(rr, scratch);
-  if (threadIdx.x == 0) {
-    store_partial(p0, rz);
-    store_partial(p1, rr);
-  }
-  if (!arrive_last(&st->ticket[2])) return;
-  const double trz = sum_partials(p0, scratch);
-  const double trr = sum_partials(p1, scratch);
-  if (threadIdx.x == 0) {
-    const double beta = trz / st->rz;
+    const double beta = -zq / dq;
     st->beta = beta;
-    st->rz = trz;
-    st->rr = trr;
+    st->rz = rz;
+    st->rr = rr;
+    st->bb = rr;
+    st->tol2 = inner_rel_tol * inner_rel_tol * rr;
+    finish_done(st, (isfinite(beta) && rz > 0.0 && dq > 0.0) ? 0 : 2);
+  }
+}
+
+// Element energies of an apply over more workgroups than a vector kernel's workgroups
+// should each sum: workgroup b adds the entries of the 64-byte groups b, b + 256, ...
+// into entry 8 b, which no other workgroup reads.
+__global__ void __launch_bounds__(256) fold_kernel(double* __restrict__ e, int n) {
+  __shared__ double scratch[256 / kWave];
+  double v = 0.0;
+#pragma unroll 4
+  for (int64_t k = threadIdx.x / 8; k * (8 * kCGBlocks) < n; k += 32) {
+    const int64_t i = k * (8 * kCGBlocks) + 8 * blockIdx.x + threadIdx.x % 8;
+    if (i < n) v += e[i];
+  }
+  v = block_sum(v, scratch);
+  if (threadIdx.x == 0) e[8 * blockIdx.x] = v;
+}
+
+// alpha = rz / (d . q) in every thread, d . q from the apply's element energies
+// (epart) plus d_b^2 over the essential rows of a constrained operator (q_b = d_b
+// there; pess, written with d).  Returns false on breakdown (done = 2) in every
+// workgroup.  st->rz is written only by direction kernels, rz_old only here.
+__device__ __forceinline__ bool step_length(CGState* st, const EnergyParts& ep,
+                                            const double* pess, int nb, double* scratch,
+                                            double& alpha) {
+  double s = strided_share(ep.e, ep.n, ep.stride);
+  if (pess) s += strided_share(pess, nb, 1);
+  const double pq = block_sum(s, scratch);
+  const double rz = st->rz;
+  alpha = rz / pq;
+  const bool ok = pq > 0.0 && isfinite(alpha);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->rz_old = rz;
+    st->alpha = alpha;
+    if (!ok) finish_done(st, 2);
+  }
+  return ok;
+}
+
+// Writes this block's partials of two sums (p0, p1).
+__device__ __forceinline__ void put_partials2(double a, double b, double* p0, double* p1,
+                                              double* scratch) {
+  block_sum2(a, b, scratch);
+  if (threadIdx.x == 0) {
+    p0[blockIdx.x] = a;
+    p1[blockIdx.x] = b;
+  }
+}
+
+// State after an update: convergence on rr, history, iteration count.  Same decision
+// in every workgroup, written by the first; returns true when the iteration stops.
+__device__ __forceinline__ bool close_update(CGState* st, double rr, bool broken, double* hist) {
+  const int done = (!isfinite(rr) || broken) ? 2 : rr <= st->tol2 ? 1 : 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->rr = rr;
     const int it = st->iter + 1;
     st->iter = it;
-    if (hist && it < st->max_hist) hist[it] = sqrt(trr / st->bb);
-    int done = 0;
-    if (!isfinite(trr) || !isfinite(beta)) done = 2;
-    else if (trr <= st->tol2) done = 1;
-    if (done) __hip_atomic_store(&st->done, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&st->ticket[2], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (hist && it < st->max_hist) hist[it] = sqrt(rr / st->bb);
+    if (done) finish_done(st, done);
   }
+  return done != 0;
 }
 
-template <typename TV>
+// r = b - q (q may be null: r = b), d = z = r / diag, x = 0 if zero_guess; partials
+// rz, rr, bb and d_b^2 (p2); qi (may be null, may be q): the first apply's init of d
 __global__ void __launch_bounds__(kCGThreads)
-    cg_direction_kernel(const CGState* st, const TV* __restrict__ r,
-                        const TV* __restrict__ diag, TV* __restrict__ d, int64_t n) {
-  if (state_done(st)) return;
-  const TV beta = TV(st->beta);
+    cg_init_kernel(double* partials, const double* __restrict__ b, const double* q,
+                   const double* __restrict__ diag, double* __restrict__ x,
+                   double* __restrict__ r, double* __restrict__ d, double* qi,
+                   const uint8_t* __restrict__ bmask, int zero_guess, int64_t n) {
+  __shared__ double scratch[2 * kCGThreads / kWave];
+  double rz = 0.0, rr = 0.0, bb = 0.0, ess = 0.0;
   GRID_LOOP(i, n) {
-    const TV zi = diag ? r[i] / diag[i] : r[i];
-    d[i] = zi + beta * d[i];
+    const double bi = b[i];
+    const double ri = q ? bi - q[i] : bi;
+    if (zero_guess) x[i] = 0.0;
+    const double zi = diag ? ri / diag[i] : ri;
+    r[i] = ri;
+    d[i] = zi;
+    const bool e = bmask && bmask[i];
+    if (qi) qi[i] = e ? zi : 0.0;
+    if (e) ess += zi * zi;
+    rz += ri * zi;
+    rr += ri * ri;
+    bb += bi * bi;
   }
+  put_partials2(rz, rr, partials, partials + kCGBlocks, scratch);
+  put_partials2(ess, bb, partials + 2 * kCGBlocks, partials + 3 * kCGBlocks, scratch);
 }
 
-// d = r / diag + beta d, and q = the next apply's init: d on essential dofs of a
-// constrained operator (bmask non-null), 0 elsewhere
+// x += alpha d; r -= alpha q; partials of rz and rr
 __global__ void __launch_bounds__(kCGThreads)
-    cg_direction_init_kernel(const CGState* st, const double* __restrict__ r,
-                             const double* __restrict__ diag, double* __restrict__ d,
-                             double* __restrict__ q, const uint8_t* __restrict__ bmask,
-                             int64_t n) {
+    cg_update_kernel(CGState* st, EnergyParts ep, double* partials, int has_ess,
+                     double* __restrict__ x, double* __restrict__ r,
+                     const double* __restrict__ d, const double* __restrict__ q,
+                     const double* __restrict__ diag, int64_t n) {
+  __shared__ double scratch[2 * kCGThreads / kWave];
   if (state_done(st)) return;
-  const double beta = st->beta;
+  double alpha;
+  if (!step_length(st, ep, has_ess ? partials + 2 * kCGBlocks : nullptr, gridDim.x, scratch,
+                   alpha))
+    return;
+  double rz = 0.0, rr = 0.0;
+  GRID_LOOP(i, n) {
+    const double di = d[i];
+    x[i] += alpha * di;
+    const double ri = r[i] - alpha * q[i];
+    r[i] = ri;
+    const double zi = diag ? ri / diag[i] : ri;
+    rz += ri * zi;
+    rr += ri * ri;
+  }
+  put_partials2(rz, rr, partials, partials + kCGBlocks, scratch);
+}
+
+// beta = rz / rz_old, state; d = r / diag + beta d; partials of d_b^2; q (null: the
+// apply needs no init) = the next apply's init: d on essential dofs of a constrained
+// operator (bmask non-null), 0 elsewhere
+__global__ void __launch_bounds__(kCGThreads)
+    cg_direction_kernel(CGState* st, double* partials, const double* __restrict__ r,
+                        const double* __restrict__ diag, double* __restrict__ d,
+                        double* __restrict__ q, const uint8_t* __restrict__ bmask, double* hist,
+                        int64_t n) {
+  __shared__ double scratch[2 * kCGThreads / kWave];
+  if (state_done(st)) return;
+  double rz = strided_share(partials, gridDim.x, 1);
+  double rr = strided_share(partials + kCGBlocks, gridDim.x, 1);
+  block_sum2(rz, rr, scratch);
+  const double beta = rz / st->rz_old;
+  if (close_update(st, rr, !isfinite(beta), hist)) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->rz = rz;
+    return;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->rz = rz;
+    st->beta = beta;
+  }
+  double ess = 0.0;
   GRID_LOOP(i, n) {
     const double zi = diag ? r[i] / diag[i] : r[i];
     const double di = zi + beta * d[i];
     d[i] = di;
-    q[i] = (bmask && bmask[i]) ? di : 0.0;
+    const bool e = bmask && bmask[i];
+    if (q) q[i] = e ? di : 0.0;
+    if (e) ess += di * di;
+  }
+  if (bmask) {
+    ess = block_sum(ess, scratch);
+    if (threadIdx.x == 0) partials[2 * kCGBlocks + blockIdx.x] = ess;
   }
 }
 
 // ---- flexible CG (variable preconditioner) ----
-// r = b - q (q may be null), x = 0 if zero_guess; rr, bb, tol2; iteration count kept
+// r = b - q (q may be null), x = 0 if zero_guess; partials rr, bb
 __global__ void __launch_bounds__(kCGThreads)
-    fcg_init_kernel(CGState* st, double* partials, const double* __restrict__ b,
-                    const double* __restrict__ q, double* __restrict__ x, double* __restrict__ r,
-                    int zero_guess, double rel_tol, double* hist, int64_t n) {
-  __shared__ double scratch[kCGThreads / kWave];
+    fcg_init_kernel(double* partials, const double* __restrict__ b, const double* __restrict__ q,
+                    double* __restrict__ x, double* __restrict__ r, int zero_guess, int64_t n) {
+  __shared__ double scratch[2 * kCGThreads / kWave];
   double rr = 0.0, bb = 0.0;
   GRID_LOOP(i, n) {
     const double bi = b[i];
@@ -227,62 +304,40 @@ __global__ void __launch_bounds__(kCGThreads)
     rr += ri * ri;
     bb += bi * bi;
   }
-  rr = block_sum(rr, scratch);
-  bb = block_sum(bb, scratch);
-  if (threadIdx.x == 0) {
-    store_partial(partials, rr);
-    store_partial(partials + kCGBlocks, bb);
-  }
-  if (!arrive_last(&st->ticket[0])) return;
-  const double trr = sum_partials(partials, scratch);
-  const double tbb = sum_partials(partials + kCGBlocks, scratch);
-  if (threadIdx.x == 0) {
-    st->rr = trr;
-    const double ref = tbb > 0.0 ? tbb : trr;  // as in cg_init_kernel
-    st->bb = ref;
-    st->tol2 = rel_tol * rel_tol * ref;
-    const int conv = trr <= st->tol2;
-    if (hist && st->max_hist > 0) hist[0] = ref > 0.0 ? sqrt(trr / ref) : 0.0;
-    __hip_atomic_store(&st->done, conv ? 1 : 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&st->ticket[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  put_partials2(rr, bb, partials + kCGBlocks, partials + 3 * kCGBlocks, scratch);
 }
 
-// rz = r . z (must be > 0: otherwise done = 3, the preconditioner is not positive); p = z
+// p = z; partials of r . z and p_b^2; q = the apply's init of p (null: none)
 __global__ void __launch_bounds__(kCGThreads)
-    fcg_start_kernel(CGState* st, double* partials, const double* __restrict__ r,
-                     const double* __restrict__ z, double* __restrict__ p, int64_t n) {
-  __shared__ double scratch[kCGThreads / kWave];
+    fcg_start_kernel(const CGState* st, double* partials, const double* __restrict__ r,
+                     const double* __restrict__ z, double* __restrict__ p,
+                     double* __restrict__ q, const uint8_t* __restrict__ bmask, int64_t n) {
+  __shared__ double scratch[2 * kCGThreads / kWave];
   if (state_done(st)) return;
-  double rz = 0.0;
+  double rz = 0.0, ess = 0.0;
   GRID_LOOP(i, n) {
     const double zi = z[i];
     p[i] = zi;
+    const bool e = bmask && bmask[i];
+    if (q) q[i] = e ? zi : 0.0;
+    if (e) ess += zi * zi;
     rz += r[i] * zi;
   }
-  rz = block_sum(rz, scratch);
-  if (threadIdx.x == 0) store_partial(partials, rz);
-  if (!arrive_last(&st->ticket[4])) return;
-  const double t = sum_partials(partials, scratch);
-  if (threadIdx.x == 0) {
-    st->rz = t;
-    if (!(t > 0.0) || !isfinite(t))
-      __hip_atomic_store(&st->done, 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&st->ticket[4], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  put_partials2(rz, ess, partials, partials + 2 * kCGBlocks, scratch);
 }
 
-// x += alpha p; r -= alpha q; zj = r / diag (0 on essential dofs: the Jacobi part of
-// the next preconditioned residual); rr, iteration count, history, convergence
+// x += alpha p; r -= alpha q; zj = r / diag (r on essential dofs: the Jacobi part of
+// the next preconditioned residual); partials of rr
 __global__ void __launch_bounds__(kCGThreads)
-    fcg_update_kernel(CGState* st, double* partials, double* __restrict__ x,
+    fcg_update_kernel(CGState* st, EnergyParts ep, double* partials, double* __restrict__ x,
                       double* __restrict__ r, const double* __restrict__ p,
                       const double* __restrict__ q, const double* __restrict__ diag,
-                      const uint8_t* __restrict__ bmask, double* __restrict__ zj, double* hist,
-                      int64_t n) {
+                      const uint8_t* __restrict__ bmask, double* __restrict__ zj, int64_t n) {
   __shared__ double scratch[kCGThreads / kWave];
   if (state_done(st)) return;
-  const double alpha = st->alpha;
+  double alpha;
+  if (!step_length(st, ep, bmask ? partials + 2 * kCGBlocks : nullptr, gridDim.x, scratch, alpha))
+    return;
   double rr = 0.0;
   GRID_LOOP(i, n) {
     x[i] += alpha * p[i];
@@ -292,64 +347,63 @@ __global__ void __launch_bounds__(kCGThreads)
     rr += ri * ri;
   }
   rr = block_sum(rr, scratch);
-  if (threadIdx.x == 0) store_partial(partials, rr);
-  if (!arrive_last(&st->ticket[2])) return;
-  const double t = sum_partials(partials, scratch);
-  if (threadIdx.x == 0) {
-    st->rr = t;
-    const int it = st->iter + 1;
-    st->iter = it;
-    if (hist && it < st->max_hist) hist[it] = sqrt(t / st->bb);
-    int done = 0;
-    if (!isfinite(t)) done = 2;
-    else if (t <= st->tol2) done = 1;
-    if (done) __hip_atomic_store(&st->done, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&st->ticket[2], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  if (threadIdx.x == 0) partials[kCGBlocks + blockIdx.x] = rr;
 }
 
-// beta = r.(z - z_old) / rz_old (Polak-Ribiere); rz = r.z (> 0 else done = 3)
+// state after the update; partials of r . z (p0) and r . z_old (p3)
 __global__ void __launch_bounds__(kCGThreads)
     fcg_beta_kernel(CGState* st, double* partials, const double* __restrict__ r,
-                    const double* __restrict__ z, const double* __restrict__ zold, int64_t n) {
-  __shared__ double scratch[kCGThreads / kWave];
+                    const double* __restrict__ z, const double* __restrict__ zold, double* hist,
+                    int64_t n) {
+  __shared__ double scratch[2 * kCGThreads / kWave];
   if (state_done(st)) return;
+  const double rr = block_sum(strided_share(partials + kCGBlocks, gridDim.x, 1), scratch);
+  if (close_update(st, rr, false, hist)) return;
   double rz = 0.0, rzo = 0.0;
   GRID_LOOP(i, n) {
     const double ri = r[i];
     rz += ri * z[i];
     rzo += ri * zold[i];
   }
-  rz = block_sum(rz, scratch);
-  rzo = block_sum(rzo, scratch);
-  if (threadIdx.x == 0) {
-    store_partial(partials, rz);
-    store_partial(partials + kCGBlocks, rzo);
-  }
-  if (!arrive_last(&st->ticket[5])) return;
-  const double trz = sum_partials(partials, scratch);
-  const double trzo = sum_partials(partials + kCGBlocks, scratch);
-  if (threadIdx.x == 0) {
-    st->beta = (trz - trzo) / st->rz;
-    st->rz = trz;
-    if (!(trz > 0.0) || !isfinite(st->beta))
-      __hip_atomic_store(&st->done, 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&st->ticket[5], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  put_partials2(rz, rzo, partials, partials + 3 * kCGBlocks, scratch);
 }
 
-// p = z + beta p
+// beta = r.(z - z_old) / rz_old (Polak-Ribiere; r.z > 0 else done = 3); p = z + beta p;
+// q = the next apply's init of p (null: none)
 __global__ void __launch_bounds__(kCGThreads)
-    fcg_direction_kernel(const CGState* st, const double* __restrict__ z, double* __restrict__ p,
-                         int64_t n) {
+    fcg_direction_kernel(CGState* st, double* partials, const double* __restrict__ z,
+                         double* __restrict__ p, double* __restrict__ q,
+                         const uint8_t* __restrict__ bmask, int64_t n) {
+  __shared__ double scratch[2 * kCGThreads / kWave];
   if (state_done(st)) return;
-  const double beta = st->beta;
-  GRID_LOOP(i, n) p[i] = z[i] + beta * p[i];
+  double rz = strided_share(partials, gridDim.x, 1);
+  double rzo = strided_share(partials + 3 * kCGBlocks, gridDim.x, 1);
+  block_sum2(rz, rzo, scratch);
+  const double beta = (rz - rzo) / st->rz_old;
+  const bool ok = rz > 0.0 && isfinite(beta);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->beta = beta;
+    st->rz = rz;
+    if (!ok) finish_done(st, 3);
+  }
+  if (!ok) return;
+  double ess = 0.0;
+  GRID_LOOP(i, n) {
+    const double pi = z[i] + beta * p[i];
+    p[i] = pi;
+    const bool e = bmask && bmask[i];
+    if (q) q[i] = e ? pi : 0.0;
+    if (e) ess += pi * pi;
+  }
+  if (bmask) {
+    ess = block_sum(ess, scratch);
+    if (threadIdx.x == 0) partials[2 * kCGBlocks + blockIdx.x] = ess;
+  }
 }
 
 __global__ void __launch_bounds__(kCGThreads)
-    residual_kernel(CGState* st, double* partials, const double* __restrict__ b,
-                    const double* __restrict__ q, double* __restrict__ r, int64_t n) {
+    residual_kernel(double* partials, const double* __restrict__ b, const double* __restrict__ q,
+                    double* __restrict__ r, int64_t n) {
   __shared__ double scratch[kCGThreads / kWave];
   double s = 0.0;
   GRID_LOOP(i, n) {
@@ -358,15 +412,8 @@ __global__ void __launch_bounds__(kCGThreads)
     s += v * v;
   }
   s = block_sum(s, scratch);
-  if (threadIdx.x == 0) store_partial(partials, s);
-  if (!arrive_last(&st->ticket[3])) return;
-  const double t = sum_partials(partials, scratch);
-  if (threadIdx.x == 0) {
-    st->res2 = t;
-    __hip_atomic_store(&st->ticket[3], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
-
 
 // ---- inner PCG of iterative refinement --------------------------------------
 // The inner solve of A_lo d = r / s keeps its residual r, the preconditioned
@@ -381,54 +428,43 @@ __device__ __forceinline__ double ir_z(const double* r, const float* dinv, int64
   return dinv ? r[i] * double(dinv[i]) : r[i];
 }
 
-// r *= inv_s (r holds the FP64 residual), d = z, q = apply init of d;
-// rz, rr, bb = rr, tol2 = inner_rel_tol^2 rr, iter = 0, done
+// r *= inv_s (r holds the FP64 residual), d = z, q = apply init of d; partials of rz,
+// rr and d_b^2
 __global__ void __launch_bounds__(kCGThreads)
-    ir_start_kernel(CGState* st, double* partials, double* __restrict__ r, double inv_s,
+    ir_start_kernel(double* partials, double* __restrict__ r, double inv_s,
                     const float* __restrict__ dinv, float* __restrict__ d, float* __restrict__ q,
-                    const uint8_t* __restrict__ ess, double inner_rel_tol, int64_t n) {
-  __shared__ double scratch[kCGThreads / kWave];
-  double rz = 0.0, rr = 0.0;
+                    const uint8_t* __restrict__ ess, int64_t n) {
+  __shared__ double scratch[2 * kCGThreads / kWave];
+  double rz = 0.0, rr = 0.0, de = 0.0;
   GRID_LOOP(i, n) {
     const double ri = r[i] * inv_s;
     r[i] = ri;
     const double zi = dinv ? ri * double(dinv[i]) : ri;
     const float di = float(zi);
     d[i] = di;
-    q[i] = (ess && ess[i]) ? di : 0.0f;
+    const bool e = ess && ess[i];
+    q[i] = e ? di : 0.0f;
+    if (e) de += double(di) * double(di);
     rz += ri * zi;
     rr += ri * ri;
   }
-  rz = block_sum(rz, scratch);
-  rr = block_sum(rr, scratch);
-  if (threadIdx.x == 0) {
-    store_partial(partials, rz);
-    store_partial(partials + kCGBlocks, rr);
-  }
-  if (!arrive_last(&st->ticket[0])) return;
-  const double trz = sum_partials(partials, scratch);
-  const double trr = sum_partials(partials + kCGBlocks, scratch);
-  if (threadIdx.x == 0) {
-    st->rz = trz;
-    st->rr = trr;
-    st->bb = trr;
-    st->tol2 = inner_rel_tol * inner_rel_tol * trr;
-    st->iter = 0;
-    st->alpha = st->beta = 0.0;
-    const int done = trr > 0.0 ? 0 : 1;
-    __hip_atomic_store(&st->done, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&st->ticket[0], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  put_partials2(rz, rr, partials, partials + kCGBlocks, scratch);
+  de = block_sum(de, scratch);
+  if (threadIdx.x == 0) partials[2 * kCGBlocks + blockIdx.x] = de;
 }
 
-// x += (s alpha) d; r -= alpha q (FP64); rz, rr, beta = rz / rz_old, iter, convergence
+// x += (s alpha) d; r -= alpha q (FP64); partials of rz and rr
 __global__ void __launch_bounds__(kCGThreads)
-    ir_update_kernel(CGState* st, double* partials, double* __restrict__ x, double s,
-                     double* __restrict__ r, const float* __restrict__ d,
-                     const float* __restrict__ q, const float* __restrict__ dinv, int64_t n) {
-  __shared__ double scratch[kCGThreads / kWave];
+    ir_update_kernel(CGState* st, EnergyParts ep, double* partials, int has_ess,
+                     double* __restrict__ x, double s, double* __restrict__ r,
+                     const float* __restrict__ d, const float* __restrict__ q,
+                     const float* __restrict__ dinv, int64_t n) {
+  __shared__ double scratch[2 * kCGThreads / kWave];
   if (state_done(st)) return;
-  const double alpha = st->alpha;
+  double alpha;
+  if (!step_length(st, ep, has_ess ? partials + 2 * kCGBlocks : nullptr, gridDim.x, scratch,
+                   alpha))
+    return;
   const double xstep = s * alpha;
   double rz = 0.0, rr = 0.0;
   GRID_LOOP(i, n) {
@@ -439,40 +475,41 @@ __global__ void __launch_bounds__(kCGThreads)
     rz += ri * zi;
     rr += ri * ri;
   }
-  rz = block_sum(rz, scratch);
-  rr = block_sum(rr, scratch);
-  if (threadIdx.x == 0) {
-    store_partial(partials, rz);
-    store_partial(partials + kCGBlocks, rr);
-  }
-  if (!arrive_last(&st->ticket[2])) return;
-  const double trz = sum_partials(partials, scratch);
-  const double trr = sum_partials(partials + kCGBlocks, scratch);
-  if (threadIdx.x == 0) {
-    const double beta = trz / st->rz;
-    st->beta = beta;
-    st->rz = trz;
-    st->rr = trr;
-    st->iter = st->iter + 1;
-    int done = 0;
-    if (!isfinite(trr) || !isfinite(beta)) done = 2;
-    else if (trr <= st->tol2) done = 1;
-    if (done) __hip_atomic_store(&st->done, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&st->ticket[2], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  put_partials2(rz, rr, partials, partials + kCGBlocks, scratch);
 }
 
-// d = z + beta d (stored FP32), q = apply init of the new d
+// d = z + beta d (stored FP32), q = apply init of the new d; partials of d_b^2.
+// beta and the state as in cg_direction_kernel, or (replaced) the beta that the
+// residual replacement left in the state.
 __global__ void __launch_bounds__(kCGThreads)
-    ir_direction_kernel(const CGState* st, const double* __restrict__ r,
+    ir_direction_kernel(CGState* st, double* partials, int replaced, const double* __restrict__ r,
                         const float* __restrict__ dinv, float* __restrict__ d,
                         float* __restrict__ q, const uint8_t* __restrict__ ess, int64_t n) {
+  __shared__ double scratch[2 * kCGThreads / kWave];
   if (state_done(st)) return;
-  const double beta = st->beta;
+  double beta;
+  if (replaced) {
+    beta = st->beta;
+  } else {
+    double rz = strided_share(partials, gridDim.x, 1);
+    double rr = strided_share(partials + kCGBlocks, gridDim.x, 1);
+    block_sum2(rz, rr, scratch);
+    beta = rz / st->rz_old;
+    const bool stop = close_update(st, rr, !isfinite(beta), nullptr);
+    if (blockIdx.x == 0 && threadIdx.x == 0) st->rz = rz;
+    if (stop) return;
+  }
+  double de = 0.0;
   GRID_LOOP(i, n) {
     const float di = float(ir_z(r, dinv, i) + beta * double(d[i]));
     d[i] = di;
-    q[i] = (ess && ess[i]) ? di : 0.0f;
+    const bool e = ess && ess[i];
+    q[i] = e ? di : 0.0f;
+    if (e) de += double(di) * double(di);
+  }
+  if (ess) {
+    de = block_sum(de, scratch);
+    if (threadIdx.x == 0) partials[2 * kCGBlocks + blockIdx.x] = de;
   }
 }
 
@@ -483,10 +520,10 @@ __global__ void __launch_bounds__(kCGThreads)
 // is the usual beta in the new scaling (times s_old / s_new for the kept direction);
 // with a replaced residual it keeps at least the last direction conjugate.
 __global__ void __launch_bounds__(kCGThreads)
-    ir_replace_kernel(CGState* st, double* partials, double* __restrict__ r, double inv_s_new,
+    ir_replace_kernel(double* partials, double* __restrict__ r, double inv_s_new,
                       const float* __restrict__ dinv, const float* __restrict__ d,
-                      const float* __restrict__ q, double inner_rel_tol, int64_t n) {
-  __shared__ double scratch[kCGThreads / kWave];
+                      const float* __restrict__ q, int64_t n) {
+  __shared__ double scratch[2 * kCGThreads / kWave];
   double rz = 0.0, rr = 0.0, zq = 0.0, dq = 0.0;
   GRID_LOOP(i, n) {
     const double ri = r[i] * inv_s_new;
@@ -498,32 +535,8 @@ __global__ void __launch_bounds__(kCGThreads)
     zq += zi * qi;
     dq += double(d[i]) * qi;
   }
-  rz = block_sum(rz, scratch);
-  rr = block_sum(rr, scratch);
-  zq = block_sum(zq, scratch);
-  dq = block_sum(dq, scratch);
-  if (threadIdx.x == 0) {
-    store_partial(partials, rz);
-    store_partial(partials + kCGBlocks, rr);
-    store_partial(partials + 2 * kCGBlocks, zq);
-    store_partial(partials + 3 * kCGBlocks, dq);
-  }
-  if (!arrive_last(&st->ticket[6])) return;
-  const double trz = sum_partials(partials, scratch);
-  const double trr = sum_partials(partials + kCGBlocks, scratch);
-  const double tzq = sum_partials(partials + 2 * kCGBlocks, scratch);
-  const double tdq = sum_partials(partials + 3 * kCGBlocks, scratch);
-  if (threadIdx.x == 0) {
-    const double beta = -tzq / tdq;
-    st->beta = beta;
-    st->rz = trz;
-    st->rr = trr;
-    st->bb = trr;
-    st->tol2 = inner_rel_tol * inner_rel_tol * trr;
-    const int done = (isfinite(beta) && trz > 0.0 && tdq > 0.0) ? 0 : 2;
-    __hip_atomic_store(&st->done, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&st->ticket[6], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  put_partials2(rz, rr, partials, partials + kCGBlocks, scratch);
+  put_partials2(zq, dq, partials + 2 * kCGBlocks, partials + 3 * kCGBlocks, scratch);
 }
 
 // dinv = 1 / diag rounded to FP32
@@ -561,134 +574,107 @@ int vec_grid(int64_t n) {
   return int(g < 1 ? 1 : (g > 65536 ? 65536 : g));
 }
 
+// workgroups of a vector kernel, and so partials of each of its sums: one element per
+// thread until every compute unit has a workgroup (a fixed grid would leave most of its
+// workgroups empty on small vectors, where their start and their partials are the time)
+int cg_blocks(int64_t n) {
+  return int(std::min<int64_t>(kCGBlocks, std::max<int64_t>(1, (n + kCGThreads - 1) / kCGThreads)));
+}
+
+#define CG_LAUNCH(kernel, n, s, ...)                                                          \
+  hipLaunchKernelGGL(kernel, dim3(cg_blocks(n)), dim3(kCGThreads), 0, s, __VA_ARGS__);        \
+  check_launch(#kernel)
+#define CG_FINISH(kernel, s, ...)                                                             \
+  hipLaunchKernelGGL(kernel, dim3(1), dim3(kCGThreads), 0, s, __VA_ARGS__);                   \
+  check_launch(#kernel)
+
+EnergyParts energy_parts(double* epart, int nepart, hipStream_t s) {
+  if (nepart <= kFoldAbove) return {epart, nepart, 1};
+  hipLaunchKernelGGL(fold_kernel, dim3(kCGBlocks), dim3(256), 0, s, epart, nepart);
+  check_launch("fold_kernel");
+  return {epart, kCGBlocks, 8};
+}
+
 }  // namespace
 
-void launch_cg_reset(CGState* st, int32_t max_hist, hipStream_t s) {
-  hipLaunchKernelGGL(cg_reset_kernel, dim3(1), dim3(64), 0, s, st, max_hist);
-  check_launch("cg_reset");
-}
-
-template <typename TB, typename TV>
-void launch_cg_init(CGState* st, double* partials, const TB* b, double bscale, const TV* q,
-                    const TV* diag, TV* x, TV* r, TV* d, int zero_guess, double rel_tol,
+void launch_cg_init(CGState* st, double* partials, const double* b, const double* q,
+                    const double* diag, double* x, double* r, double* d, double* qi,
+                    const uint8_t* bmask, int zero_guess, double rel_tol, int32_t max_hist,
                     double* hist, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL((cg_init_kernel<TB, TV>), dim3(kCGBlocks), dim3(kCGThreads), 0, s, st,
-                     partials, b, bscale, q, diag, x, r, d, zero_guess, rel_tol, hist, n);
-  check_launch("cg_init");
+  CG_LAUNCH(cg_init_kernel, n, s, partials, b, q, diag, x, r, d, qi, bmask, zero_guess, n);
+  CG_FINISH(cg_start_finish_kernel, s, st, partials, cg_blocks(n), rel_tol, max_hist, hist, 0);
 }
 
-template <typename TV>
-void launch_cg_alpha(CGState* st, double* partials, const double* epart, int nepart,
-                     const uint8_t* bmask, const TV* d, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL((cg_alpha_kernel<TV>), dim3(kCGBlocks), dim3(kCGThreads), 0, s, st, partials,
-                     epart, nepart, bmask, d, n);
-  check_launch("cg_alpha");
+void launch_cg_update(CGState* st, double* partials, double* epart, int nepart, bool has_ess,
+                      double* x, double* r, const double* d, const double* q, const double* diag,
+                      int64_t n, hipStream_t s) {
+  const EnergyParts ep = energy_parts(epart, nepart, s);
+  CG_LAUNCH(cg_update_kernel, n, s, st, ep, partials, int(has_ess), x, r, d, q, diag, n);
 }
 
-template <typename TV>
-void launch_cg_update(CGState* st, double* partials, TV* x, TV* r, const TV* d, const TV* q,
-                      const TV* diag, double* hist, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL((cg_update_kernel<TV>), dim3(kCGBlocks), dim3(kCGThreads), 0, s, st,
-                     partials, x, r, d, q, diag, hist, n);
-  check_launch("cg_update");
-}
-
-template <typename TV>
-void launch_cg_direction(CGState* st, const TV* r, const TV* diag, TV* d, int64_t n,
+void launch_cg_direction(CGState* st, double* partials, const double* r, const double* diag,
+                         double* d, double* q, const uint8_t* bmask, double* hist, int64_t n,
                          hipStream_t s) {
-  hipLaunchKernelGGL((cg_direction_kernel<TV>), dim3(kCGBlocks), dim3(kCGThreads), 0, s, st, r,
-                     diag, d, n);
-  check_launch("cg_direction");
+  CG_LAUNCH(cg_direction_kernel, n, s, st, partials, r, diag, d, q, bmask, hist, n);
 }
-
-template void launch_cg_init<double, double>(CGState*, double*, const double*, double,
-                                             const double*, const double*, double*, double*,
-                                             double*, int, double, double*, int64_t, hipStream_t);
-template void launch_cg_alpha<double>(CGState*, double*, const double*, int, const uint8_t*,
-                                      const double*, int64_t, hipStream_t);
-template void launch_cg_alpha<float>(CGState*, double*, const double*, int, const uint8_t*,
-                                     const float*, int64_t, hipStream_t);
-template void launch_cg_update<double>(CGState*, double*, double*, double*, const double*,
-                                       const double*, const double*, double*, int64_t,
-                                       hipStream_t);
-template void launch_cg_direction<double>(CGState*, const double*, const double*, double*,
-                                          int64_t, hipStream_t);
 
 void launch_fcg_init(CGState* st, double* partials, const double* b, const double* q, double* x,
-                     double* r, int zero_guess, double rel_tol, double* hist, int64_t n,
-                     hipStream_t s) {
-  hipLaunchKernelGGL(fcg_init_kernel, dim3(kCGBlocks), dim3(kCGThreads), 0, s, st, partials, b, q,
-                     x, r, zero_guess, rel_tol, hist, n);
-  check_launch("fcg_init");
+                     double* r, int zero_guess, double rel_tol, int32_t max_hist, double* hist,
+                     int64_t n, hipStream_t s) {
+  CG_LAUNCH(fcg_init_kernel, n, s, partials, b, q, x, r, zero_guess, n);
+  CG_FINISH(cg_start_finish_kernel, s, st, partials, cg_blocks(n), rel_tol, max_hist, hist, 1);
 }
 void launch_fcg_start(CGState* st, double* partials, const double* r, const double* z, double* p,
-                      int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(fcg_start_kernel, dim3(kCGBlocks), dim3(kCGThreads), 0, s, st, partials, r, z,
-                     p, n);
-  check_launch("fcg_start");
+                      double* q, const uint8_t* bmask, int64_t n, hipStream_t s) {
+  CG_LAUNCH(fcg_start_kernel, n, s, st, partials, r, z, p, q, bmask, n);
+  CG_FINISH(fcg_start_finish_kernel, s, st, partials, cg_blocks(n));
 }
-void launch_fcg_update(CGState* st, double* partials, double* x, double* r, const double* p,
-                       const double* q, const double* diag, const uint8_t* bmask, double* zj,
-                       double* hist, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(fcg_update_kernel, dim3(kCGBlocks), dim3(kCGThreads), 0, s, st, partials, x,
-                     r, p, q, diag, bmask, zj, hist, n);
-  check_launch("fcg_update");
+void launch_fcg_update(CGState* st, double* partials, double* epart, int nepart, double* x,
+                       double* r, const double* p, const double* q, const double* diag,
+                       const uint8_t* bmask, double* zj, int64_t n, hipStream_t s) {
+  const EnergyParts ep = energy_parts(epart, nepart, s);
+  CG_LAUNCH(fcg_update_kernel, n, s, st, ep, partials, x, r, p, q, diag, bmask, zj, n);
 }
 void launch_fcg_beta(CGState* st, double* partials, const double* r, const double* z,
-                     const double* zold, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(fcg_beta_kernel, dim3(kCGBlocks), dim3(kCGThreads), 0, s, st, partials, r, z,
-                     zold, n);
-  check_launch("fcg_beta");
+                     const double* zold, double* hist, int64_t n, hipStream_t s) {
+  CG_LAUNCH(fcg_beta_kernel, n, s, st, partials, r, z, zold, hist, n);
 }
-void launch_cg_direction_init(CGState* st, const double* r, const double* diag, double* d,
-                              double* q, const uint8_t* bmask, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(cg_direction_init_kernel, dim3(kCGBlocks), dim3(kCGThreads), 0, s, st, r,
-                     diag, d, q, bmask, n);
-  check_launch("cg_direction_init");
-}
-
-void launch_fcg_direction(CGState* st, const double* z, double* p, int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(fcg_direction_kernel, dim3(kCGBlocks), dim3(kCGThreads), 0, s, st, z, p, n);
-  check_launch("fcg_direction");
+void launch_fcg_direction(CGState* st, double* partials, const double* z, double* p, double* q,
+                          const uint8_t* bmask, int64_t n, hipStream_t s) {
+  CG_LAUNCH(fcg_direction_kernel, n, s, st, partials, z, p, q, bmask, n);
 }
 
 void launch_residual(CGState* st, double* partials, const double* b, const double* q, double* r,
                      int64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(residual_kernel, dim3(kCGBlocks), dim3(kCGThreads), 0, s, st, partials, b, q,
-                     r, n);
-  check_launch("residual");
+  CG_LAUNCH(residual_kernel, n, s, partials, b, q, r, n);
+  CG_FINISH(residual_finish_kernel, s, st, partials, cg_blocks(n));
 }
-
 
 void launch_ir_start(CGState* st, double* partials, double* r, double s, const float* dinv,
                      float* d, float* q, const uint8_t* ess, double inner_rel_tol, int64_t n,
                      hipStream_t stream) {
-  hipLaunchKernelGGL(ir_start_kernel, dim3(kCGBlocks), dim3(kCGThreads), 0, stream, st, partials,
-                     r, 1.0 / s, dinv, d, q, ess, inner_rel_tol, n);
-  check_launch("ir_start");
+  CG_LAUNCH(ir_start_kernel, n, stream, partials, r, 1.0 / s, dinv, d, q, ess, n);
+  CG_FINISH(ir_start_finish_kernel, stream, st, partials, cg_blocks(n), inner_rel_tol);
 }
 
-void launch_ir_update(CGState* st, double* partials, double* x, double s, double* r,
-                      const float* d, const float* q, const float* dinv, int64_t n,
-                      hipStream_t stream) {
-  hipLaunchKernelGGL(ir_update_kernel, dim3(kCGBlocks), dim3(kCGThreads), 0, stream, st,
-                     partials, x, s, r, d, q, dinv, n);
-  check_launch("ir_update");
+void launch_ir_update(CGState* st, double* partials, double* epart, int nepart, bool has_ess,
+                      double* x, double s, double* r, const float* d, const float* q,
+                      const float* dinv, int64_t n, hipStream_t stream) {
+  const EnergyParts ep = energy_parts(epart, nepart, stream);
+  CG_LAUNCH(ir_update_kernel, n, stream, st, ep, partials, int(has_ess), x, s, r, d, q, dinv, n);
 }
 
-void launch_ir_direction(CGState* st, const double* r, const float* dinv, float* d, float* q,
-                         const uint8_t* ess, int64_t n, hipStream_t stream) {
-  hipLaunchKernelGGL(ir_direction_kernel, dim3(kCGBlocks), dim3(kCGThreads), 0, stream, st, r,
-                     dinv, d, q, ess, n);
-  check_launch("ir_direction");
+void launch_ir_direction(CGState* st, double* partials, bool replaced, const double* r,
+                         const float* dinv, float* d, float* q, const uint8_t* ess, int64_t n,
+                         hipStream_t stream) {
+  CG_LAUNCH(ir_direction_kernel, n, stream, st, partials, int(replaced), r, dinv, d, q, ess, n);
 }
 
 void launch_ir_replace(CGState* st, double* partials, double* r, double s_new, const float* dinv,
                        const float* d, const float* q, double inner_rel_tol, int64_t n,
                        hipStream_t stream) {
-  hipLaunchKernelGGL(ir_replace_kernel, dim3(kCGBlocks), dim3(kCGThreads), 0, stream, st,
-                     partials, r, 1.0 / s_new, dinv, d, q, inner_rel_tol, n);
-  check_launch("ir_replace");
+  CG_LAUNCH(ir_replace_kernel, n, stream, partials, r, 1.0 / s_new, dinv, d, q, n);
+  CG_FINISH(ir_replace_finish_kernel, stream, st, partials, cg_blocks(n), inner_rel_tol);
 }
 
 void launch_ir_dinv(const double* diag, float* dinv, int64_t n, hipStream_t stream) {

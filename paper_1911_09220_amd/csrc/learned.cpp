@@ -448,7 +448,7 @@ FCGLayout fcg_layout(const Op& op, int max_iter) {
     return at;
   };
   L.state = take(sizeof(CGState));
-  L.partials = take(3 * kCGBlocks * sizeof(double));
+  L.partials = take(kPartials * kCGBlocks * sizeof(double));
   L.hist = take((size_t(max_iter) + 1) * sizeof(double));
   L.r = take(n * 8);
   L.z = take(n * 8);
@@ -511,12 +511,13 @@ pafem_status fcg_solve(const Op& op, Net* net, const float* feats, const double*
       launch_jacobi(sp, rr, diag, zz, st, ess_mode);
   };
 
-  launch_cg_reset(state, opts.max_iter + 1, st);
+  const bool evec = op.flags & PAFEM_OP_SCATTER_EVEC;
+  double* const qi = evec ? nullptr : q;  // the apply's y-init, written with the direction
   if (!opts.zero_guess) apply_op(op, x, q, lw + LW.opwork, st);
   launch_fcg_init(state, partials, b, opts.zero_guess ? nullptr : q, x, r, opts.zero_guess,
-                  opts.rel_tol, hist, n, st);
+                  opts.rel_tol, opts.max_iter + 1, hist, n, st);
   precond(r, z);
-  launch_fcg_start(state, partials, r, z, p, n, st);
+  launch_fcg_start(state, partials, r, z, p, qi, ess, n, st);
   const int check = std::max(1, opts.check_every);
   double best_rr = 1e308;
   int launched = 0;
@@ -533,24 +534,22 @@ pafem_status fcg_solve(const Op& op, Net* net, const float* feats, const double*
       use_net = false;
       res.fell_back = 1;
       res.fallback_iter = h.iter;
-      hip_check(hipMemsetAsync(&state->done, 0, 4, st), "reset flag");
       apply_op(op, x, q, lw + LW.opwork, st);
-      launch_fcg_init(state, partials, b, q, x, r, 0, opts.rel_tol, nullptr, n, st);
+      launch_fcg_init(state, partials, b, q, x, r, 0, opts.rel_tol, -1, nullptr, n, st);
       precond(r, z);
-      launch_fcg_start(state, partials, r, z, p, n, st);
+      launch_fcg_start(state, partials, r, z, p, qi, ess, n, st);
       continue;
     }
     if (h.iter > 0) best_rr = std::min(best_rr, h.rr);
     if (launched >= opts.max_iter || h.iter >= opts.max_iter) break;
     const int batch = std::min(check, opts.max_iter - launched);
     for (int k = 0; k < batch; ++k) {
-      apply_op(op, p, q, lw + LW.opwork, st, dotp);
-      launch_cg_alpha<double>(state, partials, dotp, nap, ess, p, n, st);
+      apply_op(op, p, q, lw + LW.opwork, st, dotp, !evec);
       // new z into the spare buffer: the update writes its Jacobi part
-      launch_fcg_update(state, partials, x, r, p, q, diag, ess, zold, hist, n, st);
+      launch_fcg_update(state, partials, dotp, nap, x, r, p, q, diag, ess, zold, n, st);
       if (use_net) learned_correct(*net, op, r, zold, lw, LW, st);
-      launch_fcg_beta(state, partials, r, zold, z, n, st);
-      launch_fcg_direction(state, zold, p, n, st);
+      launch_fcg_beta(state, partials, r, zold, z, hist, n, st);
+      launch_fcg_direction(state, partials, zold, p, qi, ess, n, st);
       std::swap(z, zold);
     }
     launched += batch;

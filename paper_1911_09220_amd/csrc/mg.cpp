@@ -159,7 +159,7 @@ VLayout vcycle_layout(const PMG& g, size_t base) {
   }
   const Op& c = *g.ops[size_t(g.L - 1)];
   L.state = take(sizeof(CGState));
-  L.partials = take(3 * kCGBlocks * sizeof(double));
+  L.partials = take(kPartials * kCGBlocks * sizeof(double));
   L.hist = take((size_t(std::max(0, g.o.coarse_iters)) + 1) * sizeof(double));
   L.dotp = take(size_t(pa_apply_blocks(c.space->dev)) * sizeof(double));
   L.opwork = take(opw);
@@ -206,14 +206,16 @@ void coarse_pcg(const PMG& g, const double* b, double* x, VBufs& B, hipStream_t 
   LevelBufs& v = B.lv[size_t(l)];
   const int nap = pa_apply_blocks(op.space->dev);
   const uint8_t* ess = (op.flags & PAFEM_OP_CONSTRAINED) ? op.space->dev.bmask : nullptr;
-  launch_cg_reset(B.state, iters + 1, st);
-  launch_cg_init<double, double>(B.state, B.partials, b, 1.0, nullptr, diag, x, v.r, v.d, 1, 0.0,
-                                 B.hist, n, st);
+  const bool evec = op.flags & PAFEM_OP_SCATTER_EVEC;
+  double* const yi = evec ? nullptr : v.y;  // the apply's y-init, written with the direction
+  launch_cg_init(B.state, B.partials, b, nullptr, diag, x, v.r, v.d, yi, ess, 1, 0.0, iters + 1,
+                 B.hist, n, st);
   for (int k = 0; k < iters; ++k) {
-    apply_op(op, v.d, v.y, B.opwork, st, B.dotp);
-    launch_cg_alpha<double>(B.state, B.partials, B.dotp, nap, ess, v.d, n, st);
-    launch_cg_update<double>(B.state, B.partials, x, v.r, v.d, v.y, diag, B.hist, n, st);
-    launch_cg_direction<double>(B.state, v.r, diag, v.d, n, st);
+    apply_op(op, v.d, v.y, B.opwork, st, B.dotp, !evec);
+    launch_cg_update(B.state, B.partials, B.dotp, nap, ess != nullptr, x, v.r, v.d, v.y, diag, n,
+                     st);
+    if (k + 1 < iters)  // the last direction is not used
+      launch_cg_direction(B.state, B.partials, v.r, diag, v.d, yi, ess, B.hist, n, st);
   }
 }
 
@@ -252,7 +254,7 @@ FLayout fcg_layout_mg(const Op& op, int max_iter) {
     return at;
   };
   L.state = take(sizeof(CGState));
-  L.partials = take(3 * kCGBlocks * sizeof(double));
+  L.partials = take(kPartials * kCGBlocks * sizeof(double));
   L.hist = take((size_t(std::max(0, max_iter)) + 1) * sizeof(double));
   L.r = take(n * 8);
   L.z = take(n * 8);
@@ -480,20 +482,20 @@ pafem_status pafem_pmg_fcg_solve(pafem_pmg pmg, const double* b, double* x, void
     const uint8_t* ess = sp.bmask;
     auto st = static_cast<hipStream_t>(stream);
 
-    launch_cg_reset(state, opts->max_iter + 1, st);
+    const bool evec = op.flags & PAFEM_OP_SCATTER_EVEC;
+    double* const qi = evec ? nullptr : q;  // the apply's y-init, written with the direction
     if (!opts->zero_guess) apply_op(op, x, q, B.opwork, st);
     launch_fcg_init(state, partials, b, opts->zero_guess ? nullptr : q, x, r, opts->zero_guess,
-                    opts->rel_tol, hist, n, st);
+                    opts->rel_tol, opts->max_iter + 1, hist, n, st);
     vcycle(g, 0, r, z, B, st);
-    launch_fcg_start(state, partials, r, z, p, n, st);
+    launch_fcg_start(state, partials, r, z, p, qi, ess, n, st);
     // one iteration: the new preconditioned residual goes to zn, zc holds the current one
     auto iteration = [&](hipStream_t s2, double* zc, double* zn) {
-      apply_op(op, p, q, B.opwork, s2, dotp);
-      launch_cg_alpha<double>(state, partials, dotp, nap, ess, p, n, s2);
-      launch_fcg_update(state, partials, x, r, p, q, g.diag[0], ess, zn, hist, n, s2);
+      apply_op(op, p, q, B.opwork, s2, dotp, !evec);
+      launch_fcg_update(state, partials, dotp, nap, x, r, p, q, g.diag[0], ess, zn, n, s2);
       vcycle(g, 0, r, zn, B, s2);
-      launch_fcg_beta(state, partials, r, zn, zc, n, s2);
-      launch_fcg_direction(state, zn, p, n, s2);
+      launch_fcg_beta(state, partials, r, zn, zc, hist, n, s2);
+      launch_fcg_direction(state, partials, zn, p, qi, ess, n, s2);
     };
     const bool graphs = graphs_enabled();
     int check = std::max(1, opts->check_every);

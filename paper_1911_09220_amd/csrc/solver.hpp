@@ -16,62 +16,71 @@ struct CGState {
   double bb;     // b . b
   double tol2;   // rel_tol^2 * b . b
   double res2;   // ||b - A x||^2 computed at exit
-  double pad0;
+  double rz_old; // rz at the last update (the denominator of beta)
   int32_t iter;  // completed iterations
   int32_t done;  // 0 running, 1 converged, 2 breakdown, 3 preconditioner not positive
   int32_t max_hist;
   int32_t pad1;
-  uint32_t ticket[8];  // arrival counters of the last-block reductions
 };
 
-constexpr int kCGBlocks = 256;  // fixed grid of the vector kernels = number of partials
+constexpr int kCGBlocks = 256;  // most workgroups of a vector kernel = partials per sum
 constexpr int kCGThreads = 1024;
+// Partials of one solver: kPartials arrays of kCGBlocks doubles.  p0: r.z; p1: r.r; p2: d_b^2
+// over the essential rows, written with the direction and read by the next update; p3:
+// b.b at the start, r.z_old in flexible CG.  No kernel writes an array that it reads.
+constexpr int kPartials = 4;
 
-// zero the state and tickets; hist holds max_hist entries
-void launch_cg_reset(CGState* st, int32_t max_hist, hipStream_t s);
+// The element energies of an apply (one per workgroup) as the update kernels read them:
+// n entries, stride apart.  Up to kFoldAbove of them every workgroup of the update sums
+// them all itself; a larger apply's are folded to kCGBlocks first, in place.  The fold's
+// launch costs 1-3 us an iteration up to 17562 of them (p = 1, 40^3 elements: 38.8 us
+// folded, 35.8 direct), nothing at 31598, and gains 4 of 523 us at 74899 (p = 1, 128^3).
+struct EnergyParts {
+  const double* e;
+  int n, stride;
+};
+constexpr int kFoldAbove = 32768;
 
-// The iteration kernels are templated on the vector type TV (double is built);
-// dot products always accumulate in double.
+// Dot products always accumulate in double.  Every apply between two kernels below
+// passes its element energies as epart (nepart of them, overwritten).  q / qi arguments
+// receive the next apply's init (d on the essential dofs given by bmask, 0 elsewhere;
+// bmask null: 0 everywhere); null: the apply needs none.
 //
-// r = b*bscale - q (q may be null); x = 0 if zero_guess; d = z = r / diag;
-// rz, rr, bb, tol2, done, hist[0].
-template <typename TB, typename TV>
-void launch_cg_init(CGState* st, double* partials, const TB* b, double bscale, const TV* q,
-                    const TV* diag, TV* x, TV* r, TV* d, int zero_guess, double rel_tol,
+// r = b - q (q may be null; qi may be q); x = 0 if zero_guess; d = z = r / diag; sets
+// the whole state, hist[0]; hist holds max_hist entries
+void launch_cg_init(CGState* st, double* partials, const double* b, const double* q,
+                    const double* diag, double* x, double* r, double* d, double* qi,
+                    const uint8_t* bmask, int zero_guess, double rel_tol, int32_t max_hist,
                     double* hist, int64_t n, hipStream_t s);
-// alpha = rz / (d . q) from the apply's element-energy partials (epart, nepart of
-// them) plus sum of d_b^2 over the essential dofs (bmask; null for an unconstrained
-// operator); breakdown (done = 2) if d . q <= 0 or alpha is not finite
-template <typename TV>
-void launch_cg_alpha(CGState* st, double* partials, const double* epart, int nepart,
-                     const uint8_t* bmask, const TV* d, int64_t n, hipStream_t s);
-// x += alpha d; r -= alpha q; z = r / diag; rz, rr, beta, iter, hist, convergence
-template <typename TV>
-void launch_cg_update(CGState* st, double* partials, TV* x, TV* r, const TV* d, const TV* q,
-                      const TV* diag, double* hist, int64_t n, hipStream_t s);
-// d = r / diag + beta d
-template <typename TV>
-void launch_cg_direction(CGState* st, const TV* r, const TV* diag, TV* d, int64_t n,
-                         hipStream_t s);
-// d = r / diag + beta d (FP64) and q = the apply init of the new d (d on the
-// essential dofs given by bmask, 0 elsewhere; bmask null: 0 everywhere)
-void launch_cg_direction_init(CGState* st, const double* r, const double* diag, double* d,
-                              double* q, const uint8_t* bmask, int64_t n, hipStream_t s);
-// Flexible CG (done = 3: the preconditioner returned r.z <= 0)
-void launch_fcg_init(CGState* st, double* partials, const double* b, const double* q, double* x,
-                     double* r, int zero_guess, double rel_tol, double* hist, int64_t n,
-                     hipStream_t s);
-void launch_fcg_start(CGState* st, double* partials, const double* r, const double* z, double* p,
+// alpha = rz / (d . q), d . q from the element energies plus d_b^2 over the essential
+// rows (has_ess: a constrained operator); breakdown (done = 2) if d . q <= 0 or alpha
+// is not finite; x += alpha d; r -= alpha q
+void launch_cg_update(CGState* st, double* partials, double* epart, int nepart, bool has_ess,
+                      double* x, double* r, const double* d, const double* q, const double* diag,
                       int64_t n, hipStream_t s);
+// rz, rr, beta, iter, hist, convergence; d = r / diag + beta d
+void launch_cg_direction(CGState* st, double* partials, const double* r, const double* diag,
+                         double* d, double* q, const uint8_t* bmask, double* hist, int64_t n,
+                         hipStream_t s);
+// Flexible CG (done = 3: the preconditioner returned r.z <= 0).  max_hist < 0: a restart
+// inside a solve, which keeps the iteration count
+void launch_fcg_init(CGState* st, double* partials, const double* b, const double* q, double* x,
+                     double* r, int zero_guess, double rel_tol, int32_t max_hist, double* hist,
+                     int64_t n, hipStream_t s);
+void launch_fcg_start(CGState* st, double* partials, const double* r, const double* z, double* p,
+                      double* q, const uint8_t* bmask, int64_t n, hipStream_t s);
 // x += alpha p; r -= alpha q; zj = r / diag, and zj = r where bmask (may be null) marks
 // the essential rows of a constrained operator (unit diagonal there): the Jacobi part
 // of the next preconditioned residual
-void launch_fcg_update(CGState* st, double* partials, double* x, double* r, const double* p,
-                       const double* q, const double* diag, const uint8_t* bmask, double* zj,
-                       double* hist, int64_t n, hipStream_t s);
+void launch_fcg_update(CGState* st, double* partials, double* epart, int nepart, double* x,
+                       double* r, const double* p, const double* q, const double* diag,
+                       const uint8_t* bmask, double* zj, int64_t n, hipStream_t s);
+// rr, iter, hist, convergence; r.z and r.z_old
 void launch_fcg_beta(CGState* st, double* partials, const double* r, const double* z,
-                     const double* zold, int64_t n, hipStream_t s);
-void launch_fcg_direction(CGState* st, const double* z, double* p, int64_t n, hipStream_t s);
+                     const double* zold, double* hist, int64_t n, hipStream_t s);
+// beta; p = z + beta p
+void launch_fcg_direction(CGState* st, double* partials, const double* z, double* p, double* q,
+                          const uint8_t* bmask, int64_t n, hipStream_t s);
 // res2 = ||b - q||^2 and, if r is not null, r = b - q (always runs, ignores `done`)
 void launch_residual(CGState* st, double* partials, const double* b, const double* q, double* r,
                      int64_t n, hipStream_t s);
@@ -84,16 +93,18 @@ void launch_residual(CGState* st, double* partials, const double* b, const doubl
 void launch_ir_start(CGState* st, double* partials, double* r, double s, const float* dinv,
                      float* d, float* q, const uint8_t* ess, double inner_rel_tol, int64_t n,
                      hipStream_t stream);
-// x += (s alpha) d; r -= alpha q; rz, rr, beta, iter, convergence
-void launch_ir_update(CGState* st, double* partials, double* x, double s, double* r,
-                      const float* d, const float* q, const float* dinv, int64_t n,
-                      hipStream_t stream);
-// d = z + beta d; q = apply init of d
-void launch_ir_direction(CGState* st, const double* r, const float* dinv, float* d, float* q,
-                         const uint8_t* ess, int64_t n, hipStream_t stream);
+// alpha; x += (s alpha) d; r -= alpha q
+void launch_ir_update(CGState* st, double* partials, double* epart, int nepart, bool has_ess,
+                      double* x, double s, double* r, const float* d, const float* q,
+                      const float* dinv, int64_t n, hipStream_t stream);
+// rz, rr, beta, iter, convergence (replaced: beta as launch_ir_replace left it, nothing
+// else changes); d = z + beta d; q = apply init of d
+void launch_ir_direction(CGState* st, double* partials, bool replaced, const double* r,
+                         const float* dinv, float* d, float* q, const uint8_t* ess, int64_t n,
+                         hipStream_t stream);
 // Reliable update after a residual replacement: r (the FP64 residual) *= 1/s_new,
 // beta = -(z.q)/(d.q) so that launch_ir_direction continues with a direction
-// conjugate to the kept one (done = 2 on breakdown).  partials: 4 * kCGBlocks.
+// conjugate to the kept one (done = 2 on breakdown)
 void launch_ir_replace(CGState* st, double* partials, double* r, double s_new, const float* dinv,
                        const float* d, const float* q, double inner_rel_tol, int64_t n,
                        hipStream_t stream);
