@@ -99,22 +99,24 @@ void apply_op(const Op& op, const void* x, void* y, void* work, hipStream_t st, 
       launch_evec_gather_f32(s.dev, static_cast<const float*>(work), static_cast<const float*>(x),
                              constrained ? 1 : 0, static_cast<float*>(y), st);
   } else {
+    const bool skip = s.dim == 3 && vdt == PAFEM_F64 && has_private(op.kind, s.p);
     if (y_ready) {
       // the caller already set y = x on essential dofs (constrained) and 0 elsewhere
     } else if (op.kind == PAFEM_GRADIENT) {
-      launch_fill(static_cast<double*>(y), 0.0, 3 * s.ndofs, st);  // three output components
+      launch_scatter_init(s.dev, static_cast<const double*>(nullptr), false,
+                          static_cast<double*>(y), st, 3);  // three output components
     } else if (op.kind == PAFEM_DIVERGENCE) {
-      launch_fill(static_cast<double*>(y), 0.0, s.ndofs, st);
+      launch_scatter_init(s.dev, static_cast<const double*>(nullptr), false,
+                          static_cast<double*>(y), st);
     } else if ((op.flags & PAFEM_OP_VECTOR3) || op.kind == PAFEM_ELASTICITY) {
-      for (int c = 0; c < 3; ++c)
-        launch_scatter_init(s.dev, static_cast<const double*>(x) + c * s.ndofs, constrained,
-                            static_cast<double*>(y) + c * s.ndofs, st);
+      launch_scatter_init(s.dev, static_cast<const double*>(x), constrained,
+                          static_cast<double*>(y), st, 3, skip);
     } else if (vdt == PAFEM_F64) {
       launch_scatter_init(s.dev, static_cast<const double*>(x), constrained,
-                          static_cast<double*>(y), st);
+                          static_cast<double*>(y), st, 1, skip);
     } else {
-      launch_scatter_init_f32(s.dev, static_cast<const float*>(x), constrained,
-                              static_cast<float*>(y), st);
+      launch_scatter_init(s.dev, static_cast<const float*>(x), constrained,
+                          static_cast<float*>(y), st);
     }
     const int kkind = (op.flags & PAFEM_OP_VECTOR3) ? kVectorKind + op.kind : op.kind;
     require(launch_pa_apply(s.dev, kkind, op.q1d, op.qdtype, constrained, false, op.qdata, x,
@@ -393,6 +395,8 @@ pafem_status pafem_space_upload(pafem_space space, void* device_buf, size_t nbyt
     up(14, s.tables_open.data(), s.tables_open.size() * 8, "upload open-basis tables");
     up(15, s.faces.data(), s.faces.size() * 4, "upload faces");
     up(16, s.bfaces.data(), s.bfaces.size() * 4, "upload boundary faces");
+    up(17, s.tile_priv.data(), s.tile_priv.size() * 4, "upload private dof counts");
+    up(18, s.shared.data(), s.shared.size() * 4, "upload shared dofs");
     hip_check(hipStreamSynchronize(st), "upload sync");
     s.dev_buf = device_buf;
     s.dev_bytes = nbytes;
@@ -417,6 +421,9 @@ pafem_status pafem_space_upload(pafem_space space, void* device_buf, size_t nbyt
     s.dev.bfaces = s.bfaces.empty() ? nullptr : reinterpret_cast<const int32_t*>(base + off[16]);
     s.dev.nfaces = int64_t(s.faces.size() / kFaceInts);
     s.dev.nbfaces = int64_t(s.bfaces.size() / 2);
+    s.dev.tile_priv = reinterpret_cast<const int32_t*>(base + off[17]);
+    s.dev.shared = reinterpret_cast<const int32_t*>(base + off[18]);
+    s.dev.nshared = int64_t(s.shared.size());
     s.dev.ne = s.ne;
     s.dev.ndofs = s.ndofs;
     s.dev.p = s.p;

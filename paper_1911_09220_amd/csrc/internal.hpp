@@ -138,7 +138,11 @@ struct DevSpace {
   int32_t* status = nullptr;           // [64] small device status words
   const int32_t* elem_orig = nullptr;  // [ne] caller element id of each device element
   const int32_t* tile_off = nullptr;   // [ntiles+1] offsets into tile_dofs
-  const int32_t* tile_dofs = nullptr;  // unique dofs of each apply tile (~g if essential)
+  // unique dofs of each apply tile (~g if essential): first its tile_priv[tile] private
+  // dofs (of this tile alone, in lines of kLineDofs such dofs), then the shared ones
+  const int32_t* tile_dofs = nullptr;
+  const int32_t* tile_priv = nullptr;  // [ntiles]
+  const int32_t* shared = nullptr;     // [nshared] dofs that are not private (~g if essential)
   const uint16_t* tile_slot = nullptr; // [ntiles*tile_ne*D^3] node -> index in its tile's list
   const uint32_t* owner = nullptr;     // [ne][owner_words(D^dim)] first-occurrence bits
   const int8_t* sign = nullptr;        // Nedelec: [ne][dpe] orientation sign of each local dof
@@ -146,6 +150,7 @@ struct DevSpace {
   const int32_t* faces = nullptr;      // L2: interior faces [nfaces][kFaceInts]
   const int32_t* bfaces = nullptr;     // L2: boundary faces [nbfaces][2]
   int64_t nfaces = 0, nbfaces = 0;
+  int64_t nshared = 0;
   int64_t ne = 0, ndofs = 0;
   int p = 0, ng = 0, tile_ne = 0;
   int dim = 3;                         // 3: hexahedra, 2: quadrilaterals
@@ -206,7 +211,7 @@ struct Space {
   std::vector<int32_t> gmap;      // [ne][dpe] dof ids, caller element order
   std::vector<int32_t> dev_order; // device element position -> caller element id
   int tile_ne = 0;                // elements per apply tile (qdata_tile(p + 2), 2D: qdata_tile_2d)
-  std::vector<int32_t> tile_off, tile_dofs;
+  std::vector<int32_t> tile_off, tile_dofs, tile_priv, shared;
   std::vector<uint16_t> tile_slot;
   std::vector<uint8_t> bmask;     // [ndofs]
   std::vector<int32_t> bdr;       // essential dofs ascending
@@ -234,7 +239,8 @@ inline int nd_dofs_per_elem(int p) { return 3 * p * (p + 1) * (p + 1); }
 // face lists for the face terms
 Space* build_l2_space(const Mesh* mesh, int order, int flags);
 void space_dof_coords(const Space& s, double* xyz);
-constexpr int kSpaceSegments = 17;
+constexpr int kLineDofs = 16;  // FP64 values of a 128-byte cache line
+constexpr int kSpaceSegments = 19;
 // words of the per-element owner bitmask (bit i of element k: node i is the first
 // occurrence of its dof in device element order)
 inline int owner_words(int dpe) { return (dpe + 31) / 32; }

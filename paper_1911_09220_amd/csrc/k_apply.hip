@@ -21,9 +21,10 @@
 //        point, streamed from HBM with non-temporal loads issued before the gather
 //        (at some orders only the first planes, the rest one z-iteration ahead)
 //   B^t  z-lines (in registers) -> y-lines -> x-lines
-//   G^t  either: sum the element outputs per unique dof of the tile in LDS, then one
-//        hardware FP atomic per unique dof into y (y pre-set by an init kernel); or
-//        a plain store of the element vector for the deterministic transposed gather.
+//   G^t  either: sum the element outputs per unique dof of the tile in LDS, then per
+//        unique dof a plain store if no other tile has the dof, else one hardware FP
+//        atomic into y (pre-set on such dofs by an init kernel); or a plain store of the
+//        element vector for the deterministic transposed gather.
 // With DOT, each workgroup also writes the sum of its elements' energies
 // u_E . (A_E u_E) (u_E the gathered input, essential entries 0 when constrained) to
 // dotp[blockIdx.x], taken at the quadrature points as the sum of (B G u) . D (B G u):
@@ -52,7 +53,8 @@ __global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, KIND != PAFEM_DI
                     const TC* __restrict__ tabG, const TD* __restrict__ qd,
                     const TV* __restrict__ x, TV* __restrict__ y, double* __restrict__ dotp,
                     const double* __restrict__ gnodes, const TC* __restrict__ tabBg,
-                    const TC* __restrict__ tabGg, int ne, int constrained, int64_t ystride) {
+                    const TC* __restrict__ tabGg, int ne, int constrained, int64_t ystride,
+                    const int32_t* __restrict__ tile_priv) {
   constexpr int D = P + 1, DD = D * D, QQ = Q * Q, QQQ = Q * Q * Q, DDD = D * D * D;
   constexpr int NE = elems_per_block<Q>();
   // GEOM: diffusion storing alpha kappa per point; J recomputed from the 8 corners
@@ -88,6 +90,13 @@ __global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, KIND != PAFEM_DI
   constexpr int NA = GRAD ? 2 : 1;   // arrays after the x-lines (B and G along x)
   constexpr int NCC = (GRAD || DGV) ? 3 : 1;  // arrays after the y-lines (one per derivative)
   constexpr int NOUT = GRADV ? 3 : 1;  // output components
+  // Tiles store their private dofs and add only the others atomically: the mass action at
+  // p >= 3, whose scatter is a third of its time (p = 4 / 5 / 6 / 7 / 8 at ~1.7M dofs 44.4 /
+  // 42.4 / 41.1 / 39.2 / 48.2 -> 40.9 / 37.0 / 34.4 / 33.9 / 40.9 us with the init of the
+  // other dofs alone), and the convection (p = 5..8 2-5%).  At p <= 2 few lines are a
+  // tile's own (no difference); the diffusion at p = 5..7 and the divergence were 3-14%
+  // slower (their registers are at the occupancy limit), the H(curl) one equal.
+  constexpr bool PRIV = DGV || (sizeof(TV) == 8 && has_private(K0, P));
   static_assert(!((CONV || GRADV || DIVV || DGV) && DOT), "the convection, gradient and divergence operators have no energy");
   static_assert(!(DGV && EVEC), "the DG volume term stores through the tile lists");
   static_assert(!((GRADV || DIVV) && EVEC), "the gradient and divergence operators use the atomic scatter");
@@ -594,35 +603,35 @@ __global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, KIND != PAFEM_DI
   }
   if (EVEC) return;
   __syncthreads();
-  // G^t: one global atomic per unique dof of the tile.  The DG volume term's dofs belong
-  // to one element each (no dof is shared between tiles), so it stores instead, and the
-  // call needs no y-init (the face kernel adds its atomics afterwards).
-  auto put = [&](TV* dst, TV v) {
-    if constexpr (DGV)
-      *dst = v;
-    else
-      unsafeAtomicAdd(dst, v);
+  // G^t: per unique dof of the tile one store (dofs of this tile alone) or one global
+  // atomic.  The DG volume term's dofs belong to one element each, so it only stores (the
+  // face kernel adds its atomics afterwards).
+  const int np = DGV ? nu : PRIV ? tile_priv[tile] : 0;
+  auto put = [&](int s, int g, int oc) {
+    TV* const dst = &y[(DIVV ? 0 : GRADC ? GC : comp + oc) * ystride + (g < 0 ? ~g : g)];
+    const TV v = TV(sX[oc * NE * DDD + s]);
+    if constexpr (PRIV) {
+      if (s < np) {  // an essential one keeps x (the init does not cover it)
+        *dst = (constrained && g < 0) ? x[dst - y] : v;
+        return;
+      }
+    }
+    if (!(constrained && g < 0)) unsafeAtomicAdd(dst, v);
   };
   if constexpr (ONEPASS && NV == 1) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int s = tid + k * NE * QQ;
-      const int g = gkeep[k];
-      if (s < nu && !(constrained && g < 0))
+      if (s < nu)
 #pragma unroll
-        for (int oc = 0; oc < NOUT; ++oc)
-          put(&y[(DIVV ? 0 : GRADC ? GC : comp + oc) * ystride + (g < 0 ? ~g : g)],
-              TV(sX[oc * NE * DDD + s]));
+        for (int oc = 0; oc < NOUT; ++oc) put(s, gkeep[k], oc);
     }
   } else {
 #pragma unroll 4
     for (int s = tid; s < nu; s += NE * QQ) {
       const int g = tile_dofs[u0 + s];
-      if (!(constrained && g < 0))
 #pragma unroll
-        for (int oc = 0; oc < NOUT; ++oc)
-          put(&y[(DIVV ? 0 : GRADC ? GC : comp + oc) * ystride + (g < 0 ? ~g : g)],
-              TV(sX[oc * NE * DDD + s]));
+      for (int oc = 0; oc < NOUT; ++oc) put(s, g, oc);
     }
   }
   if (NV > 1) __syncthreads();  // sX is gathered again for the next component
@@ -656,7 +665,7 @@ void launch_one(const DevSpace& sp, bool constrained, const void* qd, const void
                      dim3(NE * Q * Q), 0, st, sp.tile_off, sp.tile_dofs, sp.tile_slot, tabB, tabG,
                      static_cast<const TD*>(qd), static_cast<const TV*>(x),
                      static_cast<TV*>(out), dotp, sp.gnodes, tabBg, tabGg, int(sp.ne),
-                     int(constrained), int64_t(sp.ndofs));
+                     int(constrained), int64_t(sp.ndofs), sp.tile_priv);
 }
 
 template <int P, int KIND, typename TV, typename TD, typename TC>

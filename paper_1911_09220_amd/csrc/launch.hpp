@@ -23,11 +23,18 @@ void launch_evec_gather(const DevSpace& sp, const double* ye, const double* x, i
                         double bc_value, double* y, hipStream_t st);
 void launch_evec_gather_f32(const DevSpace& sp, const float* ye, const float* x, int bc_mode,
                             float* y, hipStream_t st);
-// y = x on essential dofs (constrained) and 0 elsewhere: start of an atomic scatter
+// y = x on essential dofs (constrained) and 0 elsewhere: start of an atomic scatter.
+// ncomp vectors at stride ndofs.  skip_private: only on the dofs that are not private to
+// an apply tile, for the kinds whose apply stores those (has_private).
 void launch_scatter_init(const DevSpace& sp, const double* x, bool constrained, double* y,
+                         hipStream_t st, int ncomp = 1, bool skip_private = false);
+void launch_scatter_init(const DevSpace& sp, const float* x, bool constrained, float* y,
                          hipStream_t st);
-void launch_scatter_init_f32(const DevSpace& sp, const float* x, bool constrained, float* y,
-                             hipStream_t st);
+// whether the FP64 fused apply of this kind (without kVectorKind) and order stores its tiles'
+// private dofs instead of adding them
+constexpr bool has_private(int kind, int p) {
+  return p >= 3 && (kind == PAFEM_MASS || kind == PAFEM_CONVECTION);
+}
 
 // ---- apply (k_apply.hip) ----
 // Fused G -> B -> D -> B^t -> G^t.  evec: write element vectors to `out`
