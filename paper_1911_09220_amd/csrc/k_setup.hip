@@ -1,10 +1,7 @@
-// Setup kernels: geometric factors + quadrature data (PA setup), the linear
-// form, the operator diagonal, and the transposed element restriction G^t.
-//
-// These run once per solve, so they are written for clarity with runtime sizes
-// (one workgroup per element, dynamic LDS).  All arithmetic is FP64.
-#include <climits>
-
+// The transposed element restriction G^t and the atomic scatter's start, and the linear form
+// on rules other than q1d = p + 2 (a general kernel with runtime sizes: one workgroup per
+// element, dynamic LDS).  The other setup kernels are in k_assemble.hip.  FP64.
+#include "assemble.hpp"
 #include "device.hpp"
 #include "launch.hpp"
 
@@ -63,150 +60,30 @@ __device__ void element_jacobian(int q, int Q, int NG, const double* X, const do
       }
 }
 
-__global__ void qdata_kernel(const double* __restrict__ gnodes, const int32_t* __restrict__ orig,
-                             int NG, TabView tv, int Q, int kind,
-                             const double* __restrict__ coeff, double scale,
-                             double* __restrict__ qd, int32_t* status) {
-  extern __shared__ double smem[];
-  const int e = blockIdx.x;
-  const int NN = NG * NG * NG, QQQ = Q * Q * Q;
-  double* sX = smem;
-  double* sBg = sX + 3 * NN;
-  double* sGg = sBg + Q * NG;
-  for (int i = threadIdx.x; i < 3 * NN; i += blockDim.x) sX[i] = gnodes[size_t(e) * 3 * NN + i];
-  for (int i = threadIdx.x; i < Q * NG; i += blockDim.x) {
-    sBg[i] = tv.Bg[i];
-    sGg[i] = tv.Gg[i];
-  }
-  __syncthreads();
-  for (int q = threadIdx.x; q < QQQ; q += blockDim.x) {
-    double J[3][3], x[3];
-    element_jacobian(q, Q, NG, sX, sBg, sGg, J, x);
-    // adjugate A = det(J) J^{-1}
-    const double A00 = J[1][1] * J[2][2] - J[1][2] * J[2][1];
-    const double A01 = J[0][2] * J[2][1] - J[0][1] * J[2][2];
-    const double A02 = J[0][1] * J[1][2] - J[0][2] * J[1][1];
-    const double A10 = J[1][2] * J[2][0] - J[1][0] * J[2][2];
-    const double A11 = J[0][0] * J[2][2] - J[0][2] * J[2][0];
-    const double A12 = J[0][2] * J[1][0] - J[0][0] * J[1][2];
-    const double A20 = J[1][0] * J[2][1] - J[1][1] * J[2][0];
-    const double A21 = J[0][1] * J[2][0] - J[0][0] * J[2][1];
-    const double A22 = J[0][0] * J[1][1] - J[0][1] * J[1][0];
-    const double det = J[0][0] * A00 + J[0][1] * A10 + J[0][2] * A20;
-    if (!(det > 0.0)) atomicMin(&status[0], orig[e]);
-    const int q1 = q % Q, q2 = (q / Q) % Q, q3 = q / (Q * Q);
-    const double w = tv.wts[q1] * tv.wts[q2] * tv.wts[q3];
-    // scalar coefficient per point (convection, elasticity and the definite Maxwell
-    // form read theirs below)
-    const double c = (kind == PAFEM_CONVECTION || kind == PAFEM_ELASTICITY ||
-                      kind == PAFEM_HCURL_MAXWELL || kind == PAFEM_DG_CONVECTION)
-                         ? 0.0
-                         : scale * (coeff ? coeff[size_t(orig[e]) * QQQ + q] : 1.0);
-    if (kind == PAFEM_HCURL_CURLCURL || kind == PAFEM_HCURL_MAXWELL) {
-      // curl-curl: w alpha J^T J / det J (the reference curl maps with J / det J);
-      // Maxwell: that with alpha, then the mass part w beta A A^T / det J with beta,
-      // (alpha, beta) the point's coefficient pair
-      const int nc = kind == PAFEM_HCURL_MAXWELL ? 12 : 6;
-      double ca = c, cb = 0.0;
-      if (kind == PAFEM_HCURL_MAXWELL) {
-        const double* ab = coeff + (size_t(orig[e]) * QQQ + q) * 2;
-        ca = scale * ab[0];
-        cb = scale * ab[1];
-      }
-      const double f = w * ca / det;
-      double T[3][3];
-      for (int a = 0; a < 3; ++a)
-        for (int b = 0; b < 3; ++b) T[a][b] = J[0][a] * J[0][b] + J[1][a] * J[1][b] + J[2][a] * J[2][b];
-      qd[qdata_index(e, 0, q, Q, nc)] = f * T[0][0];
-      qd[qdata_index(e, 1, q, Q, nc)] = f * T[0][1];
-      qd[qdata_index(e, 2, q, Q, nc)] = f * T[0][2];
-      qd[qdata_index(e, 3, q, Q, nc)] = f * T[1][1];
-      qd[qdata_index(e, 4, q, Q, nc)] = f * T[1][2];
-      qd[qdata_index(e, 5, q, Q, nc)] = f * T[2][2];
-      if (kind == PAFEM_HCURL_MAXWELL) {
-        const double g = w * cb / det;
-        qd[qdata_index(e, 6, q, Q, 12)] = g * (A00 * A00 + A01 * A01 + A02 * A02);
-        qd[qdata_index(e, 7, q, Q, 12)] = g * (A00 * A10 + A01 * A11 + A02 * A12);
-        qd[qdata_index(e, 8, q, Q, 12)] = g * (A00 * A20 + A01 * A21 + A02 * A22);
-        qd[qdata_index(e, 9, q, Q, 12)] = g * (A10 * A10 + A11 * A11 + A12 * A12);
-        qd[qdata_index(e, 10, q, Q, 12)] = g * (A10 * A20 + A11 * A21 + A12 * A22);
-        qd[qdata_index(e, 11, q, Q, 12)] = g * (A20 * A20 + A21 * A21 + A22 * A22);
-      }
-    } else if (kind == PAFEM_MASS) {
-      qd[qdata_index(e, 0, q, Q, 1)] = w * c * det;
-    } else if (kind == PAFEM_GRADIENT || kind == PAFEM_DIVERGENCE) {
-      // w kappa det J J^{-T} as D[c][b] = w kappa adj(J)[b][c]: physical derivative c
-      // (the gradient's output component, the divergence's input component),
-      // reference derivative b
-      const double f = w * c;
-      qd[qdata_index(e, 0, q, Q, 9)] = f * A00;
-      qd[qdata_index(e, 1, q, Q, 9)] = f * A10;
-      qd[qdata_index(e, 2, q, Q, 9)] = f * A20;
-      qd[qdata_index(e, 3, q, Q, 9)] = f * A01;
-      qd[qdata_index(e, 4, q, Q, 9)] = f * A11;
-      qd[qdata_index(e, 5, q, Q, 9)] = f * A21;
-      qd[qdata_index(e, 6, q, Q, 9)] = f * A02;
-      qd[qdata_index(e, 7, q, Q, 9)] = f * A12;
-      qd[qdata_index(e, 8, q, Q, 9)] = f * A22;
-    } else if (kind == PAFEM_ELASTICITY) {
-      // J^{-1} = A / det J as [b][d] = d xhat_b / d x_d, then w det J lambda and
-      // w det J mu, lambda and mu from the point's coefficient pair
-      const double* lm = coeff + (size_t(orig[e]) * QQQ + q) * 2;
-      const double id = 1.0 / det, wd = scale * w * det;
-      const double Kinv[9] = {A00, A01, A02, A10, A11, A12, A20, A21, A22};
-      for (int k = 0; k < 9; ++k) qd[qdata_index(e, k, q, Q, 11)] = Kinv[k] * id;
-      qd[qdata_index(e, 9, q, Q, 11)] = wd * lm[0];
-      qd[qdata_index(e, 10, q, Q, 11)] = wd * lm[1];
-    } else if (kind == PAFEM_CONVECTION || kind == PAFEM_DG_CONVECTION) {
-      // alpha det J J^{-1} beta = alpha adj(J) beta, beta = scale * velocity at the point
-      // (the DG convection: one constant velocity)
-      const double* v =
-          kind == PAFEM_DG_CONVECTION ? coeff : coeff + (size_t(orig[e]) * QQQ + q) * 3;
-      const double b0 = scale * v[0], b1 = scale * v[1], b2 = scale * v[2];
-      qd[qdata_index(e, 0, q, Q, 3)] = w * (A00 * b0 + A01 * b1 + A02 * b2);
-      qd[qdata_index(e, 1, q, Q, 3)] = w * (A10 * b0 + A11 * b1 + A12 * b2);
-      qd[qdata_index(e, 2, q, Q, 3)] = w * (A20 * b0 + A21 * b1 + A22 * b2);
-    } else if (kind == PAFEM_DIFFUSION_GEOM) {
-      qd[qdata_index(e, 0, q, Q, 1)] = w * c;  // the apply recomputes the geometric part
-    } else {
-      // diffusion and the H(curl) mass: alpha kappa det J J^{-1} J^{-T} = alpha kappa
-      // A A^T / det J
-      const double f = w * c / det;
-      qd[qdata_index(e, 0, q, Q, 6)] = f * (A00 * A00 + A01 * A01 + A02 * A02);
-      qd[qdata_index(e, 1, q, Q, 6)] = f * (A00 * A10 + A01 * A11 + A02 * A12);
-      qd[qdata_index(e, 2, q, Q, 6)] = f * (A00 * A20 + A01 * A21 + A02 * A22);
-      qd[qdata_index(e, 3, q, Q, 6)] = f * (A10 * A10 + A11 * A11 + A12 * A12);
-      qd[qdata_index(e, 4, q, Q, 6)] = f * (A10 * A20 + A11 * A21 + A12 * A22);
-      qd[qdata_index(e, 5, q, Q, 6)] = f * (A20 * A20 + A21 * A21 + A22 * A22);
-    }
-  }
-}
-
-// out[i1,i2,i3] (+)= factor * sum_q T1[q1,i1] T2[q2,i2] T3[q3,i3] in[q1,q2,q3] by three
-// one-axis contractions through LDS (sum factorization of B^t).
+// out[i1,i2,i3] = sum_q T[q1,i1] T[q2,i2] T[q3,i3] in[q1,q2,q3] by three one-axis
+// contractions through LDS (sum factorization of B^t).
 __device__ void contract_to_dofs(int Q, int D, const double* in, double* t1, double* t2,
-                                 double* out, const double* T1, const double* T2,
-                                 const double* T3, double factor, bool accumulate) {
+                                 double* out, const double* T) {
   const int nt = blockDim.x, tid = threadIdx.x;
   for (int idx = tid; idx < Q * Q * D; idx += nt) {
     const int i1 = idx % D, q23 = idx / D;
     double s = 0.0;
-    for (int q1 = 0; q1 < Q; ++q1) s += T1[q1 * D + i1] * in[q23 * Q + q1];
+    for (int q1 = 0; q1 < Q; ++q1) s += T[q1 * D + i1] * in[q23 * Q + q1];
     t1[idx] = s;
   }
   __syncthreads();
   for (int idx = tid; idx < Q * D * D; idx += nt) {
     const int i1 = idx % D, i2 = (idx / D) % D, q3 = idx / (D * D);
     double s = 0.0;
-    for (int q2 = 0; q2 < Q; ++q2) s += T2[q2 * D + i2] * t1[(q3 * Q + q2) * D + i1];
+    for (int q2 = 0; q2 < Q; ++q2) s += T[q2 * D + i2] * t1[(q3 * Q + q2) * D + i1];
     t2[idx] = s;
   }
   __syncthreads();
   for (int idx = tid; idx < D * D * D; idx += nt) {
     const int i1 = idx % D, i2 = (idx / D) % D, i3 = idx / (D * D);
     double s = 0.0;
-    for (int q3 = 0; q3 < Q; ++q3) s += T3[q3 * D + i3] * t2[(q3 * D + i2) * D + i1];
-    out[idx] = (accumulate ? out[idx] : 0.0) + factor * s;
+    for (int q3 = 0; q3 < Q; ++q3) s += T[q3 * D + i3] * t2[(q3 * D + i2) * D + i1];
+    out[idx] = s;
   }
   __syncthreads();
 }
@@ -252,51 +129,7 @@ __global__ void linear_form_kernel(const double* __restrict__ gnodes,
     sF[q] = w * det * f;
   }
   __syncthreads();
-  contract_to_dofs(Q, D, sF, t1, t2, out, sB, sB, sB, 1.0, false);
-  for (int i = threadIdx.x; i < DDD; i += blockDim.x) ye[size_t(e) * DDD + i] = out[i];
-}
-
-__global__ void diagonal_kernel(TabView tv, int Q, int D, int kind,
-                                const double* __restrict__ qd, double* __restrict__ ye) {
-  extern __shared__ double smem[];
-  const int e = blockIdx.x;
-  const int QQQ = Q * Q * Q, DDD = D * D * D, QD = Q * D;
-  double* sBB = smem;      // B o B
-  double* sGG = sBB + QD;  // G o G
-  double* sBG = sGG + QD;  // B o G
-  double* sF = sBG + QD;
-  double* t1 = sF + QQQ;
-  double* t2 = t1 + Q * Q * D;
-  double* out = t2 + Q * D * D;
-  for (int i = threadIdx.x; i < QD; i += blockDim.x) {
-    const double b = tv.B[i], g = tv.G[i];
-    sBB[i] = b * b;
-    sGG[i] = g * g;
-    sBG[i] = b * g;
-  }
-  __syncthreads();
-  if (kind == PAFEM_MASS) {
-    for (int q = threadIdx.x; q < QQQ; q += blockDim.x) sF[q] = qd[qdata_index(e, 0, q, Q, 1)];
-    __syncthreads();
-    contract_to_dofs(Q, D, sF, t1, t2, out, sBB, sBB, sBB, 1.0, false);
-  } else {
-    // diag_i = sum_q sum_ab D_ab(q) d_a phi_i(q) d_b phi_i(q); d_a phi_i is a product of
-    // G in direction a and B in the others, so each (a,b) term is a tensor
-    // contraction with elementwise products of the 1D tables.
-    int comp = 0;
-    for (int a = 0; a < 3; ++a)
-      for (int b = a; b < 3; ++b, ++comp) {
-        for (int q = threadIdx.x; q < QQQ; q += blockDim.x)
-          sF[q] = qd[qdata_index(e, comp, q, Q, 6)];
-        __syncthreads();
-        const double* T[3];
-        for (int d = 0; d < 3; ++d) {
-          const int hits = (d == a) + (d == b);
-          T[d] = hits == 2 ? sGG : (hits == 1 ? sBG : sBB);
-        }
-        contract_to_dofs(Q, D, sF, t1, t2, out, T[0], T[1], T[2], a == b ? 1.0 : 2.0, comp > 0);
-      }
-  }
+  contract_to_dofs(Q, D, sF, t1, t2, out, sB);
   for (int i = threadIdx.x; i < DDD; i += blockDim.x) ye[size_t(e) * DDD + i] = out[i];
 }
 
@@ -312,9 +145,20 @@ __global__ void evec_gather_kernel(const int32_t* __restrict__ toff,
       y[g] = (bc_mode == 1) ? x[g] : bc_value;
       continue;
     }
+    // four entries at a time: their loads in flight together, the sum in index order
     T s = T(0);
     const int32_t k1 = toff[g + 1];
-    for (int32_t k = toff[g]; k < k1; ++k) s += ye[tidx[k]];
+    for (int32_t k = toff[g]; k < k1; k += 4) {
+      int32_t i[4];
+      T v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) i[j] = tidx[min(k + j, k1 - 1)];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = ye[i[j]];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (k + j < k1) s += v[j];
+    }
     y[g] = s;
   }
 }
@@ -365,12 +209,7 @@ void launch_qdata(const DevSpace& sp, int kind, int q1d, const double* coeff, do
     HIP_LAUNCH_CHECK();
     return;
   }
-  const TabView tv = tab_view(sp, q1d);
-  const int NN = sp.ng * sp.ng * sp.ng;
-  const size_t lds = sizeof(double) * (3 * NN + 2 * q1d * sp.ng);
-  hipLaunchKernelGGL(qdata_kernel, dim3(unsigned(sp.ne)), dim3(256), lds, st, sp.gnodes,
-                     sp.elem_orig, sp.ng, tv, q1d, kind, coeff, scale, qd, sp.status);
-  HIP_LAUNCH_CHECK();
+  launch_qdata_tiles(sp, kind, q1d, coeff, scale, qd, st);
 }
 
 void launch_linear_form_evec(const DevSpace& sp, int q1d, int source, const double* fqp,
@@ -378,6 +217,10 @@ void launch_linear_form_evec(const DevSpace& sp, int q1d, int source, const doub
   if (sp.dim == 2) {
     launch_linear_form_evec_2d(sp, q1d, source, fqp, scale, ye, st);
     HIP_LAUNCH_CHECK();
+    return;
+  }
+  if (q1d == sp.p + 2) {
+    launch_linear_form_tiles(sp, source, fqp, scale, ye, st);
     return;
   }
   const TabView tv = tab_view(sp, q1d);
@@ -396,13 +239,9 @@ void launch_diagonal_evec(const DevSpace& sp, int kind, int q1d, const double* q
     HIP_LAUNCH_CHECK();
     return;
   }
-  const TabView tv = tab_view(sp, q1d);
-  const int Q = q1d, D = sp.p + 1;
-  const size_t lds =
-      sizeof(double) * (3 * Q * D + Q * Q * Q + Q * Q * D + Q * D * D + D * D * D);
-  hipLaunchKernelGGL(diagonal_kernel, dim3(unsigned(sp.ne)), dim3(256), lds, st, tv, Q, D, kind,
-                     qd, ye);
-  HIP_LAUNCH_CHECK();
+  if (q1d != sp.p + 2)
+    throw Error(PAFEM_EUNSUPPORTED, "diagonal: operators have q1d = p + 2");
+  launch_diagonal_tiles(sp, kind, qd, ye, st);
 }
 
 void launch_evec_gather(const DevSpace& sp, const double* ye, const double* x, int bc_mode,
