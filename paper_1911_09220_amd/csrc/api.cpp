@@ -70,11 +70,7 @@ void apply_op(const Op& op, const void* x, void* y, void* work, hipStream_t st, 
   const int vdt = vector_dtype(op.qdtype);
   if (op.kind == PAFEM_DG_CONVECTION) {
     const double* qd = static_cast<const double*>(op.qdata);
-    // the volume kernel stores every dof (each belongs to one element); the faces add
-    require(launch_pa_apply(s.dev, op.kind, op.q1d, PAFEM_F64, false, false, qd, x, y,
-                            PAFEM_F64, st, nullptr),
-            PAFEM_EUNSUPPORTED, "DG volume kernel not built for this order/q1d");
-    launch_dg_faces(s.dev, op.q1d, qd + qdata_values(s.ne, op.q1d, 3),
+    launch_dg_apply(s.dev, op.q1d, qd, qd + qdata_values(s.ne, op.q1d, 3),
                     static_cast<const double*>(x), static_cast<double*>(y), st);
     return;
   }
@@ -396,6 +392,7 @@ pafem_status pafem_space_upload(pafem_space space, void* device_buf, size_t nbyt
     up(15, s.faces.data(), s.faces.size() * 4, "upload faces");
     up(16, s.bfaces.data(), s.bfaces.size() * 4, "upload boundary faces");
     up(17, s.tile_priv.data(), s.tile_priv.size() * 4, "upload private dof counts");
+    up(19, s.efaces.data(), s.efaces.size() * 4, "upload faces by element");
     up(18, s.shared.data(), s.shared.size() * 4, "upload shared dofs");
     hip_check(hipStreamSynchronize(st), "upload sync");
     s.dev_buf = device_buf;
@@ -423,6 +420,7 @@ pafem_status pafem_space_upload(pafem_space space, void* device_buf, size_t nbyt
     s.dev.nbfaces = int64_t(s.bfaces.size() / 2);
     s.dev.tile_priv = reinterpret_cast<const int32_t*>(base + off[17]);
     s.dev.shared = reinterpret_cast<const int32_t*>(base + off[18]);
+    s.dev.efaces = s.efaces.empty() ? nullptr : reinterpret_cast<const int32_t*>(base + off[19]);
     s.dev.nshared = int64_t(s.shared.size());
     s.dev.ne = s.ne;
     s.dev.ndofs = s.ndofs;

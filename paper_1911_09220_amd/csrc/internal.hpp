@@ -149,6 +149,7 @@ struct DevSpace {
   const double* tables_open = nullptr; // Nedelec: open-basis tables for q1d = 1..kMaxQ1d
   const int32_t* faces = nullptr;      // L2: interior faces [nfaces][kFaceInts]
   const int32_t* bfaces = nullptr;     // L2: boundary faces [nbfaces][2]
+  const int32_t* efaces = nullptr;     // L2: [ne][6][kElemFaceInts] faces by element
   int64_t nfaces = 0, nbfaces = 0;
   int64_t nshared = 0;
   int64_t ne = 0, ndofs = 0;
@@ -192,6 +193,11 @@ constexpr int kFamilyL2 = 2;
 // bit 0 swap, bit 1 reverse u, bit 2 reverse v, mapping the "-" side's face indices
 // (s, t) to the "+" side's (u, v); s, u along the lower tangential axis)
 constexpr int kFaceInts = 3;
+// face f of an element of an L2 space: its number (interior faces, then boundary ones), the
+// first dof of the element across it (-1: none), and code = s | f' << 1 | orientation << 4:
+// s = 1 on the face's "+" element, f' the neighbour's local face, the orientation from this
+// element's face indices to the neighbour's; one unused word (16-byte records)
+constexpr int kElemFaceInts = 4;
 // the family an operator kind needs
 inline int kind_family(int kind) {
   return nd_kind(kind) ? kFamilyND : l2_kind(kind) ? kFamilyL2 : kFamilyH1;
@@ -219,6 +225,7 @@ struct Space {
   std::vector<double> tables;     // build_tables(p, ng)
   std::vector<int8_t> gsign;      // Nedelec: [ne][dpe] dof signs, caller element order
   std::vector<int32_t> faces;     // L2: [nfaces][kFaceInts] interior faces (device elements)
+  std::vector<int32_t> efaces;    // L2: [ne][6][kElemFaceInts], device element order
   std::vector<int32_t> bfaces;    // L2: [nbfaces][2] boundary faces (device element, face)
   std::vector<double> tables_open;  // Nedelec: build_open_tables(p)
   // device image (caller-owned buffer)
@@ -240,7 +247,7 @@ inline int nd_dofs_per_elem(int p) { return 3 * p * (p + 1) * (p + 1); }
 Space* build_l2_space(const Mesh* mesh, int order, int flags);
 void space_dof_coords(const Space& s, double* xyz);
 constexpr int kLineDofs = 16;  // FP64 values of a 128-byte cache line
-constexpr int kSpaceSegments = 19;
+constexpr int kSpaceSegments = 20;
 // words of the per-element owner bitmask (bit i of element k: node i is the first
 // occurrence of its dof in device element order)
 inline int owner_words(int dpe) { return (dpe + 31) / 32; }

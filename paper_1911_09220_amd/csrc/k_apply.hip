@@ -75,20 +75,17 @@ __global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, KIND != PAFEM_DI
   constexpr bool DIFF = (K0 == PAFEM_DIFFUSION) || GEOM;  // gradient in, gradient out
   // CONV: convection, gradient in, value out (the back contractions are the mass ones)
   constexpr bool CONV = (K0 == PAFEM_CONVECTION);
-  // DGV: volume term of the DG convection, -(u, beta . grad v): value in, gradient out
-  // (the forward contractions are the mass ones, the back ones the diffusion ones)
-  constexpr bool DGV = (K0 == PAFEM_DG_CONVECTION);
   // GRADV: gradient into a vector-valued output, gradient in, 3 values out (each
   // contracted back with B only), output component c at y + c * ystride
   constexpr bool GRADV = (K0 == PAFEM_GRADIENT);
   constexpr bool GRAD = DIFF || CONV || GRADV || DIVV;  // the forward contractions produce the gradient
-  constexpr bool BACK3 = DIFF || GRADV || DGV;  // three arrays in the back contractions
-  constexpr bool BACKD = DIFF || DGV;           // gradient back contractions
+  constexpr bool BACK3 = DIFF || GRADV;  // three arrays in the back contractions
+  constexpr bool BACKD = DIFF;           // gradient back contractions
   // values per point in registers; DIVV stores 9 and reads those of one input component
-  constexpr int NC = GEOM ? 1 : DIFF ? 6 : (CONV || DIVV || DGV) ? 3 : GRADV ? 9 : 1;
+  constexpr int NC = GEOM ? 1 : DIFF ? 6 : (CONV || DIVV) ? 3 : GRADV ? 9 : 1;
   constexpr int NCT = (DIVV || GRADC) ? 9 : NC;  // stored values per point
   constexpr int NA = GRAD ? 2 : 1;   // arrays after the x-lines (B and G along x)
-  constexpr int NCC = (GRAD || DGV) ? 3 : 1;  // arrays after the y-lines (one per derivative)
+  constexpr int NCC = GRAD ? 3 : 1;  // arrays after the y-lines (one per derivative)
   constexpr int NOUT = GRADV ? 3 : 1;  // output components
   // Tiles store their private dofs and add only the others atomically: the mass action at
   // p >= 3, whose scatter is a third of its time (p = 4 / 5 / 6 / 7 / 8 at ~1.7M dofs 44.4 /
@@ -96,9 +93,8 @@ __global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, KIND != PAFEM_DI
   // other dofs alone), and the convection (p = 5..8 2-5%).  At p <= 2 few lines are a
   // tile's own (no difference); the diffusion at p = 5..7 and the divergence were 3-14%
   // slower (their registers are at the occupancy limit), the H(curl) one equal.
-  constexpr bool PRIV = DGV || (sizeof(TV) == 8 && has_private(K0, P));
-  static_assert(!((CONV || GRADV || DIVV || DGV) && DOT), "the convection, gradient and divergence operators have no energy");
-  static_assert(!(DGV && EVEC), "the DG volume term stores through the tile lists");
+  constexpr bool PRIV = sizeof(TV) == 8 && has_private(K0, P);
+  static_assert(!((CONV || GRADV || DIVV) && DOT), "the convection, gradient and divergence operators have no energy");
   static_assert(!((GRADV || DIVV) && EVEC), "the gradient and divergence operators use the atomic scatter");
   static_assert(NOUT * D <= NCC * Q, "back x-line arrays must fit the element region");
   static_assert(NV == 1 || DIVV || (!DOT && !EVEC && (K0 == PAFEM_MASS || K0 == PAFEM_DIFFUSION)),
@@ -442,19 +438,6 @@ __global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, KIND != PAFEM_DI
 #pragma unroll
           for (int dz = 0; dz < D; ++dz) t0[dz] += rb[dz] * sdiv[qz];
         }
-      } else if constexpr (DGV) {
-        // -u (w adj(J) beta) . grad_ref v: the value at the point times minus the stored
-        // vector, contracted back against the reference gradient
-        TC u = TC(0);
-#pragma unroll
-        for (int dz = 0; dz < D; ++dz) u += rb[dz] * c0[dz];
-        const TC vx = -dq[qz][0] * u, vy = -dq[qz][1] * u, vz = -dq[qz][2] * u;
-#pragma unroll
-        for (int dz = 0; dz < D; ++dz) {
-          t0[dz] += rb[dz] * vx;
-          t1[dz] += rb[dz] * vy;
-          t2[dz] += rg[dz] * vz;
-        }
       } else if constexpr (CONV) {
         // (beta . grad u) at the point: w adj(J) beta . (reference gradient)
         TC ux = TC(0), uy = TC(0), uz = TC(0);
@@ -603,10 +586,8 @@ __global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, KIND != PAFEM_DI
   }
   if (EVEC) return;
   __syncthreads();
-  // G^t: per unique dof of the tile one store (dofs of this tile alone) or one global
-  // atomic.  The DG volume term's dofs belong to one element each, so it only stores (the
-  // face kernel adds its atomics afterwards).
-  const int np = DGV ? nu : PRIV ? tile_priv[tile] : 0;
+  // G^t: per unique dof of the tile one store (its private dofs) or one global atomic
+  const int np = PRIV ? tile_priv[tile] : 0;
   auto put = [&](int s, int g, int oc) {
     TV* const dst = &y[(DIVV ? 0 : GRADC ? GC : comp + oc) * ystride + (g < 0 ? ~g : g)];
     const TV v = TV(sX[oc * NE * DDD + s]);
@@ -735,12 +716,6 @@ bool launch_order(const DevSpace& sp, int kind, int qdtype, int vdtype, bool con
     if (vdtype != PAFEM_F64 || qdtype != PAFEM_F64 || dotp || evec) return false;
     launch_one<P, PAFEM_DIVERGENCE, false, false, double, double, double>(sp, constrained, qd, x,
                                                                            out, nullptr, st);
-    return true;
-  }
-  if (kind == PAFEM_DG_CONVECTION) {
-    if (vdtype != PAFEM_F64 || qdtype != PAFEM_F64 || dotp || evec) return false;
-    launch_one<P, PAFEM_DG_CONVECTION, false, false, double, double, double>(sp, false, qd, x,
-                                                                              out, nullptr, st);
     return true;
   }
   if (kind == PAFEM_CONVECTION) {

@@ -1,15 +1,13 @@
-// Face terms of the upwind DG convection on a discontinuous nodal space of hexahedra
-// (convection "including DG" among the partially assembled integrators of "GPU
-// Acceleration"); the volume term runs in the fused apply (k_apply.hip).
+// Upwind DG convection on a discontinuous nodal space of hexahedra (convection "including
+// DG" among the partially assembled integrators of "GPU Acceleration"): the volume and the
+// face terms in one kernel, and the setup of the face values.
 //
 // With the Gauss-Lobatto nodes the trace of an element function on one of its faces
-// depends only on the (p+1)^2 dofs of that face, so a face needs no more than its two
-// sides' face dofs: each side's trace is evaluated at the Q x Q Gauss points of the
-// face by two one-axis contractions, the upwind value times the stored w (beta . N)
-// is formed at each point (the "+" side's points reached through the face's
-// orientation), and the flux is contracted back onto both sides' face dofs (with
-// opposite signs) and added to y with FP64 atomics.  Boundary faces keep the outflow
-// part only (zero inflow data).  One workgroup holds several faces, Q*Q threads each.
+// depends only on the (p+1)^2 dofs of that face, so an element needs no more of a
+// neighbour than those.  At each Gauss point of a face the upwind value times the stored
+// w (beta . N) is formed (the neighbour's points reached through the face's orientation)
+// and contracted back onto the element's face dofs.  Boundary faces keep the outflow part
+// only (zero inflow data).
 #include "device.hpp"
 #include "launch.hpp"
 
@@ -65,7 +63,7 @@ __device__ inline void geom_basis(int NG, int j, double x, double& val, double& 
 // w_s w_t scale (beta . N) at the Q x Q Gauss points of every face, N = T_b x T_c
 // oriented outward from the face's first element (the interior face's "-" side); after
 // them, one 8-byte slot per face with its two elements' caller indices (the dof blocks
-// the face kernel reads and writes), so the apply needs no lookup through elem_orig
+// a kernel over the faces reads and writes)
 __global__ void dg_face_qdata_kernel(const int32_t* __restrict__ faces,
                                      const int32_t* __restrict__ bfaces, int64_t nf, int64_t nb,
                                      const int32_t* __restrict__ orig,
@@ -128,142 +126,324 @@ __global__ void dg_face_qdata_kernel(const int32_t* __restrict__ faces,
   }
 }
 
+// One workgroup = one tile of the volume data (k_apply.hip's tiles), Q*Q threads per
+// element, everything one 1D line per thread.  Face stages, on the 6 faces of every
+// element at once and in the element's own frame of each face:
+//   lines (f, j): the D face dofs of both sides, own from LDS, the neighbour's straight from
+//                 x into registers through the orientation; contracted to Q values each
+//   lines (f, q): the other axis for both sides, the upwind flux at the line's Q points,
+//                 contracted back along the same axis in registers
+//   lines (f, j): contracted back to the D face dofs, kept in registers
+// then the volume term (mass contractions forward, -u (w adj(J) beta) at the points,
+// gradient contractions back), the face lines' results added per dof in LDS on the way.
+//
+// Every interior face is evaluated from both sides (a quarter more arithmetic) so that each
+// element writes its own dofs once, with plain stores.  A kernel over the faces, after the
+// volume one, added 2 (p+1)^2 FP64 atomics per face, which go to memory one by one: 166 of
+// the 266 us at p = 4 on 40^3 elements; fused 138 us.
 template <int P>
-constexpr int faces_per_block() {
-  return (256 / ((P + 2) * (P + 2))) > 0 ? (256 / ((P + 2) * (P + 2))) : 1;
-}
+__global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2))
+    dg_apply_kernel(const int32_t* __restrict__ gmap, const int4* __restrict__ efaces,
+                    const double* __restrict__ tabB, const double* __restrict__ tabG,
+                    const double* __restrict__ qd, const double* __restrict__ fq,
+                    const double* __restrict__ x, double* __restrict__ y, int ne) {
+  constexpr int Q = P + 2, D = P + 1, QQ = Q * Q, DD = D * D, DDD = DD * D;
+  constexpr int NE = qdata_tile(Q), NT = NE * QQ;
+  constexpr int LC = D | 1, QL = Q | 1;
+  constexpr int VOL = 3 * QQ * LC, FACE = 12 * D * QL;
+  constexpr int ELEM = VOL > FACE ? VOL : FACE;
+  constexpr int RD = (6 * D + QQ - 1) / QQ, RQ = (6 * Q + QQ - 1) / QQ;  // lines per thread
+  __shared__ double sW[NE * ELEM];
+  __shared__ double sX[NE * DDD];
 
-template <int P>
-__global__ void __launch_bounds__(faces_per_block<P>() * (P + 2) * (P + 2))
-    dg_face_kernel(const int32_t* __restrict__ faces, const int32_t* __restrict__ bfaces,
-                   int64_t nf, int64_t nb, const double* __restrict__ tabB,
-                   const double* __restrict__ fq,
-                   const double* __restrict__ x, double* __restrict__ y) {
-  constexpr int Q = P + 2, D = P + 1, QQ = Q * Q, DD = D * D, DDD = D * D * D;
-  constexpr int FPB = faces_per_block<P>();
-  constexpr int PER = 2 * DD + 4 * Q * D + 4 * QQ;  // LDS values per face
-  __shared__ double sm[FPB * PER];
-  const int lf = threadIdx.x / QQ, r = threadIdx.x - lf * QQ;
-  const int64_t g = int64_t(blockIdx.x) * FPB + lf;
-  const bool act = g < nf + nb;
-  const bool inner = g < nf;
-  double* uM = sm + lf * PER;
-  double* uP = uM + DD;
-  double* tM = uP + DD;
-  double* tP = tM + Q * D;
-  double* vM = tP + Q * D;
-  double* vP = vM + QQ;
-  double* FM = vP + QQ;
-  double* FP = FM + QQ;
-  double* sM = FP + QQ;
-  double* sP = sM + Q * D;
-  auto bB = [&](int q, int d) { return tabB[q * D + d]; };
-
-  int fm = 0, fp = 0, orient = 0;
-  int2 eo = {0, 0};  // the two sides' caller element indices
-  if (act) {
-    eo = reinterpret_cast<const int2*>(fq + (nf + nb) * QQ)[g];
-    if (inner) {
-      const int code = faces[g * kFaceInts + 2];
-      fm = code & 7;
-      fp = (code >> 3) & 7;
-      orient = code >> 6;
-    } else {
-      fm = bfaces[(g - nf) * 2 + 1];
-    }
-  }
-  // face node (i, j) of face f of an element -> lexicographic element dof
-  auto face_dof = [&](int f, int i, int j) {
-    int a, b, c;
-    face_axes(f, a, b, c);
-    int idx[3];
-    idx[a] = (f & 1) ? P : 0;
-    idx[b] = i;
-    idx[c] = j;
-    return idx[0] + D * (idx[1] + D * idx[2]);
+  const int tid = threadIdx.x, el = tid / QQ, r = tid - el * QQ;
+  const int tile = xcd_remap(blockIdx.x, gridDim.x);
+  const int e = tile * NE + el;
+  const bool act = e < ne;
+  double* const W = sW + el * ELEM;
+  double* const X = sX + el * DDD;
+  auto at = [&](int c, int qy, int qx, int dz) -> double& {
+    return W[((c * Q + qy) * Q + qx) * LC + dz];
   };
-  const int64_t baseM = int64_t(eo.x) * DDD;
-  const int64_t baseP = inner ? int64_t(eo.y) * DDD : 0;
+  // face arrays: side h (0 own, 1 neighbour), line (f, j), q
+  auto fa = [&](int h, int f, int j, int q) -> double& { return W[((h * 6 + f) * D + j) * QL + q]; };
+  // at p = 8 the table entries are loaded per loop iteration (k_apply.hip)
+  auto tab = [&](const double* t) {
+    if constexpr (P >= 8)
+      return opaque_ptr(t);
+    else
+      return t;
+  };
+  auto rowB = [&](int q) { return tab(tabB + q * D); };
+  auto rowG = [&](int q) { return tab(tabG + q * D); };
+  auto colB = [&](int d) { return tab(tabB + d); };
+  auto colG = [&](int d) { return tab(tabG + d); };
+  // first dof and strides of the face lines of face f: node (i, j) at base + i si + j sj
+  auto face_base = [](int f) { return (f & 1) ? P * (f < 2 ? 1 : f < 4 ? D : DD) : 0; };
+  auto stride_i = [](int f) { return f < 2 ? D : 1; };
+  auto stride_j = [](int f) { return f < 4 ? DD : D; };
 
-  if (act && r < DD) {
-    const int i = r % D, j = r / D;
-    uM[r] = x[baseM + face_dof(fm, i, j)];
-    uP[r] = inner ? x[baseP + face_dof(fp, i, j)] : 0.0;
-  }
-  __syncthreads();
-  if (act && r < Q * D) {
-    const int q = r % Q, j = r / Q;
-    double am = 0.0, ap = 0.0;
-#pragma unroll
-    for (int i = 0; i < D; ++i) {
-      am += bB(q, i) * uM[i + D * j];
-      ap += bB(q, i) * uP[i + D * j];
-    }
-    tM[r] = am;
-    tP[r] = ap;
-  }
-  __syncthreads();
+  // the volume data of this thread's z-line
+  double dq[Q][3];
   if (act) {
-    const int qs = r % Q, qt = r / Q;
-    double am = 0.0, ap = 0.0;
+    const double* const qe = qd + size_t(tile) * (3 * Q * NT) + tid;
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
-      am += bB(qt, j) * tM[qs + Q * j];
-      ap += bB(qt, j) * tP[qs + Q * j];
+    for (int qz = 0; qz < Q; ++qz)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) dq[qz][c] = load_value<double, double>(qe + (c * Q + qz) * NT);
+  }
+  // the element's dofs (one contiguous block) into LDS
+  const int own = act ? gmap[size_t(e) * DDD] : 0;
+  if (act)
+    for (int i = r; i < DDD; i += QQ) X[i] = x[own + i];
+  // the neighbours' face dofs of this thread's lines (f, j), in this element's frame
+  double nb[RD][D];
+#pragma unroll
+  for (int k = 0; k < RD; ++k) {
+    const int l = r + k * QQ, f = l / D, j = l - f * D;
+#pragma unroll
+    for (int i = 0; i < D; ++i) nb[k][i] = 0.0;
+    if (act && l < 6 * D) {
+      const int4 rec = efaces[size_t(e) * 6 + f];
+      if (rec.y >= 0) {
+        const int g = (rec.z >> 1) & 7, o = rec.z >> 4;
+        // (i, j) -> (u, v): u = i or j, reversed or not; so a line along i is a line there
+        const int si = stride_i(g), sj = stride_j(g);
+        const int su = (o & 2) ? -si : si, sv = (o & 4) ? -sj : sj;
+        const int b0 = rec.y + face_base(g) + ((o & 2) ? P * si : 0) + ((o & 4) ? P * sj : 0);
+        const int step = (o & 1) ? sv : su;
+        const double* const xn = x + (b0 + j * ((o & 1) ? su : sv));
+#pragma unroll
+        for (int i = 0; i < D; ++i) nb[k][i] = xn[i * step];
+      }
     }
-    vM[r] = am;
-    vP[r] = ap;
   }
   __syncthreads();
+
+  // face lines (f, j)
+#pragma unroll
+  for (int k = 0; k < RD; ++k) {
+    const int l = r + k * QQ, f = l / D, j = l - f * D;
+    if (act && l < 6 * D) {
+      double u[D];
+      const int b0 = face_base(f) + j * stride_j(f), si = stride_i(f);
+#pragma unroll
+      for (int i = 0; i < D; ++i) u[i] = X[b0 + i * si];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const auto rb = rowB(q);
+        double a = 0.0, b = 0.0;
+#pragma unroll
+        for (int i = 0; i < D; ++i) {
+          a += rb[i] * u[i];
+          b += rb[i] * nb[k][i];
+        }
+        fa(0, f, j, q) = a;
+        fa(1, f, j, q) = b;
+      }
+    }
+  }
+  // weights of the lines (f, q), outward from this element; the face's own frame is its
+  // "-" element's
+  double w[RQ][Q];
+#pragma unroll
+  for (int k = 0; k < RQ; ++k) {
+    const int l = r + k * QQ, f = l / Q, q = l - f * Q;
+    if (act && l < 6 * Q) {
+      const int4 rec = efaces[size_t(e) * 6 + f];
+      const double* const wf = fq + size_t(rec.x) * QQ;
+      const bool plus = rec.z & 1;
+#pragma unroll
+      for (int t = 0; t < Q; ++t) {
+        const double v = wf[plus ? face_perm(rec.z >> 4, q, t, Q) : q + Q * t];
+        w[k][t] = plus ? -v : v;
+      }
+    }
+  }
+  __syncthreads();
+  // face lines (f, q): values, upwind flux, back along the same axis
+#pragma unroll
+  for (int k = 0; k < RQ; ++k) {
+    const int l = r + k * QQ, f = l / Q, q = l - f * Q;
+    if (act && l < 6 * Q) {
+      double a[D], b[D], o[D];
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        a[j] = fa(0, f, j, q);
+        b[j] = fa(1, f, j, q);
+        o[j] = 0.0;
+      }
+#pragma unroll
+      for (int t = 0; t < Q; ++t) {
+        const auto rb = rowB(t);
+        double va = 0.0, vb = 0.0;
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+          va += rb[j] * a[j];
+          vb += rb[j] * b[j];
+        }
+        const double F = w[k][t] * (w[k][t] > 0.0 ? va : vb);
+#pragma unroll
+        for (int j = 0; j < D; ++j) o[j] += rb[j] * F;
+      }
+#pragma unroll
+      for (int j = 0; j < D; ++j) fa(0, f, j, q) = o[j];
+    }
+  }
+  __syncthreads();
+  // face lines (f, j): back to the face dofs, kept in registers until the volume's x-lines
+  // have read the element's dofs
+  double fv[RD][D];
+#pragma unroll
+  for (int k = 0; k < RD; ++k) {
+    const int l = r + k * QQ, f = l / D, j = l - f * D;
+    if (act && l < 6 * D) {
+      double in[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) in[q] = fa(0, f, j, q);
+#pragma unroll
+      for (int i = 0; i < D; ++i) {
+        const auto cb = colB(i);
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) s += cb[q * D] * in[q];
+        fv[k][i] = s;
+      }
+    }
+  }
+  // volume, along x: thread (dz, dy)
+  const bool xline = act && r < DD, yline = act && r < D * Q;
+  const int xz = r / D, xy = r - xz * D, l1 = r / Q, l0 = r - l1 * Q;
+  double u[D];
+  if (xline) {
+#pragma unroll
+    for (int dx = 0; dx < D; ++dx) u[dx] = X[r * D + dx];
+  }
+  __syncthreads();  // the face lines have read the region, the x-lines the dofs
+  if (xline) {
+#pragma unroll
+    for (int qx = 0; qx < Q; ++qx) {
+      const auto rb = rowB(qx);
+      double b = 0.0;
+#pragma unroll
+      for (int dx = 0; dx < D; ++dx) b += rb[dx] * u[dx];
+      at(xy / Q, xy % Q, qx, xz) = b;
+    }
+  }
+  if (act)
+    for (int i = r; i < DDD; i += QQ) X[i] = 0.0;
+  __syncthreads();
+  // the face terms, per dof
+#pragma unroll
+  for (int k = 0; k < RD; ++k) {
+    const int l = r + k * QQ, f = l / D, j = l - f * D;
+    if (act && l < 6 * D) {
+      const int b0 = face_base(f) + j * stride_j(f), si = stride_i(f);
+#pragma unroll
+      for (int i = 0; i < D; ++i) atomicAdd(&X[b0 + i * si], fv[k][i]);
+    }
+  }
+  // along y: thread (dz, qx)
+  if (yline) {
+    double a[D];
+#pragma unroll
+    for (int dy = 0; dy < D; ++dy) a[dy] = at(dy / Q, dy % Q, l0, l1);
+#pragma unroll
+    for (int qy = 0; qy < Q; ++qy) {
+      const auto rb = rowB(qy);
+      double b = 0.0;
+#pragma unroll
+      for (int dy = 0; dy < D; ++dy) b += rb[dy] * a[dy];
+      at(0, qy, l0, l1) = b;
+    }
+  }
+  __syncthreads();
+  // along z, the points, back along z: thread (qy, qx)
   if (act) {
-    // upwind flux at the "-" side's point r; the "+" side's value at its own index
-    const int qs = r % Q, qt = r / Q;
-    const double w = fq[size_t(g) * QQ + r];
-    if (inner) {
-      const int rp = face_perm(orient, qs, qt, Q);
-      const double F = w > 0.0 ? w * vM[r] : w * vP[rp];
-      FM[r] = F;
-      FP[rp] = -F;
-    } else {
-      FM[r] = w > 0.0 ? w * vM[r] : 0.0;
-      FP[r] = 0.0;
+    double c[D], t0[D], t1[D], t2[D];
+#pragma unroll
+    for (int dz = 0; dz < D; ++dz) {
+      c[dz] = at(0, l1, l0, dz);
+      t0[dz] = t1[dz] = t2[dz] = 0.0;
+    }
+#pragma unroll
+    for (int qz = 0; qz < Q; ++qz) {
+      const auto rb = rowB(qz);
+      const auto rg = rowG(qz);
+      double v = 0.0;
+#pragma unroll
+      for (int dz = 0; dz < D; ++dz) v += rb[dz] * c[dz];
+      const double vx = -dq[qz][0] * v, vy = -dq[qz][1] * v, vz = -dq[qz][2] * v;
+#pragma unroll
+      for (int dz = 0; dz < D; ++dz) {
+        t0[dz] += rb[dz] * vx;
+        t1[dz] += rb[dz] * vy;
+        t2[dz] += rg[dz] * vz;
+      }
+    }
+#pragma unroll
+    for (int dz = 0; dz < D; ++dz) {
+      at(0, l1, l0, dz) = t0[dz];
+      at(1, l1, l0, dz) = t1[dz];
+      at(2, l1, l0, dz) = t2[dz];
     }
   }
   __syncthreads();
-  if (act && r < Q * D) {
-    const int q = r % Q, j = r / Q;
-    double am = 0.0, ap = 0.0;
+  // back along y
+  if (yline) {
+    double v0[Q], v1[Q], v2[Q];
 #pragma unroll
-    for (int qt = 0; qt < Q; ++qt) {
-      am += bB(qt, j) * FM[q + Q * qt];
-      ap += bB(qt, j) * FP[q + Q * qt];
+    for (int qy = 0; qy < Q; ++qy) {
+      v0[qy] = at(0, qy, l0, l1);
+      v1[qy] = at(1, qy, l0, l1);
+      v2[qy] = at(2, qy, l0, l1);
     }
-    sM[r] = am;
-    sP[r] = ap;
+#pragma unroll
+    for (int dy = 0; dy < D; ++dy) {
+      const auto cb = colB(dy);
+      const auto cg = colG(dy);
+      double b = 0.0, g = 0.0;
+#pragma unroll
+      for (int qy = 0; qy < Q; ++qy) {
+        g += cb[qy * D] * v0[qy];
+        b += cg[qy * D] * v1[qy] + cb[qy * D] * v2[qy];
+      }
+      at(dy / Q, dy % Q, l0, l1) = b;
+      at((D + dy) / Q, (D + dy) % Q, l0, l1) = g;
+    }
   }
   __syncthreads();
-  if (act && r < DD) {
-    const int i = r % D, j = r / D;
-    double am = 0.0, ap = 0.0;
+  // back along x, onto the face terms
+  if (xline) {
+    double wB[Q], wG[Q];
 #pragma unroll
-    for (int q = 0; q < Q; ++q) {
-      am += bB(q, i) * sM[q + Q * j];
-      ap += bB(q, i) * sP[q + Q * j];
+    for (int qx = 0; qx < Q; ++qx) {
+      wB[qx] = at(xy / Q, xy % Q, qx, xz);
+      wG[qx] = at((D + xy) / Q, (D + xy) % Q, qx, xz);
     }
-    unsafeAtomicAdd(&y[baseM + face_dof(fm, i, j)], am);
-    if (inner) unsafeAtomicAdd(&y[baseP + face_dof(fp, i, j)], ap);
+#pragma unroll
+    for (int dx = 0; dx < D; ++dx) {
+      const auto cb = colB(dx);
+      const auto cg = colG(dx);
+      double s = 0.0;
+#pragma unroll
+      for (int qx = 0; qx < Q; ++qx) s += cb[qx * D] * wB[qx] + cg[qx * D] * wG[qx];
+      X[r * D + dx] += s;
+    }
   }
+  __syncthreads();
+  if (act)
+    for (int i = r; i < DDD; i += QQ) y[own + i] = X[i];
 }
 
 template <int P>
-void launch_faces_p(const DevSpace& sp, const double* tabB, const double* fq, const double* x,
-                    double* y, hipStream_t st) {
-  constexpr int Q = P + 2, FPB = faces_per_block<P>();
-  const int64_t total = sp.nfaces + sp.nbfaces;
-  if (total == 0) return;
-  const unsigned nblk = unsigned((total + FPB - 1) / FPB);
-  hipLaunchKernelGGL((dg_face_kernel<P>), dim3(nblk), dim3(FPB * Q * Q), 0, st, sp.faces,
-                     sp.bfaces, sp.nfaces, sp.nbfaces, tabB, fq, x, y);
+void launch_apply_p(const DevSpace& sp, const double* tabB, const double* qd, const double* fq,
+                    const double* x, double* y, hipStream_t st) {
+  constexpr int Q = P + 2, NE = qdata_tile(Q);
+  const unsigned nblk = unsigned((sp.ne + NE - 1) / NE);
+  hipLaunchKernelGGL((dg_apply_kernel<P>), dim3(nblk), dim3(NE * Q * Q), 0, st, sp.gmap,
+                     reinterpret_cast<const int4*>(sp.efaces), tabB, tabB + Q * (P + 1), qd, fq, x,
+                     y, int(sp.ne));
 }
 
 }  // namespace
@@ -279,20 +459,20 @@ void launch_dg_face_qdata(const DevSpace& sp, int q1d, const double* beta3, doub
   HIP_LAUNCH_CHECK_DG();
 }
 
-void launch_dg_faces(const DevSpace& sp, int q1d, const double* fq, const double* x, double* y,
-                     hipStream_t st) {
-  if (q1d != sp.p + 2) throw Error(PAFEM_EUNSUPPORTED, "DG faces are built for q1d = p + 2");
+void launch_dg_apply(const DevSpace& sp, int q1d, const double* qd, const double* fq,
+                     const double* x, double* y, hipStream_t st) {
+  if (q1d != sp.p + 2) throw Error(PAFEM_EUNSUPPORTED, "the DG apply is built for q1d = p + 2");
   const double* tabB = sp.tables + table_offset_doubles(q1d, sp.p + 1, sp.ng) + 2 * q1d;
   switch (sp.p) {
-    case 1: launch_faces_p<1>(sp, tabB, fq, x, y, st); break;
-    case 2: launch_faces_p<2>(sp, tabB, fq, x, y, st); break;
-    case 3: launch_faces_p<3>(sp, tabB, fq, x, y, st); break;
-    case 4: launch_faces_p<4>(sp, tabB, fq, x, y, st); break;
-    case 5: launch_faces_p<5>(sp, tabB, fq, x, y, st); break;
-    case 6: launch_faces_p<6>(sp, tabB, fq, x, y, st); break;
-    case 7: launch_faces_p<7>(sp, tabB, fq, x, y, st); break;
-    case 8: launch_faces_p<8>(sp, tabB, fq, x, y, st); break;
-    default: throw Error(PAFEM_EUNSUPPORTED, "DG faces: order not built");
+    case 1: launch_apply_p<1>(sp, tabB, qd, fq, x, y, st); break;
+    case 2: launch_apply_p<2>(sp, tabB, qd, fq, x, y, st); break;
+    case 3: launch_apply_p<3>(sp, tabB, qd, fq, x, y, st); break;
+    case 4: launch_apply_p<4>(sp, tabB, qd, fq, x, y, st); break;
+    case 5: launch_apply_p<5>(sp, tabB, qd, fq, x, y, st); break;
+    case 6: launch_apply_p<6>(sp, tabB, qd, fq, x, y, st); break;
+    case 7: launch_apply_p<7>(sp, tabB, qd, fq, x, y, st); break;
+    case 8: launch_apply_p<8>(sp, tabB, qd, fq, x, y, st); break;
+    default: throw Error(PAFEM_EUNSUPPORTED, "DG apply: order not built");
   }
   HIP_LAUNCH_CHECK_DG();
 }

@@ -54,9 +54,9 @@ int pa_apply_blocks(const DevSpace& sp);
 // every boundary face, Q^2 per face (beta = scale * beta3[0..2], device)
 void launch_dg_face_qdata(const DevSpace& sp, int q1d, const double* beta3, double scale,
                           double* fq, hipStream_t st);
-// adds the upwind face terms of the DG convection to y
-void launch_dg_faces(const DevSpace& sp, int q1d, const double* fq, const double* x, double* y,
-                     hipStream_t st);
+// y = the DG convection of x: qd the volume data, fq the face values
+void launch_dg_apply(const DevSpace& sp, int q1d, const double* qd, const double* fq,
+                     const double* x, double* y, hipStream_t st);
 // H(curl) mass / curl-curl / definite Maxwell apply on a Nedelec space (k_hcurl.hip);
 // false when the order, q1d or kind is not built
 bool launch_nd_apply(const DevSpace& sp, int kind, int q1d, bool constrained, const double* qd,

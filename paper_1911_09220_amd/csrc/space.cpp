@@ -932,6 +932,26 @@ Space* build_l2_space(const Mesh* mesh, int order, int flags) {
     s->bfaces.push_back(r[1]);
     s->bfaces.push_back(r[2]);
   }
+  // the same by element: what element k needs of its face f (kElemFaceInts)
+  s->efaces.assign(size_t(ne) * 6 * kElemFaceInts, 0);
+  auto base_of = [&](int32_t k) { return s->gmap[size_t(s->dev_order[size_t(k)]) * dpe]; };
+  auto put = [&](int32_t k, int f, int32_t face, int32_t base, int32_t code) {
+    int32_t* const r = s->efaces.data() + (size_t(k) * 6 + size_t(f)) * kElemFaceInts;
+    r[0] = face;
+    r[1] = base;
+    r[2] = code;
+  };
+  const int32_t nf = int32_t(recs.size());
+  for (int32_t i = 0; i < nf; ++i) {
+    const FaceRec& r = recs[size_t(i)];
+    const int fm = r.code & 7, fp = (r.code >> 3) & 7, o = r.code >> 6;
+    // the inverse of a symmetry of the square: the reversals change places with a swap
+    const int inv = (o & 1) ? 1 | ((o & 2) << 1) | ((o & 4) >> 1) : o;
+    put(r.em, fm, i, base_of(r.ep), (fp << 1) | (o << 4));
+    put(r.ep, fp, i, base_of(r.em), 1 | (fm << 1) | (inv << 4));
+  }
+  for (int32_t i = 0; i < int32_t(brecs.size()); ++i)
+    put(brecs[size_t(i)][1], brecs[size_t(i)][2], nf + i, -1, 0);
   return s;
 }
 
@@ -1067,7 +1087,8 @@ void space_device_layout(const Space& s, size_t* off, size_t* total) {
       sizeof(int32_t) * s.faces.size(),            // 15 L2 interior faces
       sizeof(int32_t) * s.bfaces.size(),           // 16 L2 boundary faces
       sizeof(int32_t) * s.tile_priv.size(),        // 17 private dofs of each tile
-      sizeof(int32_t) * s.shared.size(),           // 18 dofs of more than one tile
+      sizeof(int32_t) * s.shared.size(),           // 18 dofs that are not private
+      sizeof(int32_t) * s.efaces.size(),           // 19 L2 faces by element
   };
   for (int i = 0; i < kSpaceSegments; ++i) {
     off[i] = o;
