@@ -8,8 +8,13 @@
 // NRB right-hand sides with the rhs index fastest (coalesced X loads and Y
 // atomics, broadcast D loads, conflict-free LDS).  Table entries are the same for
 // every lane and come from scalar loads; the quadrature data D of a z-line is
-// loaded once into registers and reused for every right-hand side.  The
-// workgroup loops over the nrhs/NRB chunks.  All meshes of one order share one
+// read from L2 again for every chunk of right-hand sides, one plane ahead.  The
+// workgroup loops over the nrhs/NRB chunks.  Bound by latency at the waves that the
+// registers and LDS leave, and by the atomics.  16 right-hand sides in FP64, best tile, with D
+// in registers and every address kept across the chunks -> now: p = 2 (40^3 elements)
+// 367 -> 370 us, p = 3 (24^3) 263 -> 192, p = 4 (20^3) 442 -> 288, p = 5 (15^3) 278 -> 232,
+// p = 6 (12^3) 206 -> 206; FP32 274 -> 216, 173 -> 139, 274 -> 182, 187 -> 139, 174 -> 122.
+// An interior node's sum is stored (no other element has it), the others are added.  All meshes of one order share one
 // grouped launch: a workgroup finds its mesh from a prefix table of tile counts.
 #include "batch.hpp"
 #include "device.hpp"
@@ -18,8 +23,24 @@ namespace pafem {
 
 namespace {
 
+template <typename TC, typename TD>
+struct Pair {
+  typedef TD type __attribute__((ext_vector_type(2)));
+};
+
+// Waves per SIMD to compile for: what the LDS of the tile allows a CU, at most what the
+// z-line's arrays leave registers for.
+constexpr int mrhs_waves(int P, int threads, int lds) {
+  const int wgs = (160 * 1024) / lds, waves = wgs * ((threads + 63) / 64) / 4;
+  const int cap = P <= 1 ? 7 : P <= 3 ? 5 : P <= 5 ? 4 : 3;
+  return waves < 1 ? 1 : waves < cap ? waves : cap;
+}
+
 template <int P, int Q, int NE, int NRB, int KIND, typename TV, typename TD, typename TC>
-__global__ void __launch_bounds__(NE * Q * Q * NRB)
+__global__ void __launch_bounds__(NE * Q * Q * NRB,
+                                  mrhs_waves(P, NE * Q * Q * NRB,
+                                             NE * (KIND == PAFEM_DIFFUSION ? 3 : 1) * Q * Q *
+                                                 (P + 1) * NRB * int(sizeof(TC))))
     pa_apply_mrhs_kernel(const BatchMesh* __restrict__ meshes, int nmesh,
                          const TC* __restrict__ tabB, const TC* __restrict__ tabG, int nrhs) {
   constexpr int D = P + 1, DD = D * D, QQ = Q * Q;
@@ -38,44 +59,58 @@ __global__ void __launch_bounds__(NE * Q * Q * NRB)
   const BatchMesh& M = meshes[m];
   const int tile = blk - M.block_begin;
 
-  const int tid = threadIdx.x;
-  const int rb = tid % NRB;
-  const int pl = tid / NRB;  // line thread: (el, r)
-  const int el = pl / QQ;
-  const int r = pl - el * QQ;
-  const int e = tile * NE + el;
-  const bool act = e < M.ne;
   const int constrained = M.constrained;
-  TC* const W = sW + el * ELEM * NRB + rb;
-  // entry (c, qy, qx, dz) of this element and rhs; the x-line outputs (a, dz, dy, qx)
-  // live at c*Q + qy = a*D + dy
-  auto at = [&](int c, int qy, int qx, int dz) -> TC& {
-    return W[(((c * Q + qy) * Q + qx) * D + dz) * NRB];
-  };
   auto bB = [&](int q, int d) -> TC { return tabB[q * D + d]; };
   auto bG = [&](int q, int d) -> TC { return tabG[q * D + d]; };
-
-  // D of this thread's z-line (qy, qx) = r, reused for every chunk of right-hand sides
-  TC dq[Q][NC];
-  if (act) {
-    const TD* qd = static_cast<const TD*>(M.qdata);
-#pragma unroll
-    for (int qz = 0; qz < Q; ++qz)
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-        dq[qz][c] = load_value<TC, TD>(qd + qdata_index(e, c, qz * QQ + r, Q, NC));
-  }
-  // x-line (dz, dy) = r < D*D: the dofs of its D nodes (re-read where used: cached)
-  const bool xline = act && r < DD;
-  const int xz = r / D, xy = r - (r / D) * D;
-  const int32_t* __restrict__ gline = M.gmap + size_t(e) * (DD * D) + r * D;
-  const bool yline = act && r < D * Q;
-  const int yz = r / Q, yx = r - (r / Q) * Q;
-  const int zy = r / Q, zx = r - (r / Q) * Q;
   const TV* __restrict__ X = static_cast<const TV*>(M.x);
   TV* __restrict__ Y = static_cast<TV*>(M.y);
 
   for (int r0 = 0; r0 < nrhs; r0 += NRB) {
+    // everything below is derived from the thread index anew in every chunk: kept across
+    // the loop, the addresses of all stages were 40 registers at p = 4
+    int tid = threadIdx.x;
+    __asm__ volatile("" : "+v"(tid));
+    const int rb = tid % NRB;
+    const int pl = tid / NRB;  // line thread: (el, r)
+    const int el = NE == 1 ? 0 : pl / QQ;  // one element: e, and with it D's address, uniform
+    const int r = pl - el * QQ;
+    const int e = tile * NE + el;
+    const bool act = e < M.ne;
+    TC* const W = sW + el * ELEM * NRB + rb;
+    // entry (c, qy, qx, dz) of this element and rhs; the x-line outputs (a, dz, dy, qx)
+    // live at c*Q + qy = a*D + dy
+    auto at = [&](int c, int qy, int qx, int dz) -> TC& {
+      return W[(((c * Q + qy) * Q + qx) * D + dz) * NRB];
+    };
+    // D of this thread's z-line (qy, qx) = r, read again for every chunk of right-hand sides
+    // one plane ahead of its use (it stays in L2): held in registers (12 Q of them) it left
+    // one workgroup of 5 waves per CU at p = 4
+    constexpr int NT = qdata_tile(Q), PL = NT * QQ;  // elements of a qdata tile, values a plane
+    const TD* const qe = static_cast<const TD*>(M.qdata) + size_t(e / NT) * (NC * Q * PL) +
+                         (DIFF ? 2 : 1) * ((e % NT) * QQ);
+    const unsigned rq = (DIFF ? 2 : 1) * r;
+    TC dq[Q][NC];
+    auto load_plane = [&](int qz) {
+      if constexpr (DIFF) {
+        typedef typename Pair<TC, TD>::type pair_t;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          const pair_t v = *reinterpret_cast<const pair_t*>(qe + 2 * ((k * Q + qz) * PL) + rq);
+          dq[qz][2 * k] = TC(v.x);
+          dq[qz][2 * k + 1] = TC(v.y);
+        }
+      } else {
+        dq[qz][0] = TC(qe[qz * PL + rq]);
+      }
+    };
+    // x-line (dz, dy) = r < D*D: the dofs of its D nodes (re-read where used: cached)
+    const bool xline = act && r < DD;
+    const int xz = r / D, xy = r - (r / D) * D;
+    const bool xline_inner = xz > 0 && xz < P && xy > 0 && xy < P;
+    const int32_t* __restrict__ gline = M.gmap + size_t(e) * (DD * D) + r * D;
+    const bool yline = act && r < D * Q;
+    const int yz = r / Q, yx = r - (r / Q) * Q;
+    const int zy = r / Q, zx = r - (r / Q) * Q;
     const int rr = r0 + rb;
     // G and B along x: thread (dz, dy)
     if (xline) {
@@ -129,6 +164,7 @@ __global__ void __launch_bounds__(NE * Q * Q * NRB)
     __syncthreads();
     // B along z, D, B^t along z: thread (qy, qx), in place
     if (act) {
+      load_plane(0);
       TC c0[D], c1[D], c2[D];
 #pragma unroll
       for (int dz = 0; dz < D; ++dz) {
@@ -143,6 +179,8 @@ __global__ void __launch_bounds__(NE * Q * Q * NRB)
       for (int dz = 0; dz < D; ++dz) t0[dz] = t1[dz] = t2[dz] = TC(0);
 #pragma unroll
       for (int qz = 0; qz < Q; ++qz) {
+        if (qz + 1 < Q) load_plane(qz + 1);
+        __asm__ volatile("" ::: "memory");  // keep the next plane's loads in this iteration
         if (DIFF) {
           TC ux = TC(0), uy = TC(0), uz = TC(0);
 #pragma unroll
@@ -224,8 +262,11 @@ __global__ void __launch_bounds__(NE * Q * Q * NRB)
           if (DIFF) acc += bG(qx, dx) * wG[qx];
         }
         const int g = gline[dx];
-        if (!(constrained && g < 0))
-          unsafeAtomicAdd(&Y[size_t(g < 0 ? ~g : g) * nrhs + rr], TV(acc));
+        TV* const dst = &Y[size_t(g < 0 ? ~g : g) * nrhs + rr];
+        if (dx > 0 && dx < P && xline_inner)  // an interior node: no other element has it
+          *dst = TV(acc);
+        else if (!(constrained && g < 0))
+          unsafeAtomicAdd(dst, TV(acc));
       }
     }
     // the next chunk overwrites the element regions only after every thread is done
@@ -234,16 +275,28 @@ __global__ void __launch_bounds__(NE * Q * Q * NRB)
 }
 
 // Y = X on essential dofs (constrained) and 0 elsewhere, for every mesh of the
-// batch; blockIdx.y selects the mesh.
+// batch; blockIdx.y selects the mesh.  nrhs is even: a thread sets two right-hand sides
+// of a dof, and divides once instead of once per value.
 template <typename TV>
-__global__ void batch_init_kernel(const BatchMesh* __restrict__ meshes, int nrhs) {
+__global__ void __launch_bounds__(256)
+    batch_init_kernel(const BatchMesh* __restrict__ meshes, int nrhs) {
   const BatchMesh& M = meshes[blockIdx.y];
-  const int64_t total = int64_t(M.ndofs) * nrhs;
+  const int pairs = nrhs / 2;
+  const int rows = pairs < 256 ? 256 / pairs : 1;  // dofs of a workgroup
+  const int row = int(threadIdx.x) / pairs, p0 = int(threadIdx.x) - row * pairs;
+  if (pairs < 256 && row >= rows) return;
   const TV* __restrict__ X = static_cast<const TV*>(M.x);
   TV* __restrict__ Y = static_cast<TV*>(M.y);
-  for (int64_t k = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; k < total;
-       k += int64_t(gridDim.x) * blockDim.x)
-    Y[k] = (M.constrained && M.bmask[k / nrhs]) ? X[k] : TV(0);
+  for (int64_t g = int64_t(blockIdx.x) * rows + (pairs < 256 ? row : 0); g < M.ndofs;
+       g += int64_t(gridDim.x) * rows) {
+    const bool keep = M.constrained && M.bmask[g];
+    for (int p = pairs < 256 ? p0 : int(threadIdx.x); p < pairs; p += 256) {
+      const int64_t k = g * nrhs + 2 * p;
+      const TV a = keep ? X[k] : TV(0), b = keep ? X[k + 1] : TV(0);
+      Y[k] = a;
+      Y[k + 1] = b;
+    }
+  }
 }
 
 template <int P, int NE, int NRB, typename TV, typename TD, typename TC>
@@ -354,7 +407,7 @@ bool launch_batch_apply(int p, int cand, int vdtype, int qdtype, int kind,
 
 void launch_batch_init(int vdtype, const BatchMesh* meshes, int nmesh, int nrhs,
                        hipStream_t st) {
-  const dim3 grid(512, unsigned(nmesh));
+  const dim3 grid(1024, unsigned(nmesh));
   if (vdtype == PAFEM_F64)
     hipLaunchKernelGGL(batch_init_kernel<double>, grid, dim3(256), 0, st, meshes, nrhs);
   else
