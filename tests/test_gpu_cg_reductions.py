@@ -27,6 +27,8 @@ def test_pcg_iterates_equal_plain_cg(p, n, scatter, constrained):
     z = r / diag
     d, rz, hist = z.clone(), r @ z, [float(r.norm() / b.norm())]
     for _ in range(5):
+        if float(rz) == 0.0:
+            break
         q = A.apply(d)
         alpha = rz / (d @ q)
         ref += alpha * d
@@ -35,7 +37,8 @@ def test_pcg_iterates_equal_plain_cg(p, n, scatter, constrained):
         rz, old = r @ z, rz
         d = z + (rz / old) * d
         hist.append(float(r.norm() / b.norm()))
-    assert info["iters"] == 5 and info["status"] == "ENOTCONV"
+    # one free dof (1, 2): the first step is exact and may leave no residual at all
+    assert (info["iters"] == 5 and info["status"] == "ENOTCONV") or info["rel_res"] == 0.0
     # five iterations of FP64 sums of at most 1e6 terms: 5 * 1e6 * 2^-53 < 1e-9 at the very worst
     assert float((got - ref).norm() / ref.norm()) < 1e-9
     # the history is relative to ||b|| already (after an exact solve it is rounding alone)
