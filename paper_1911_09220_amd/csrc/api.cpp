@@ -703,7 +703,8 @@ pafem_status pafem_pcg_solve(pafem_op op, const double* diag, const double* b, d
       hip_check(hipStreamSynchronize(st), "solver sync");
       if (host.done || launched >= opts->max_iter) break;
       const int batch = std::min(check, opts->max_iter - launched);
-      if (graphs_enabled() && batch == check && check >= 2) {
+      if (graphs_enabled() && batch == check && check >= 2 &&
+          graph_pays(3 * check, opts->max_iter / check)) {
         if (!graph.ready()) graph.capture([&](hipStream_t cs) { iterations(cs, check); });
         graph.launch(st);
       } else {

@@ -18,6 +18,15 @@ namespace pafem {
 std::atomic<int>& graph_mode_flag();
 inline bool graphs_enabled() { return graph_mode_flag().load(std::memory_order_relaxed) != 0; }
 
+// Whether a solver should capture `kernels` launches that it will replay `replays` times at
+// most.  The graphs live for one solve, and capture and instantiation cost about 2 us a
+// kernel, while a replay gains nothing where the device is the slower side anyway: 200 CG
+// iterations in 2D (p = 4, 1.3M dofs) captured as one graph of 600 kernels took 10.9 ms,
+// launched directly 9.6; multigrid FCG at p = 3 (two iterations, about 90 kernels) 19.0
+// and 18.5 ms; PCG on 4913 dofs (24 kernels, replayed 9 times) 1.60 and 1.59 ms.  Short
+// sequences replayed often stay captured, for hosts that launch slower than this one.
+inline bool graph_pays(int kernels, int replays) { return kernels <= 64 && replays >= 16; }
+
 class CapturedGraph {
  public:
   CapturedGraph() = default;

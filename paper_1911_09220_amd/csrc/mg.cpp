@@ -497,8 +497,12 @@ pafem_status pafem_pmg_fcg_solve(pafem_pmg pmg, const double* b, double* x, void
       launch_fcg_beta(state, partials, r, zn, zc, hist, n, s2);
       launch_fcg_direction(state, partials, zn, p, qi, ess, n, s2);
     };
-    const bool graphs = graphs_enabled();
     int check = std::max(1, opts->check_every);
+    // a pair of iterations: per level 4 degree + 4 kernels, the coarse PCG 3 an iteration, and
+    // 4 of the outer iteration
+    const int pair_kernels =
+        2 * ((g.L - 1) * (4 * std::max(0, g.o.degree) + 4) + 3 * std::max(0, g.o.coarse_iters) + 4);
+    const bool graphs = graphs_enabled() && graph_pays(pair_kernels, opts->max_iter / 2);
     if (graphs) check += check & 1;  // whole pairs of iterations per host check
     CapturedGraph pair;               // two iterations, z -> zold -> z
     int launched = 0;
