@@ -127,7 +127,7 @@ void Batch::build_descriptors(const void* const* x, void* const* y) {
       M.ndofs = int32_t(sp.ndofs);
       M.block_begin = block;
       M.constrained = (o->flags & PAFEM_OP_CONSTRAINED) ? 1 : 0;
-      block += int((sp.ne + ne_tile - 1) / ne_tile);
+      block += int((sp.ne + ne_tile - 1) / ne_tile) * batch_chunks(g.cand, nrhs);
     }
   }
 }
@@ -136,7 +136,7 @@ int Batch::group_blocks(const Group& g) const {
   const int ne_tile = batch_tile_elems(g.cand);
   int blocks = 0;
   for (int k = g.first; k < g.first + g.count; ++k)
-    blocks += int((ops[order[k]]->space->ne + ne_tile - 1) / ne_tile);
+    blocks += int((ops[order[k]]->space->ne + ne_tile - 1) / ne_tile) * batch_chunks(g.cand, nrhs);
   return blocks;
 }
 

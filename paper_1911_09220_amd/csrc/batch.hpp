@@ -27,6 +27,11 @@ constexpr int kBatchCandidates = 6;
 constexpr int kBatchMfmaCandidate = 5;
 int batch_tile_elems(int cand);
 int batch_tile_rhs(int cand);
+// workgroups per tile: one per chunk of right-hand sides (the matrix-core variant walks
+// them itself)
+inline int batch_chunks(int cand, int nrhs) {
+  return cand == kBatchMfmaCandidate ? 1 : nrhs / batch_tile_rhs(cand);
+}
 // Launches the multi-rhs apply of one order group; false if the (order,
 // candidate, dtype) combination is not built.
 // tabB: the order's 1D B table followed by its G table, in the vector dtype

@@ -8,14 +8,17 @@
 // NRB right-hand sides with the rhs index fastest (coalesced X loads and Y
 // atomics, broadcast D loads, conflict-free LDS).  Table entries are the same for
 // every lane and come from scalar loads; the quadrature data D of a z-line is
-// read from L2 again for every chunk of right-hand sides, one plane ahead.  The
-// workgroup loops over the nrhs/NRB chunks.  Bound by latency at the waves that the
-// registers and LDS leave, and by the atomics.  16 right-hand sides in FP64, best tile, with D
-// in registers and every address kept across the chunks -> now: p = 2 (40^3 elements)
-// 367 -> 370 us, p = 3 (24^3) 263 -> 192, p = 4 (20^3) 442 -> 288, p = 5 (15^3) 278 -> 232,
-// p = 6 (12^3) 206 -> 206; FP32 274 -> 216, 173 -> 139, 274 -> 182, 187 -> 139, 174 -> 122.
-// An interior node's sum is stored (no other element has it), the others are added.  All meshes of one order share one
-// grouped launch: a workgroup finds its mesh from a prefix table of tile counts.
+// loaded one plane ahead of its use.  One workgroup per tile and chunk of NRB
+// right-hand sides; the chunks of a tile follow each other on one die, whose L2 keeps D and
+// the dof map.  All meshes of one order share one grouped launch: a workgroup finds its
+// mesh from a prefix table of workgroup counts.
+//
+// Bound by latency at the waves that the registers and LDS leave, and by the atomics (an
+// interior node's sum is stored, no other element has it; the others are added).  16
+// right-hand sides in FP64, best tile, with D and every stage's addresses held in
+// registers across a loop over the chunks (180 at p = 4: one workgroup of 5 waves per CU) ->
+// now: p = 1 (64^3 elements) 557 -> 491 us, p = 2 (40^3) 368 -> 343, p = 3 (24^3) 263 -> 186,
+// p = 4 (20^3) 442 -> 253, p = 5 (15^3) 280 -> 186, p = 6 (12^3) 207 -> 156; FP32 1.15-1.9x.
 #include "batch.hpp"
 #include "device.hpp"
 
@@ -52,12 +55,16 @@ __global__ void __launch_bounds__(NE * Q * Q * NRB,
 
   __shared__ TC sW[NE * ELEM * NRB];
 
-  // which mesh and which tile of it
+  // which mesh, which tile of it and which chunk of right-hand sides: consecutive
+  // workgroups of one die take the chunks of a tile and then its neighbour, so D, the dof
+  // map and the shared dofs' lines stay in that die's L2
   int m = 0;
-  const int blk = blockIdx.x;
+  const int blk = xcd_remap(blockIdx.x, gridDim.x);
   while (m + 1 < nmesh && meshes[m + 1].block_begin <= blk) ++m;
   const BatchMesh& M = meshes[m];
-  const int tile = blk - M.block_begin;
+  const int nchunk = nrhs / NRB;
+  const int tile = (blk - M.block_begin) / nchunk;
+  const int r0 = (blk - M.block_begin - tile * nchunk) * NRB;
 
   const int constrained = M.constrained;
   auto bB = [&](int q, int d) -> TC { return tabB[q * D + d]; };
@@ -65,212 +72,204 @@ __global__ void __launch_bounds__(NE * Q * Q * NRB,
   const TV* __restrict__ X = static_cast<const TV*>(M.x);
   TV* __restrict__ Y = static_cast<TV*>(M.y);
 
-  for (int r0 = 0; r0 < nrhs; r0 += NRB) {
-    // everything below is derived from the thread index anew in every chunk: kept across
-    // the loop, the addresses of all stages were 40 registers at p = 4
-    int tid = threadIdx.x;
-    __asm__ volatile("" : "+v"(tid));
-    const int rb = tid % NRB;
-    const int pl = tid / NRB;  // line thread: (el, r)
-    const int el = NE == 1 ? 0 : pl / QQ;  // one element: e, and with it D's address, uniform
-    const int r = pl - el * QQ;
-    const int e = tile * NE + el;
-    const bool act = e < M.ne;
-    TC* const W = sW + el * ELEM * NRB + rb;
-    // entry (c, qy, qx, dz) of this element and rhs; the x-line outputs (a, dz, dy, qx)
-    // live at c*Q + qy = a*D + dy
-    auto at = [&](int c, int qy, int qx, int dz) -> TC& {
-      return W[(((c * Q + qy) * Q + qx) * D + dz) * NRB];
-    };
-    // D of this thread's z-line (qy, qx) = r, read again for every chunk of right-hand sides
-    // one plane ahead of its use (it stays in L2): held in registers (12 Q of them) it left
-    // one workgroup of 5 waves per CU at p = 4
-    constexpr int NT = qdata_tile(Q), PL = NT * QQ;  // elements of a qdata tile, values a plane
-    const TD* const qe = static_cast<const TD*>(M.qdata) + size_t(e / NT) * (NC * Q * PL) +
-                         (DIFF ? 2 : 1) * ((e % NT) * QQ);
-    const unsigned rq = (DIFF ? 2 : 1) * r;
-    TC dq[Q][NC];
-    auto load_plane = [&](int qz) {
-      if constexpr (DIFF) {
-        typedef typename Pair<TC, TD>::type pair_t;
+  const int tid = threadIdx.x;
+  const int rb = tid % NRB;
+  const int pl = tid / NRB;  // line thread: (el, r)
+  const int el = NE == 1 ? 0 : pl / QQ;  // one element: e, and with it D's address, uniform
+  const int r = pl - el * QQ;
+  const int e = tile * NE + el;
+  const bool act = e < M.ne;
+  TC* const W = sW + el * ELEM * NRB + rb;
+  // entry (c, qy, qx, dz) of this element and rhs; the x-line outputs (a, dz, dy, qx)
+  // live at c*Q + qy = a*D + dy
+  auto at = [&](int c, int qy, int qx, int dz) -> TC& {
+    return W[(((c * Q + qy) * Q + qx) * D + dz) * NRB];
+  };
+  // D of this thread's z-line (qy, qx) = r, one plane ahead of its use: all of it held in
+  // registers (12 Q of them) left one workgroup of 5 waves per CU at p = 4
+  constexpr int NT = qdata_tile(Q), PL = NT * QQ;  // elements of a qdata tile, values a plane
+  const TD* const qe = static_cast<const TD*>(M.qdata) + size_t(e / NT) * (NC * Q * PL) +
+                       (DIFF ? 2 : 1) * ((e % NT) * QQ);
+  const unsigned rq = (DIFF ? 2 : 1) * r;
+  TC dq[Q][NC];
+  auto load_plane = [&](int qz) {
+    if constexpr (DIFF) {
+      typedef typename Pair<TC, TD>::type pair_t;
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-          const pair_t v = *reinterpret_cast<const pair_t*>(qe + 2 * ((k * Q + qz) * PL) + rq);
-          dq[qz][2 * k] = TC(v.x);
-          dq[qz][2 * k + 1] = TC(v.y);
+      for (int k = 0; k < 3; ++k) {
+        const pair_t v = *reinterpret_cast<const pair_t*>(qe + 2 * ((k * Q + qz) * PL) + rq);
+        dq[qz][2 * k] = TC(v.x);
+        dq[qz][2 * k + 1] = TC(v.y);
+      }
+    } else {
+      dq[qz][0] = TC(qe[qz * PL + rq]);
+    }
+  };
+  // x-line (dz, dy) = r < D*D: the dofs of its D nodes (re-read where used: cached)
+  const bool xline = act && r < DD;
+  const int xz = r / D, xy = r - (r / D) * D;
+  const bool xline_inner = xz > 0 && xz < P && xy > 0 && xy < P;
+  const int32_t* __restrict__ gline = M.gmap + size_t(e) * (DD * D) + r * D;
+  const bool yline = act && r < D * Q;
+  const int yz = r / Q, yx = r - (r / Q) * Q;
+  const int zy = r / Q, zx = r - (r / Q) * Q;
+  const int rr = r0 + rb;
+  // G and B along x: thread (dz, dy)
+  if (xline) {
+    TC u[D];
+#pragma unroll
+    for (int dx = 0; dx < D; ++dx) {
+      const int g = gline[dx];
+      u[dx] = (constrained && g < 0) ? TC(0) : TC(X[size_t(g < 0 ? ~g : g) * nrhs + rr]);
+    }
+#pragma unroll
+    for (int qx = 0; qx < Q; ++qx) {
+      TC b = TC(0), g = TC(0);
+#pragma unroll
+      for (int dx = 0; dx < D; ++dx) {
+        b += bB(qx, dx) * u[dx];
+        if (DIFF) g += bG(qx, dx) * u[dx];
+      }
+      at(xy / Q, xy % Q, qx, xz) = b;
+      if (DIFF) at((D + xy) / Q, (D + xy) % Q, qx, xz) = g;
+    }
+  }
+  __syncthreads();
+  // B along y: thread (dz, qx)
+  if (yline) {
+    TC aB[D], aG[D];
+#pragma unroll
+    for (int dy = 0; dy < D; ++dy) {
+      aB[dy] = at(dy / Q, dy % Q, yx, yz);
+      if (DIFF) aG[dy] = at((D + dy) / Q, (D + dy) % Q, yx, yz);
+    }
+#pragma unroll
+    for (int qy = 0; qy < Q; ++qy) {
+      TC gb = TC(0), bg = TC(0), bb = TC(0);
+#pragma unroll
+      for (int dy = 0; dy < D; ++dy) {
+        bb += bB(qy, dy) * aB[dy];
+        if (DIFF) {
+          gb += bB(qy, dy) * aG[dy];
+          bg += bG(qy, dy) * aB[dy];
+        }
+      }
+      if (DIFF) {
+        at(0, qy, yx, yz) = gb;
+        at(1, qy, yx, yz) = bg;
+        at(2, qy, yx, yz) = bb;
+      } else {
+        at(0, qy, yx, yz) = bb;
+      }
+    }
+  }
+  __syncthreads();
+  // B along z, D, B^t along z: thread (qy, qx), in place
+  if (act) {
+    load_plane(0);
+    TC c0[D], c1[D], c2[D];
+#pragma unroll
+    for (int dz = 0; dz < D; ++dz) {
+      c0[dz] = at(0, zy, zx, dz);
+      if (DIFF) {
+        c1[dz] = at(1, zy, zx, dz);
+        c2[dz] = at(2, zy, zx, dz);
+      }
+    }
+    TC t0[D], t1[D], t2[D];
+#pragma unroll
+    for (int dz = 0; dz < D; ++dz) t0[dz] = t1[dz] = t2[dz] = TC(0);
+#pragma unroll
+    for (int qz = 0; qz < Q; ++qz) {
+      if (qz + 1 < Q) load_plane(qz + 1);
+      __asm__ volatile("" ::: "memory");  // keep the next plane's loads in this iteration
+      if (DIFF) {
+        TC ux = TC(0), uy = TC(0), uz = TC(0);
+#pragma unroll
+        for (int dz = 0; dz < D; ++dz) {
+          ux += bB(qz, dz) * c0[dz];
+          uy += bB(qz, dz) * c1[dz];
+          uz += bG(qz, dz) * c2[dz];
+        }
+        const TC vx = dq[qz][0] * ux + dq[qz][1] * uy + dq[qz][2] * uz;
+        const TC vy = dq[qz][1] * ux + dq[qz][3] * uy + dq[qz][4] * uz;
+        const TC vz = dq[qz][2] * ux + dq[qz][4] * uy + dq[qz][5] * uz;
+#pragma unroll
+        for (int dz = 0; dz < D; ++dz) {
+          t0[dz] += bB(qz, dz) * vx;
+          t1[dz] += bB(qz, dz) * vy;
+          t2[dz] += bG(qz, dz) * vz;
         }
       } else {
-        dq[qz][0] = TC(qe[qz * PL + rq]);
-      }
-    };
-    // x-line (dz, dy) = r < D*D: the dofs of its D nodes (re-read where used: cached)
-    const bool xline = act && r < DD;
-    const int xz = r / D, xy = r - (r / D) * D;
-    const bool xline_inner = xz > 0 && xz < P && xy > 0 && xy < P;
-    const int32_t* __restrict__ gline = M.gmap + size_t(e) * (DD * D) + r * D;
-    const bool yline = act && r < D * Q;
-    const int yz = r / Q, yx = r - (r / Q) * Q;
-    const int zy = r / Q, zx = r - (r / Q) * Q;
-    const int rr = r0 + rb;
-    // G and B along x: thread (dz, dy)
-    if (xline) {
-      TC u[D];
+        TC u = TC(0);
 #pragma unroll
-      for (int dx = 0; dx < D; ++dx) {
-        const int g = gline[dx];
-        u[dx] = (constrained && g < 0) ? TC(0) : TC(X[size_t(g < 0 ? ~g : g) * nrhs + rr]);
-      }
+        for (int dz = 0; dz < D; ++dz) u += bB(qz, dz) * c0[dz];
+        const TC v = dq[qz][0] * u;
 #pragma unroll
-      for (int qx = 0; qx < Q; ++qx) {
-        TC b = TC(0), g = TC(0);
-#pragma unroll
-        for (int dx = 0; dx < D; ++dx) {
-          b += bB(qx, dx) * u[dx];
-          if (DIFF) g += bG(qx, dx) * u[dx];
-        }
-        at(xy / Q, xy % Q, qx, xz) = b;
-        if (DIFF) at((D + xy) / Q, (D + xy) % Q, qx, xz) = g;
+        for (int dz = 0; dz < D; ++dz) t0[dz] += bB(qz, dz) * v;
       }
     }
-    __syncthreads();
-    // B along y: thread (dz, qx)
-    if (yline) {
-      TC aB[D], aG[D];
 #pragma unroll
-      for (int dy = 0; dy < D; ++dy) {
-        aB[dy] = at(dy / Q, dy % Q, yx, yz);
-        if (DIFF) aG[dy] = at((D + dy) / Q, (D + dy) % Q, yx, yz);
+    for (int dz = 0; dz < D; ++dz) {
+      at(0, zy, zx, dz) = t0[dz];
+      if (DIFF) {
+        at(1, zy, zx, dz) = t1[dz];
+        at(2, zy, zx, dz) = t2[dz];
       }
+    }
+  }
+  __syncthreads();
+  // B^t along y: thread (dz, qx)
+  if (yline) {
+    TC v0[Q], v1[Q], v2[Q];
+#pragma unroll
+    for (int qy = 0; qy < Q; ++qy) {
+      v0[qy] = at(0, qy, yx, yz);
+      if (DIFF) {
+        v1[qy] = at(1, qy, yx, yz);
+        v2[qy] = at(2, qy, yx, yz);
+      }
+    }
+#pragma unroll
+    for (int dy = 0; dy < D; ++dy) {
+      TC b = TC(0), g = TC(0);
 #pragma unroll
       for (int qy = 0; qy < Q; ++qy) {
-        TC gb = TC(0), bg = TC(0), bb = TC(0);
-#pragma unroll
-        for (int dy = 0; dy < D; ++dy) {
-          bb += bB(qy, dy) * aB[dy];
-          if (DIFF) {
-            gb += bB(qy, dy) * aG[dy];
-            bg += bG(qy, dy) * aB[dy];
-          }
-        }
         if (DIFF) {
-          at(0, qy, yx, yz) = gb;
-          at(1, qy, yx, yz) = bg;
-          at(2, qy, yx, yz) = bb;
+          g += bB(qy, dy) * v0[qy];
+          b += bG(qy, dy) * v1[qy] + bB(qy, dy) * v2[qy];
         } else {
-          at(0, qy, yx, yz) = bb;
+          b += bB(qy, dy) * v0[qy];
         }
       }
+      at(dy / Q, dy % Q, yx, yz) = b;
+      if (DIFF) at((D + dy) / Q, (D + dy) % Q, yx, yz) = g;
     }
-    __syncthreads();
-    // B along z, D, B^t along z: thread (qy, qx), in place
-    if (act) {
-      load_plane(0);
-      TC c0[D], c1[D], c2[D];
+  }
+  __syncthreads();
+  // B^t along x and G^t: thread (dz, dy)
+  if (xline) {
+    TC wB[Q], wG[Q];
 #pragma unroll
-      for (int dz = 0; dz < D; ++dz) {
-        c0[dz] = at(0, zy, zx, dz);
-        if (DIFF) {
-          c1[dz] = at(1, zy, zx, dz);
-          c2[dz] = at(2, zy, zx, dz);
-        }
-      }
-      TC t0[D], t1[D], t2[D];
-#pragma unroll
-      for (int dz = 0; dz < D; ++dz) t0[dz] = t1[dz] = t2[dz] = TC(0);
-#pragma unroll
-      for (int qz = 0; qz < Q; ++qz) {
-        if (qz + 1 < Q) load_plane(qz + 1);
-        __asm__ volatile("" ::: "memory");  // keep the next plane's loads in this iteration
-        if (DIFF) {
-          TC ux = TC(0), uy = TC(0), uz = TC(0);
-#pragma unroll
-          for (int dz = 0; dz < D; ++dz) {
-            ux += bB(qz, dz) * c0[dz];
-            uy += bB(qz, dz) * c1[dz];
-            uz += bG(qz, dz) * c2[dz];
-          }
-          const TC vx = dq[qz][0] * ux + dq[qz][1] * uy + dq[qz][2] * uz;
-          const TC vy = dq[qz][1] * ux + dq[qz][3] * uy + dq[qz][4] * uz;
-          const TC vz = dq[qz][2] * ux + dq[qz][4] * uy + dq[qz][5] * uz;
-#pragma unroll
-          for (int dz = 0; dz < D; ++dz) {
-            t0[dz] += bB(qz, dz) * vx;
-            t1[dz] += bB(qz, dz) * vy;
-            t2[dz] += bG(qz, dz) * vz;
-          }
-        } else {
-          TC u = TC(0);
-#pragma unroll
-          for (int dz = 0; dz < D; ++dz) u += bB(qz, dz) * c0[dz];
-          const TC v = dq[qz][0] * u;
-#pragma unroll
-          for (int dz = 0; dz < D; ++dz) t0[dz] += bB(qz, dz) * v;
-        }
-      }
-#pragma unroll
-      for (int dz = 0; dz < D; ++dz) {
-        at(0, zy, zx, dz) = t0[dz];
-        if (DIFF) {
-          at(1, zy, zx, dz) = t1[dz];
-          at(2, zy, zx, dz) = t2[dz];
-        }
-      }
+    for (int qx = 0; qx < Q; ++qx) {
+      wB[qx] = at(xy / Q, xy % Q, qx, xz);
+      if (DIFF) wG[qx] = at((D + xy) / Q, (D + xy) % Q, qx, xz);
     }
-    __syncthreads();
-    // B^t along y: thread (dz, qx)
-    if (yline) {
-      TC v0[Q], v1[Q], v2[Q];
 #pragma unroll
-      for (int qy = 0; qy < Q; ++qy) {
-        v0[qy] = at(0, qy, yx, yz);
-        if (DIFF) {
-          v1[qy] = at(1, qy, yx, yz);
-          v2[qy] = at(2, qy, yx, yz);
-        }
-      }
-#pragma unroll
-      for (int dy = 0; dy < D; ++dy) {
-        TC b = TC(0), g = TC(0);
-#pragma unroll
-        for (int qy = 0; qy < Q; ++qy) {
-          if (DIFF) {
-            g += bB(qy, dy) * v0[qy];
-            b += bG(qy, dy) * v1[qy] + bB(qy, dy) * v2[qy];
-          } else {
-            b += bB(qy, dy) * v0[qy];
-          }
-        }
-        at(dy / Q, dy % Q, yx, yz) = b;
-        if (DIFF) at((D + dy) / Q, (D + dy) % Q, yx, yz) = g;
-      }
-    }
-    __syncthreads();
-    // B^t along x and G^t: thread (dz, dy)
-    if (xline) {
-      TC wB[Q], wG[Q];
+    for (int dx = 0; dx < D; ++dx) {
+      TC acc = TC(0);
 #pragma unroll
       for (int qx = 0; qx < Q; ++qx) {
-        wB[qx] = at(xy / Q, xy % Q, qx, xz);
-        if (DIFF) wG[qx] = at((D + xy) / Q, (D + xy) % Q, qx, xz);
+        acc += bB(qx, dx) * wB[qx];
+        if (DIFF) acc += bG(qx, dx) * wG[qx];
       }
-#pragma unroll
-      for (int dx = 0; dx < D; ++dx) {
-        TC acc = TC(0);
-#pragma unroll
-        for (int qx = 0; qx < Q; ++qx) {
-          acc += bB(qx, dx) * wB[qx];
-          if (DIFF) acc += bG(qx, dx) * wG[qx];
-        }
-        const int g = gline[dx];
-        TV* const dst = &Y[size_t(g < 0 ? ~g : g) * nrhs + rr];
-        if (dx > 0 && dx < P && xline_inner)  // an interior node: no other element has it
-          *dst = TV(acc);
-        else if (!(constrained && g < 0))
-          unsafeAtomicAdd(dst, TV(acc));
-      }
+      const int g = gline[dx];
+      TV* const dst = &Y[size_t(g < 0 ? ~g : g) * nrhs + rr];
+      if (dx > 0 && dx < P && xline_inner)  // an interior node: no other element has it
+        *dst = TV(acc);
+      else if (!(constrained && g < 0))
+        unsafeAtomicAdd(dst, TV(acc));
     }
-    // the next chunk overwrites the element regions only after every thread is done
-    __syncthreads();
   }
 }
 
