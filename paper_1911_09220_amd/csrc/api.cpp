@@ -687,15 +687,30 @@ pafem_status pafem_pcg_solve(pafem_op op, const double* diag, const double* b, d
     double* const qi = evec ? nullptr : q;
     launch_cg_init(state, partials, b, opts->zero_guess ? nullptr : q, dg, x, r, d, qi, ess,
                    opts->zero_guess, opts->rel_tol, opts->max_iter + 1, hist, n, st);
+    // Small grids: the applies after the first of a batch form their direction themselves
+    // (apply_takes_direction), alternating between d and a second buffer in the scatter's
+    // workspace, which the atomic scatter does not use; the batch ends in d.
+    const bool direction_built = !evec && apply_takes_direction(s.dev, o.kind, o.qdtype);
+    double* const dbuf[2] = {d, static_cast<double*>(opwork)};
+    CGState host{};
     auto iterations = [&](hipStream_t s2, int count) {
+      const bool fused = direction_built && host.ess == 0.0;
       for (int k = 0; k < count; ++k) {
-        apply_op(o, d, q, opwork, s2, dotp, !evec);
-        launch_cg_update(state, partials, dotp, nap, ess != nullptr, x, r, d, q, dg, n, s2);
-        launch_cg_direction(state, partials, r, dg, d, qi, ess, hist, n, s2);
+        double* const dk = fused ? dbuf[k & 1] : d;
+        const bool last = k + 1 == count;
+        if (fused && k > 0)
+          launch_pa_apply_direction(
+              s.dev, o.qdtype, ess != nullptr, o.qdata,
+              make_direction(state, partials, hist, r, dg, dbuf[(k - 1) & 1], dk, n), q, dotp, s2);
+        else
+          apply_op(o, dk, q, opwork, s2, dotp, !evec);
+        launch_cg_update(state, partials, dotp, nap, ess != nullptr, x, r, dk, q, dg,
+                         fused && !last ? q : nullptr, n, s2);
+        if (!fused || last)
+          launch_cg_direction(state, partials, r, dg, dk, d, qi, ess, hist, n, s2);
       }
     };
     CapturedGraph graph;
-    CGState host{};
     int launched = 0;
     while (true) {
       hip_check(hipMemcpyAsync(&host, state, sizeof(CGState), hipMemcpyDeviceToHost, st),
@@ -831,6 +846,11 @@ pafem_status pafem_ir_solve(pafem_op a_hi, pafem_op a_lo, const double* diag, co
     const uint8_t* ess = (lo.flags & PAFEM_OP_CONSTRAINED) ? hi.space->dev.bmask : nullptr;
     auto st = static_cast<hipStream_t>(stream);
     const int check = std::max(1, opts->check_every);
+    // as in pafem_pcg_solve, here with two products too: the last one outlives its batch
+    const bool direction_built = !(lo.flags & PAFEM_OP_SCATTER_EVEC) &&
+                                 apply_takes_direction(hi.space->dev, lo.kind, lo.qdtype);
+    float* const dbuf[2] = {d32, static_cast<float*>(opwork)};
+    float* const qbuf[2] = {q32, static_cast<float*>(opwork) + n};
     if (dinv) launch_ir_dinv(diag, dinv, n, st);
     hip_check(hipMemsetAsync(x, 0, size_t(n) * 8, st), "zero x");
     // r = b, ||b||
@@ -850,19 +870,31 @@ pafem_status pafem_ir_solve(pafem_op a_hi, pafem_op a_lo, const double* diag, co
       if (restart)
         launch_ir_start(st_lo, partials, r64, s, dinv, d32, q32, ess, opts->inner_rel_tol, n, st);
       // inner: Jacobi-PCG on A_lo d = r / ||r|| with the reduced-precision apply, x += ||r|| d
-      int launched = 0;
+      int launched = 0, seen = 0;
       CGState hl{};
       while (true) {
         hip_check(hipMemcpyAsync(&hl, st_lo, sizeof(CGState), hipMemcpyDeviceToHost, st),
                   "state read");
         hip_check(hipStreamSynchronize(st), "ir sync");
+        if (launched == 0) seen = hl.iter;
         if (hl.done || launched >= opts->max_inner) break;
         const int batch = std::min(check, opts->max_inner - launched);
+        const bool fused = direction_built && hl.ess == 0.0;
+        seen = hl.iter;
         for (int k = 0; k < batch; ++k) {
-          apply_op(lo, d32, q32, opwork, st, dotp, /*y_ready=*/true);
-          launch_ir_update(st_lo, partials, dotp, nap, ess != nullptr, x, s, r64, d32, q32, dinv,
-                           n, st);
-          launch_ir_direction(st_lo, partials, false, r64, dinv, d32, q32, ess, n, st);
+          const int i = fused ? k & 1 : 0;
+          const bool last = k + 1 == batch;
+          if (fused && k > 0)
+            launch_pa_apply_direction(
+                hi.space->dev, lo.qdtype, ess != nullptr, lo.qdata,
+                make_direction(st_lo, partials, nullptr, r64, dinv, dbuf[1 - i], dbuf[i], n),
+                qbuf[i], dotp, st);
+          else
+            apply_op(lo, dbuf[i], qbuf[i], opwork, st, dotp, /*y_ready=*/true);
+          launch_ir_update(st_lo, partials, dotp, nap, ess != nullptr, x, s, r64, dbuf[i], qbuf[i],
+                           dinv, fused && !last ? qbuf[1 - i] : nullptr, n, st);
+          if (!fused || last)
+            launch_ir_direction(st_lo, partials, false, r64, dinv, dbuf[i], d32, q32, ess, n, st);
         }
         launched += batch;
       }
@@ -884,8 +916,13 @@ pafem_status pafem_ir_solve(pafem_op a_hi, pafem_op a_lo, const double* diag, co
       const double s_new = std::sqrt(rr);
       restart = !(opts->keep_direction && hl.done == 1);
       if (!restart) {
-        launch_ir_replace(st_lo, partials, r64, s_new, dinv, d32, q32, opts->inner_rel_tol, n, st);
-        launch_ir_direction(st_lo, partials, true, r64, dinv, d32, q32, ess, n, st);
+        // stopped in iteration hl.iter - seen of its batch: that direction and its product
+        // are in the buffers of that iteration
+        const int i =
+            direction_built && hl.ess == 0.0 && hl.iter > seen ? (hl.iter - seen - 1) & 1 : 0;
+        launch_ir_replace(st_lo, partials, r64, s_new, dinv, dbuf[i], qbuf[i],
+                          opts->inner_rel_tol, n, st);
+        launch_ir_direction(st_lo, partials, true, r64, dinv, dbuf[i], d32, q32, ess, n, st);
       }
       s = s_new;
     }

@@ -19,7 +19,9 @@
 //        into y (pre-set by the init kernel: x on essential dofs when constrained)
 // With DOT each workgroup writes the sum of its elements' energies (B G u) . D (B G u)
 // for the CG step length.
-#include "device.hpp"
+#include <type_traits>
+
+#include "direction.hpp"
 #include "launch.hpp"
 
 namespace pafem {
@@ -158,13 +160,16 @@ constexpr int elems2d() {
   return qdata_tile_2d(Q);
 }
 
-template <int P, int Q, int KIND, bool DOT>
+struct NoDirection {};
+
+template <int P, int Q, int KIND, bool DOT, bool DIR>
 __global__ void __launch_bounds__(k2dThreads)
     pa_apply2d_kernel(const int32_t* __restrict__ tile_off, const int32_t* __restrict__ tile_dofs,
                       const uint16_t* __restrict__ tile_slot, const double* __restrict__ tabB,
                       const double* __restrict__ tabG, const double* __restrict__ qd,
                       const double* __restrict__ x, double* __restrict__ y,
-                      double* __restrict__ dotp, int ne, int constrained) {
+                      double* __restrict__ dotp, int ne, int constrained,
+                      std::conditional_t<DIR, Direction, NoDirection> dir) {
   constexpr int D = P + 1, DD = D * D;
   constexpr int NE = elems2d<Q>();
   static_assert(NE * Q <= k2dThreads, "tile does not fit the workgroup");
@@ -213,6 +218,12 @@ __global__ void __launch_bounds__(k2dThreads)
       for (int c = 0; c < NC; ++c) dq[qy][c] = __builtin_nontemporal_load(qe + (c * Q + qy) * (NE * Q));
   }
 
+  // DIR: the input is the CG direction formed here (x is not read)
+  double beta = 0.0;
+  if constexpr (DIR) {
+    __shared__ double sBeta[2 * k2dThreads / kWave];
+    if (!direction_beta(dir, sBeta, beta)) return;
+  }
   // G: the tile's unique dofs
   for (int s0 = tid; s0 < nu; s0 += 4 * k2dThreads) {
     int gg[4];
@@ -225,7 +236,15 @@ __global__ void __launch_bounds__(k2dThreads)
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int g = gg[k];
-      xv[k] = (s0 + k * k2dThreads < nu && !(constrained && g < 0)) ? x[g < 0 ? ~g : g] : 0.0;
+      if constexpr (DIR) {
+        xv[k] = 0.0;
+        if (s0 + k * k2dThreads < nu) {
+          const double v = direction_entry(dir, beta, g < 0 ? ~g : g);
+          if (!(constrained && g < 0)) xv[k] = v;
+        }
+      } else {
+        xv[k] = (s0 + k * k2dThreads < nu && !(constrained && g < 0)) ? x[g < 0 ? ~g : g] : 0.0;
+      }
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k)
@@ -343,22 +362,25 @@ __global__ void __launch_bounds__(k2dThreads)
   }
 }
 
-template <int P, int KIND, bool DOT>
+template <int P, int KIND, bool DOT, bool DIR = false, typename DArg = NoDirection>
 void launch2d(const DevSpace& sp, bool constrained, const double* qd, const double* x, double* y,
-              double* dotp, hipStream_t st) {
+              double* dotp, hipStream_t st, DArg dir = {}) {
   constexpr int Q = P + 2;
   constexpr int NE = elems2d<Q>();
   const int nblk = int((sp.ne + NE - 1) / NE);
   const Tab2 tv = tab2(sp, Q);
-  hipLaunchKernelGGL((pa_apply2d_kernel<P, Q, KIND, DOT>), dim3(nblk), dim3(k2dThreads), 0, st,
+  hipLaunchKernelGGL((pa_apply2d_kernel<P, Q, KIND, DOT, DIR>), dim3(nblk), dim3(k2dThreads), 0, st,
                      sp.tile_off, sp.tile_dofs, sp.tile_slot, tv.B, tv.G, qd, x, y, dotp,
-                     int(sp.ne), int(constrained));
+                     int(sp.ne), int(constrained), dir);
 }
 
 template <int P>
 void launch2d_order(const DevSpace& sp, int kind, bool constrained, const double* qd,
-                    const double* x, double* y, double* dotp, hipStream_t st) {
-  if (kind == PAFEM_DIFFUSION) {
+                    const double* x, double* y, double* dotp, hipStream_t st,
+                    const Direction* dir) {
+  if (dir) {
+    launch2d<P, PAFEM_DIFFUSION, true, true, Direction>(sp, constrained, qd, x, y, dotp, st, *dir);
+  } else if (kind == PAFEM_DIFFUSION) {
     if (dotp)
       launch2d<P, PAFEM_DIFFUSION, true>(sp, constrained, qd, x, y, dotp, st);
     else
@@ -402,16 +424,17 @@ int pa_apply2d_blocks(const DevSpace& sp) {
 }
 
 bool launch_pa_apply_2d(const DevSpace& sp, int kind, bool constrained, const double* qd,
-                        const double* x, double* y, hipStream_t st, double* dotp) {
+                        const double* x, double* y, hipStream_t st, double* dotp,
+                        const Direction* dir) {
   switch (sp.p) {
-    case 1: launch2d_order<1>(sp, kind, constrained, qd, x, y, dotp, st); break;
-    case 2: launch2d_order<2>(sp, kind, constrained, qd, x, y, dotp, st); break;
-    case 3: launch2d_order<3>(sp, kind, constrained, qd, x, y, dotp, st); break;
-    case 4: launch2d_order<4>(sp, kind, constrained, qd, x, y, dotp, st); break;
-    case 5: launch2d_order<5>(sp, kind, constrained, qd, x, y, dotp, st); break;
-    case 6: launch2d_order<6>(sp, kind, constrained, qd, x, y, dotp, st); break;
-    case 7: launch2d_order<7>(sp, kind, constrained, qd, x, y, dotp, st); break;
-    case 8: launch2d_order<8>(sp, kind, constrained, qd, x, y, dotp, st); break;
+    case 1: launch2d_order<1>(sp, kind, constrained, qd, x, y, dotp, st, dir); break;
+    case 2: launch2d_order<2>(sp, kind, constrained, qd, x, y, dotp, st, dir); break;
+    case 3: launch2d_order<3>(sp, kind, constrained, qd, x, y, dotp, st, dir); break;
+    case 4: launch2d_order<4>(sp, kind, constrained, qd, x, y, dotp, st, dir); break;
+    case 5: launch2d_order<5>(sp, kind, constrained, qd, x, y, dotp, st, dir); break;
+    case 6: launch2d_order<6>(sp, kind, constrained, qd, x, y, dotp, st, dir); break;
+    case 7: launch2d_order<7>(sp, kind, constrained, qd, x, y, dotp, st, dir); break;
+    case 8: launch2d_order<8>(sp, kind, constrained, qd, x, y, dotp, st, dir); break;
     default: return false;
   }
   return true;

@@ -33,7 +33,9 @@
 // only entries that the same thread has just read, so a region of 3*Q*Q lines of
 // D values (1*Q*Q for mass) holds them all.
 // Blocks are remapped so each XCD processes one contiguous range of elements.
-#include "device.hpp"
+#include <type_traits>
+
+#include "direction.hpp"
 #include "launch.hpp"
 
 namespace pafem {
@@ -46,7 +48,10 @@ constexpr int elems_per_block() {
   return qdata_tile(Q);
 }
 
-template <int P, int Q, int KIND, bool EVEC, bool DOT, typename TV, typename TD, typename TC>
+struct NoDirection {};
+
+template <int P, int Q, int KIND, bool EVEC, bool DOT, bool DIR, typename TV, typename TD,
+          typename TC>
 __global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, KIND != PAFEM_DIFFUSION ? 1 : sizeof(TC) == 4 ? (P == 6 ? 5 : 1) : (P == 4 || P == 5) ? 4 : P == 2 ? 5 : P >= 6 ? 3 : 1)
     pa_apply_kernel(const int32_t* __restrict__ tile_off, const int32_t* __restrict__ tile_dofs,
                     const uint16_t* __restrict__ tile_slot, const TC* __restrict__ tabB,
@@ -54,7 +59,8 @@ __global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, KIND != PAFEM_DI
                     const TV* __restrict__ x, TV* __restrict__ y, double* __restrict__ dotp,
                     const double* __restrict__ gnodes, const TC* __restrict__ tabBg,
                     const TC* __restrict__ tabGg, int ne, int constrained, int64_t ystride,
-                    const int32_t* __restrict__ tile_priv) {
+                    const int32_t* __restrict__ tile_priv,
+                    std::conditional_t<DIR, Direction, NoDirection> dir) {
   constexpr int D = P + 1, DD = D * D, QQ = Q * Q, QQQ = Q * Q * Q, DDD = D * D * D;
   constexpr int NE = elems_per_block<Q>();
   // GEOM: diffusion storing alpha kappa per point; J recomputed from the 8 corners
@@ -205,6 +211,12 @@ __global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, KIND != PAFEM_DI
     }
   };
   if (!DIVV) load_dq(GRADC ? 3 * GC : 0);
+  // DIR: the input is the CG direction formed here (x is not read)
+  double beta = 0.0;
+  if constexpr (DIR) {
+    __shared__ double sBeta[2 * ((elems_per_block<Q>() * Q * Q + kWave - 1) / kWave)];
+    if (!direction_beta(dir, sBeta, beta)) return;
+  }
   TC sdiv[DIVV ? Q : 1];  // DIVV: the divergence at this thread's points, summed over components
 #pragma unroll
   for (int qz = 0; qz < (DIVV ? Q : 1); ++qz) sdiv[qz] = TC(0);
@@ -230,7 +242,19 @@ __global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, KIND != PAFEM_DI
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int g = gg[k];
-      xv[k] = (s0 + k * NE * QQ < nu && !(constrained && g < 0)) ? TC(xv_in[g < 0 ? ~g : g]) : TC(0);
+      if constexpr (DIR) {
+        xv[k] = TC(0);
+        if (s0 + k * NE * QQ < nu) {
+          TC v;
+          if constexpr (sizeof(TV) == 8)
+            v = direction_entry(dir, beta, g < 0 ? ~g : g);
+          else
+            v = direction_entry_f32(dir, beta, g < 0 ? ~g : g);
+          if (!(constrained && g < 0)) xv[k] = v;
+        }
+      } else {
+        xv[k] = (s0 + k * NE * QQ < nu && !(constrained && g < 0)) ? TC(xv_in[g < 0 ? ~g : g]) : TC(0);
+      }
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k)
@@ -631,9 +655,10 @@ const float* table_block<float>(const DevSpace& sp, int q1d) {
   return sp.tables32 + table_offset_doubles(q1d, sp.p + 1, sp.ng);
 }
 
-template <int P, int KIND, bool EVEC, bool DOT, typename TV, typename TD, typename TC>
+template <int P, int KIND, bool EVEC, bool DOT, typename TV, typename TD, typename TC,
+          bool DIR = false, typename DArg = NoDirection>
 void launch_one(const DevSpace& sp, bool constrained, const void* qd, const void* x, void* out,
-                double* dotp, hipStream_t st) {
+                double* dotp, hipStream_t st, DArg dir = {}) {
   constexpr int Q = P + 2;
   constexpr int NE = elems_per_block<Q>();
   const int nblk = int((sp.ne + NE - 1) / NE);
@@ -642,11 +667,11 @@ void launch_one(const DevSpace& sp, bool constrained, const void* qd, const void
   // geometry tables (Bg, Gg of the ng-node geometry basis) follow B and G
   const TC* tabBg = tabG + Q * (P + 1);
   const TC* tabGg = tabBg + Q * sp.ng;
-  hipLaunchKernelGGL((pa_apply_kernel<P, Q, KIND, EVEC, DOT, TV, TD, TC>), dim3(nblk),
+  hipLaunchKernelGGL((pa_apply_kernel<P, Q, KIND, EVEC, DOT, DIR, TV, TD, TC>), dim3(nblk),
                      dim3(NE * Q * Q), 0, st, sp.tile_off, sp.tile_dofs, sp.tile_slot, tabB, tabG,
                      static_cast<const TD*>(qd), static_cast<const TV*>(x),
                      static_cast<TV*>(out), dotp, sp.gnodes, tabBg, tabGg, int(sp.ne),
-                     int(constrained), int64_t(sp.ndofs), sp.tile_priv);
+                     int(constrained), int64_t(sp.ndofs), sp.tile_priv, dir);
 }
 
 template <int P, int KIND, typename TV, typename TD, typename TC>
@@ -758,7 +783,62 @@ bool launch_order(const DevSpace& sp, int kind, int qdtype, int vdtype, bool con
   return false;
 }
 
+template <int P>
+void launch_direction_order(const DevSpace& sp, int qdtype, bool constrained, const void* qd,
+                            const Direction& dir, void* out, double* dotp, hipStream_t st) {
+  if (qdtype == PAFEM_F64)
+    launch_one<P, PAFEM_DIFFUSION, false, true, double, double, double, true, Direction>(
+        sp, constrained, qd, nullptr, out, dotp, st, dir);
+  else
+    launch_one<P, PAFEM_DIFFUSION, false, true, float, float, float, true, Direction>(
+        sp, constrained, qd, nullptr, out, dotp, st, dir);
+}
+
 }  // namespace
+
+// The fused step saves a launch (about 4 us of launch gap and latencies) and costs gathers of
+// three vectors in place of one, for every tile that holds the dof.  It wins while the grid is
+// about one round of the chip, with a line that falls with the entries of a tile.  Iteration of
+// Jacobi-PCG in us, separate -> fused: 3D p = 1, 19 tiles 16.3 -> 13.2, 784: 21.0 -> 17.3,
+// 2286: 30.3 -> 30.1, 6272: 55.5 -> 63.1; p = 3, 275: 21.0 -> 18.4, 927: 30.0 -> 28.0, 1383:
+// 37.5 -> 39.2; p = 6, 54: 25.3 -> 23.6, 432: 33.2 -> 32.4 (FP32 refinement 34.9 -> 33.7);
+// p = 8, 108: 31.4 -> 30.4, 365: 37.8 -> 38.3 (not built); 2D p = 1, 265 tiles: 17.8 -> 13.5,
+// 2942: 28.3 -> 28.3; p = 4, 239: 19.5 -> 17.5, 1934: 51.2 -> 49.8.
+bool apply_takes_direction(const DevSpace& sp, int kind, int qdtype) {
+  if (kind != PAFEM_DIFFUSION || sp.family != kFamilyH1) return false;
+  if (sp.dim == 2) return qdtype == PAFEM_F64 && pa_apply_blocks(sp) <= 2048;
+  return (qdtype == PAFEM_F64 || qdtype == PAFEM_F32) && sp.p <= 7 &&
+         pa_apply_blocks(sp) * (sp.p + 1) <= 4096;
+}
+
+void launch_pa_apply_direction(const DevSpace& sp, int qdtype, bool constrained, const void* qd,
+                               const Direction& dir, void* out, double* dotp, hipStream_t st) {
+  bool built = true;
+  if (sp.dim == 2) {
+    built = launch_pa_apply_2d(sp, PAFEM_DIFFUSION, constrained, static_cast<const double*>(qd),
+                               nullptr, static_cast<double*>(out), st, dotp, &dir);
+  } else {
+    switch (sp.p) {
+#define PAFEM_ORDER_CASE(P_)                                                             \
+  case P_:                                                                               \
+    launch_direction_order<P_>(sp, qdtype, constrained, qd, dir, out, dotp, st);         \
+    break;
+      PAFEM_ORDER_CASE(1)
+      PAFEM_ORDER_CASE(2)
+      PAFEM_ORDER_CASE(3)
+      PAFEM_ORDER_CASE(4)
+      PAFEM_ORDER_CASE(5)
+      PAFEM_ORDER_CASE(6)
+      PAFEM_ORDER_CASE(7)
+#undef PAFEM_ORDER_CASE
+      default: built = false;
+    }
+  }
+  if (!built) throw Error(PAFEM_EUNSUPPORTED, "apply kernel not built for this order");
+  const hipError_t err = hipGetLastError();
+  if (err != hipSuccess)
+    throw Error(PAFEM_EHIP, std::string("apply launch: ") + hipGetErrorString(err));
+}
 
 int pa_apply_blocks(const DevSpace& sp) {
   if (sp.dim == 2) return pa_apply2d_blocks(sp);

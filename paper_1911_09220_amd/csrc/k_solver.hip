@@ -17,9 +17,8 @@
 #include <algorithm>
 #include <cmath>
 
-#include "device.hpp"
+#include "direction.hpp"
 #include "internal.hpp"
-#include "solver.hpp"
 
 namespace pafem {
 
@@ -45,10 +44,6 @@ __device__ __forceinline__ double strided_share(const double* a, int n, int stri
   return v;
 }
 
-__device__ __forceinline__ void finish_done(CGState* st, int done) {
-  __hip_atomic_store(&st->done, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // ---- one-workgroup kernels that turn partials into state --------------------
 // (a solve's start and end; inside an iteration every workgroup of the next vector
 // kernel sums the partials itself)
@@ -62,7 +57,8 @@ __global__ void __launch_bounds__(kCGThreads)
   double bb = strided_share(partials + 3 * kCGBlocks, nb, 1);
   block_sum2(rr, bb, scratch);
   double rz = flexible ? 0.0 : strided_share(partials, nb, 1);
-  rz = block_sum(rz, scratch);
+  double ess = flexible ? 0.0 : strided_share(partials + 2 * kCGBlocks, nb, 1);
+  block_sum2(rz, ess, scratch);
   if (threadIdx.x == 0) {
     // reference of the relative stop: ||b||^2, or ||r_0||^2 when b = 0 (the answer is
     // then x = 0 and the iteration reduces the initial residual; both 0: done)
@@ -72,6 +68,7 @@ __global__ void __launch_bounds__(kCGThreads)
     st->tol2 = rel_tol * rel_tol * ref;
     if (!flexible) {
       st->rz = rz;
+      st->ess = ess;
       st->alpha = st->beta = 0.0;
       st->res2 = 0.0;
     }
@@ -109,8 +106,10 @@ __global__ void __launch_bounds__(kCGThreads)
   __shared__ double scratch[2 * kCGThreads / kWave];
   double rz = strided_share(partials, nb, 1), rr = strided_share(partials + kCGBlocks, nb, 1);
   block_sum2(rz, rr, scratch);
+  const double ess = block_sum(strided_share(partials + 2 * kCGBlocks, nb, 1), scratch);
   if (threadIdx.x == 0) {
     st->rz = rz;
+    st->ess = ess;
     st->rr = rr;
     st->bb = rr;
     st->tol2 = inner_rel_tol * inner_rel_tol * rr;
@@ -188,20 +187,6 @@ __device__ __forceinline__ void put_partials2(double a, double b, double* p0, do
   }
 }
 
-// State after an update: convergence on rr, history, iteration count.  Same decision
-// in every workgroup, written by the first; returns true when the iteration stops.
-__device__ __forceinline__ bool close_update(CGState* st, double rr, bool broken, double* hist) {
-  const int done = (!isfinite(rr) || broken) ? 2 : rr <= st->tol2 ? 1 : 0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    st->rr = rr;
-    const int it = st->iter + 1;
-    st->iter = it;
-    if (hist && it < st->max_hist) hist[it] = sqrt(rr / st->bb);
-    if (done) finish_done(st, done);
-  }
-  return done != 0;
-}
-
 // r = b - q (q may be null: r = b), d = z = r / diag, x = 0 if zero_guess; partials
 // rz, rr, bb and d_b^2 (p2); qi (may be null, may be q): the first apply's init of d
 __global__ void __launch_bounds__(kCGThreads)
@@ -246,12 +231,13 @@ __device__ __forceinline__ int64_t entry_step() {
   return int64_t(gridDim.x) * kCGThreads * kAhead;
 }
 
-// x += alpha d; r -= alpha q; partials of rz and rr
+// x += alpha d; r -= alpha q; partials of rz and rr; q0 (null: none; may be q) = 0, the start
+// of an apply that forms the next direction itself
 __global__ void __launch_bounds__(kCGThreads)
     cg_update_kernel(CGState* st, EnergyParts ep, double* partials, int has_ess,
                      double* __restrict__ x, double* __restrict__ r,
-                     const double* __restrict__ d, const double* __restrict__ q,
-                     const double* __restrict__ diag, int64_t n) {
+                     const double* __restrict__ d, const double* q,
+                     const double* __restrict__ diag, double* q0, int64_t n) {
   __shared__ double scratch[2 * kCGThreads / kWave];
   const int stopped = st->done;
   const double rz0 = st->rz;
@@ -276,6 +262,7 @@ __global__ void __launch_bounds__(kCGThreads)
     if (base != first_entry()) load(base);
     AHEAD_LOOP(u, i, base, n) {
       x[i] = xv[u] + alpha * dv[u];
+      if (q0) q0[i] = 0.0;
       const double ri = rv[u] - alpha * qv[u];
       r[i] = ri;
       const double zi = diag ? ri / gv[u] : ri;
@@ -291,7 +278,7 @@ __global__ void __launch_bounds__(kCGThreads)
 // operator (bmask non-null), 0 elsewhere
 __global__ void __launch_bounds__(kCGThreads)
     cg_direction_kernel(CGState* st, double* partials, const double* __restrict__ r,
-                        const double* __restrict__ diag, double* __restrict__ d,
+                        const double* __restrict__ diag, const double* d, double* dnew,
                         double* __restrict__ q, const uint8_t* __restrict__ bmask, double* hist,
                         int64_t n) {
   __shared__ double scratch[2 * kCGThreads / kWave];
@@ -327,7 +314,7 @@ __global__ void __launch_bounds__(kCGThreads)
     AHEAD_LOOP(u, i, base, n) {
       const double zi = diag ? rv[u] / gv[u] : rv[u];
       const double di = zi + beta * dv[u];
-      d[i] = di;
+      dnew[i] = di;
       if (q) q[i] = ev[u] ? di : 0.0;
       if (ev[u]) ess += di * di;
     }
@@ -505,7 +492,7 @@ __global__ void __launch_bounds__(kCGThreads)
     ir_update_kernel(CGState* st, EnergyParts ep, double* partials, int has_ess,
                      double* __restrict__ x, double s, double* __restrict__ r,
                      const float* __restrict__ d, const float* __restrict__ q,
-                     const float* __restrict__ dinv, int64_t n) {
+                     const float* __restrict__ dinv, float* __restrict__ q0, int64_t n) {
   __shared__ double scratch[2 * kCGThreads / kWave];
   const int stopped = st->done;
   const double rz0 = st->rz;
@@ -532,6 +519,7 @@ __global__ void __launch_bounds__(kCGThreads)
     if (base != first_entry()) load(base);
     AHEAD_LOOP(u, i, base, n) {
       x[i] = xv[u] + xstep * double(dv[u]);
+      if (q0) q0[i] = 0.0f;
       const double ri = rv[u] - alpha * double(qv[u]);
       r[i] = ri;
       const double zi = ri * double(gv[u]);
@@ -547,7 +535,7 @@ __global__ void __launch_bounds__(kCGThreads)
 // residual replacement left in the state.
 __global__ void __launch_bounds__(kCGThreads)
     ir_direction_kernel(CGState* st, double* partials, int replaced, const double* __restrict__ r,
-                        const float* __restrict__ dinv, float* __restrict__ d,
+                        const float* __restrict__ dinv, const float* d, float* dnew,
                         float* __restrict__ q, const uint8_t* __restrict__ ess, int64_t n) {
   __shared__ double scratch[2 * kCGThreads / kWave];
   const int stopped = st->done;
@@ -580,7 +568,7 @@ __global__ void __launch_bounds__(kCGThreads)
     if (base != first_entry()) load(base);
     AHEAD_LOOP(u, i, base, n) {
       const float di = float(rv[u] * double(gv[u]) + beta * double(dv[u]));
-      d[i] = di;
+      dnew[i] = di;
       q[i] = ev[u] ? di : 0.0f;
       if (ev[u]) de += double(di) * double(di);
     }
@@ -659,6 +647,15 @@ int cg_blocks(int64_t n) {
   return int(std::min<int64_t>(kCGBlocks, std::max<int64_t>(1, (n + kCGThreads - 1) / kCGThreads)));
 }
 
+}  // namespace
+
+Direction make_direction(CGState* st, const double* partials, double* hist, const double* r,
+                         const void* scale, const void* dold, void* dnew, int64_t n) {
+  return {st, partials, hist, r, scale, dold, dnew, cg_blocks(n)};
+}
+
+namespace {
+
 #define CG_LAUNCH(kernel, n, s, ...)                                                          \
   hipLaunchKernelGGL(kernel, dim3(cg_blocks(n)), dim3(kCGThreads), 0, s, __VA_ARGS__);        \
   check_launch(#kernel)
@@ -685,15 +682,15 @@ void launch_cg_init(CGState* st, double* partials, const double* b, const double
 
 void launch_cg_update(CGState* st, double* partials, double* epart, int nepart, bool has_ess,
                       double* x, double* r, const double* d, const double* q, const double* diag,
-                      int64_t n, hipStream_t s) {
+                      double* q0, int64_t n, hipStream_t s) {
   const EnergyParts ep = energy_parts(epart, nepart, s);
-  CG_LAUNCH(cg_update_kernel, n, s, st, ep, partials, int(has_ess), x, r, d, q, diag, n);
+  CG_LAUNCH(cg_update_kernel, n, s, st, ep, partials, int(has_ess), x, r, d, q, diag, q0, n);
 }
 
 void launch_cg_direction(CGState* st, double* partials, const double* r, const double* diag,
-                         double* d, double* q, const uint8_t* bmask, double* hist, int64_t n,
-                         hipStream_t s) {
-  CG_LAUNCH(cg_direction_kernel, n, s, st, partials, r, diag, d, q, bmask, hist, n);
+                         const double* d, double* dnew, double* q, const uint8_t* bmask,
+                         double* hist, int64_t n, hipStream_t s) {
+  CG_LAUNCH(cg_direction_kernel, n, s, st, partials, r, diag, d, dnew, q, bmask, hist, n);
 }
 
 void launch_fcg_init(CGState* st, double* partials, const double* b, const double* q, double* x,
@@ -737,15 +734,17 @@ void launch_ir_start(CGState* st, double* partials, double* r, double s, const f
 
 void launch_ir_update(CGState* st, double* partials, double* epart, int nepart, bool has_ess,
                       double* x, double s, double* r, const float* d, const float* q,
-                      const float* dinv, int64_t n, hipStream_t stream) {
+                      const float* dinv, float* q0, int64_t n, hipStream_t stream) {
   const EnergyParts ep = energy_parts(epart, nepart, stream);
-  CG_LAUNCH(ir_update_kernel, n, stream, st, ep, partials, int(has_ess), x, s, r, d, q, dinv, n);
+  CG_LAUNCH(ir_update_kernel, n, stream, st, ep, partials, int(has_ess), x, s, r, d, q, dinv, q0,
+            n);
 }
 
 void launch_ir_direction(CGState* st, double* partials, bool replaced, const double* r,
-                         const float* dinv, float* d, float* q, const uint8_t* ess, int64_t n,
-                         hipStream_t stream) {
-  CG_LAUNCH(ir_direction_kernel, n, stream, st, partials, int(replaced), r, dinv, d, q, ess, n);
+                         const float* dinv, const float* d, float* dnew, float* q,
+                         const uint8_t* ess, int64_t n, hipStream_t stream) {
+  CG_LAUNCH(ir_direction_kernel, n, stream, st, partials, int(replaced), r, dinv, d, dnew, q, ess,
+            n);
 }
 
 void launch_ir_replace(CGState* st, double* partials, double* r, double s_new, const float* dinv,

@@ -50,6 +50,13 @@ bool launch_pa_apply(const DevSpace& sp, int kind, int q1d, int qdtype, bool con
                      bool evec, const void* qd, const void* x, void* out, int vdtype,
                      hipStream_t st, double* dotp = nullptr);
 int pa_apply_blocks(const DevSpace& sp);
+// Diffusion on the CG direction that the kernel forms itself (solver.hpp), atomic scatter
+// into `out` = 0, element energies to dotp.  The rule (where it is built and pays) stands
+// with apply_takes_direction.
+struct Direction;
+bool apply_takes_direction(const DevSpace& sp, int kind, int qdtype);
+void launch_pa_apply_direction(const DevSpace& sp, int qdtype, bool constrained, const void* qd,
+                               const Direction& dir, void* out, double* dotp, hipStream_t st);
 // DG convection (k_dg.hip): the face values w (beta . N) of every interior face, then of
 // every boundary face, Q^2 per face (beta = scale * beta3[0..2], device)
 void launch_dg_face_qdata(const DevSpace& sp, int q1d, const double* beta3, double scale,
@@ -72,6 +79,7 @@ void launch_diagonal_evec_2d(const DevSpace& sp, int kind, int q1d, const double
 int pa_apply2d_blocks(const DevSpace& sp);
 // FP64, atomic scatter only
 bool launch_pa_apply_2d(const DevSpace& sp, int kind, bool constrained, const double* qd,
-                        const double* x, double* y, hipStream_t st, double* dotp);
+                        const double* x, double* y, hipStream_t st, double* dotp,
+                        const Direction* dir = nullptr);
 
 }  // namespace pafem

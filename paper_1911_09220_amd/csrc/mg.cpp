@@ -210,12 +210,25 @@ void coarse_pcg(const PMG& g, const double* b, double* x, VBufs& B, hipStream_t 
   double* const yi = evec ? nullptr : v.y;  // the apply's y-init, written with the direction
   launch_cg_init(B.state, B.partials, b, nullptr, diag, x, v.r, v.d, yi, ess, 1, 0.0, iters + 1,
                  B.hist, n, st);
+  // Below another level b is a restriction, 0 on the essential dofs: the applies may form
+  // their direction (second buffer: the scatter's workspace).
+  const bool fused =
+      l > 0 && !evec && apply_takes_direction(op.space->dev, op.kind, op.qdtype);
+  double* const dbuf[2] = {v.d, static_cast<double*>(B.opwork)};
   for (int k = 0; k < iters; ++k) {
-    apply_op(op, v.d, v.y, B.opwork, st, B.dotp, !evec);
-    launch_cg_update(B.state, B.partials, B.dotp, nap, ess != nullptr, x, v.r, v.d, v.y, diag, n,
-                     st);
-    if (k + 1 < iters)  // the last direction is not used
-      launch_cg_direction(B.state, B.partials, v.r, diag, v.d, yi, ess, B.hist, n, st);
+    double* const dk = fused ? dbuf[k & 1] : v.d;
+    const bool last = k + 1 == iters;  // the last direction is not used
+    if (fused && k > 0)
+      launch_pa_apply_direction(
+          op.space->dev, op.qdtype, ess != nullptr, op.qdata,
+          make_direction(B.state, B.partials, B.hist, v.r, diag, dbuf[(k - 1) & 1], dk, n), v.y,
+          B.dotp, st);
+    else
+      apply_op(op, dk, v.y, B.opwork, st, B.dotp, !evec);
+    launch_cg_update(B.state, B.partials, B.dotp, nap, ess != nullptr, x, v.r, dk, v.y, diag,
+                     fused && !last ? v.y : nullptr, n, st);
+    if (!fused && !last)
+      launch_cg_direction(B.state, B.partials, v.r, diag, v.d, v.d, yi, ess, B.hist, n, st);
   }
 }
 

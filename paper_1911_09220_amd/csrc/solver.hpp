@@ -17,6 +17,7 @@ struct CGState {
   double tol2;   // rel_tol^2 * b . b
   double res2;   // ||b - A x||^2 computed at exit
   double rz_old; // rz at the last update (the denominator of beta)
+  double ess;    // sum of d_b^2 over the essential rows at the start
   int32_t iter;  // completed iterations
   int32_t done;  // 0 running, 1 converged, 2 breakdown, 3 preconditioner not positive
   int32_t max_hist;
@@ -41,6 +42,25 @@ struct EnergyParts {
 };
 constexpr int kFoldAbove = 32768;
 
+// The direction step of an iteration as part of the apply that follows it (FP64 and FP32
+// diffusion): the kernel sums rz and rr of the last update (partials, nb of each), decides
+// convergence, and forms d = z + beta d_old where it gathers its input, stored to dnew.
+// scale: the FP64 diagonal (z = r / diag) or the FP32 inverse diagonal (z = r dinv); null:
+// z = r.  Only where d is 0 on the essential rows: they are 0 in every later iteration then,
+// and need neither y's start nor their part of d . q.
+struct Direction {
+  CGState* st;
+  const double* partials;
+  double* hist;
+  const double* r;
+  const void* scale;
+  const void* dold;
+  void* dnew;
+  int nb;
+};
+Direction make_direction(CGState* st, const double* partials, double* hist, const double* r,
+                         const void* scale, const void* dold, void* dnew, int64_t n);
+
 // Dot products always accumulate in double.  Every apply between two kernels below
 // passes its element energies as epart (nepart of them, overwritten).  q / qi arguments
 // receive the next apply's init (d on the essential dofs given by bmask, 0 elsewhere;
@@ -54,14 +74,14 @@ void launch_cg_init(CGState* st, double* partials, const double* b, const double
                     double* hist, int64_t n, hipStream_t s);
 // alpha = rz / (d . q), d . q from the element energies plus d_b^2 over the essential
 // rows (has_ess: a constrained operator); breakdown (done = 2) if d . q <= 0 or alpha
-// is not finite; x += alpha d; r -= alpha q
+// is not finite; x += alpha d; r -= alpha q; q0 (null: none; may be q) = 0
 void launch_cg_update(CGState* st, double* partials, double* epart, int nepart, bool has_ess,
                       double* x, double* r, const double* d, const double* q, const double* diag,
-                      int64_t n, hipStream_t s);
-// rz, rr, beta, iter, hist, convergence; d = r / diag + beta d
+                      double* q0, int64_t n, hipStream_t s);
+// rz, rr, beta, iter, hist, convergence; dnew = r / diag + beta d (dnew may be d)
 void launch_cg_direction(CGState* st, double* partials, const double* r, const double* diag,
-                         double* d, double* q, const uint8_t* bmask, double* hist, int64_t n,
-                         hipStream_t s);
+                         const double* d, double* dnew, double* q, const uint8_t* bmask,
+                         double* hist, int64_t n, hipStream_t s);
 // Flexible CG (done = 3: the preconditioner returned r.z <= 0).  max_hist < 0: a restart
 // inside a solve, which keeps the iteration count
 void launch_fcg_init(CGState* st, double* partials, const double* b, const double* q, double* x,
@@ -93,15 +113,15 @@ void launch_residual(CGState* st, double* partials, const double* b, const doubl
 void launch_ir_start(CGState* st, double* partials, double* r, double s, const float* dinv,
                      float* d, float* q, const uint8_t* ess, double inner_rel_tol, int64_t n,
                      hipStream_t stream);
-// alpha; x += (s alpha) d; r -= alpha q
+// alpha; x += (s alpha) d; r -= alpha q; q0 (null: none; not q) = 0
 void launch_ir_update(CGState* st, double* partials, double* epart, int nepart, bool has_ess,
                       double* x, double s, double* r, const float* d, const float* q,
-                      const float* dinv, int64_t n, hipStream_t stream);
+                      const float* dinv, float* q0, int64_t n, hipStream_t stream);
 // rz, rr, beta, iter, convergence (replaced: beta as launch_ir_replace left it, nothing
-// else changes); d = z + beta d; q = apply init of d
+// else changes); dnew = z + beta d (dnew may be d); q = apply init of dnew
 void launch_ir_direction(CGState* st, double* partials, bool replaced, const double* r,
-                         const float* dinv, float* d, float* q, const uint8_t* ess, int64_t n,
-                         hipStream_t stream);
+                         const float* dinv, const float* d, float* dnew, float* q,
+                         const uint8_t* ess, int64_t n, hipStream_t stream);
 // Reliable update after a residual replacement: r (the FP64 residual) *= 1/s_new,
 // beta = -(z.q)/(d.q) so that launch_ir_direction continues with a direction
 // conjugate to the kept one (done = 2 on breakdown)
