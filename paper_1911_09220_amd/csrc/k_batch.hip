@@ -7,18 +7,20 @@
 // right-hand sides at once: the tile of a workgroup is NE elements x Q*Q lines x
 // NRB right-hand sides with the rhs index fastest (coalesced X loads and Y
 // atomics, broadcast D loads, conflict-free LDS).  Table entries are the same for
-// every lane and come from scalar loads; the quadrature data D of a z-line is
-// loaded one plane ahead of its use.  One workgroup per tile and chunk of NRB
+// every lane and come from scalar loads; the quadrature data D goes through LDS or
+// is loaded one plane ahead of its use.  One workgroup per tile and chunk of NRB
 // right-hand sides; the chunks of a tile follow each other on one die, whose L2 keeps D and
 // the dof map.  All meshes of one order share one grouped launch: a workgroup finds its
 // mesh from a prefix table of workgroup counts.
 //
 // Bound by latency at the waves that the registers and LDS leave, and by the atomics (an
-// interior node's sum is stored, no other element has it; the others are added).  16
+// interior node's sum is stored, no other element has it; the others are added).  Loads
+// return in order, so the dof ids are loaded before D: behind D's loads they, and with them
+// X, waited for D (p = 4 241 -> 230 us, p = 2 278 -> 259).  16
 // right-hand sides in FP64, best tile, with D and every stage's addresses held in
 // registers across a loop over the chunks (180 at p = 4: one workgroup of 5 waves per CU) ->
-// now: p = 1 (64^3 elements) 557 -> 491 us, p = 2 (40^3) 368 -> 343, p = 3 (24^3) 263 -> 186,
-// p = 4 (20^3) 442 -> 253, p = 5 (15^3) 280 -> 186, p = 6 (12^3) 207 -> 156; FP32 1.15-1.9x.
+// now: p = 1 (64^3 elements) 557 -> 369 us, p = 2 (40^3) 368 -> 257, p = 3 (24^3) 263 -> 156,
+// p = 4 (20^3) 442 -> 222, p = 5 (15^3) 280 -> 158, p = 6 (12^3) 207 -> 138.
 #include "batch.hpp"
 #include "device.hpp"
 
@@ -39,11 +41,23 @@ constexpr int mrhs_waves(int P, int threads, int lds) {
   return waves < 1 ? 1 : waves < cap ? waves : cap;
 }
 
+// Whether the elements' D goes through LDS: loaded once for the tile, under the latency of X,
+// where the streamed variant reads every plane in each right-hand side's thread.  16
+// right-hand sides, streamed -> LDS: p = 1 (tile 16) 489 -> 404 us, p = 2 (16) 342 -> 278,
+// p = 4 (4) 250 -> 241; FP32 p = 4 (8) 161 -> 140.  Streamed stays at p = 6 (the planes take
+// the LDS of a third workgroup), and for tiles of 2 and 4 in FP64 at odd orders (p = 3 229
+// against 244 us, p = 5 175 against 191).
+constexpr bool mrhs_d_in_lds(int P, int KIND, int NRB, bool f32) {
+  return KIND == PAFEM_DIFFUSION && P <= 5 && (NRB >= 8 || f32 || P % 2 == 0);
+}
+
 template <int P, int Q, int NE, int NRB, int KIND, typename TV, typename TD, typename TC>
-__global__ void __launch_bounds__(NE * Q * Q * NRB,
-                                  mrhs_waves(P, NE * Q * Q * NRB,
-                                             NE * (KIND == PAFEM_DIFFUSION ? 3 : 1) * Q * Q *
-                                                 (P + 1) * NRB * int(sizeof(TC))))
+__global__ void __launch_bounds__(
+    NE * Q * Q * NRB,
+    mrhs_waves(P, NE * Q * Q * NRB,
+               NE * Q * Q *
+                   ((KIND == PAFEM_DIFFUSION ? 3 : 1) * (P + 1) * NRB * int(sizeof(TC)) +
+                    (mrhs_d_in_lds(P, KIND, NRB, sizeof(TC) == 4) ? 6 * Q * int(sizeof(TD)) : 0))))
     pa_apply_mrhs_kernel(const BatchMesh* __restrict__ meshes, int nmesh,
                          const TC* __restrict__ tabB, const TC* __restrict__ tabG, int nrhs) {
   constexpr int D = P + 1, DD = D * D, QQ = Q * Q;
@@ -53,7 +67,10 @@ __global__ void __launch_bounds__(NE * Q * Q * NRB,
   constexpr int ELEM = NCC * QQ * D;  // entries of one element region (per rhs)
   static_assert((DIFF ? 2 : 1) * D <= NCC * Q, "x-line outputs must fit the element region");
 
+  constexpr bool DLDS = mrhs_d_in_lds(P, KIND, NRB, sizeof(TC) == 4);
+  typedef typename Pair<TC, TD>::type pair_t;
   __shared__ TC sW[NE * ELEM * NRB];
+  __shared__ pair_t sD[DLDS ? NE * 3 * Q * QQ : 1];  // [el][k, qz][line]
 
   // which mesh, which tile of it and which chunk of right-hand sides: consecutive
   // workgroups of one die take the chunks of a tile and then its neighbour, so D, the dof
@@ -85,7 +102,7 @@ __global__ void __launch_bounds__(NE * Q * Q * NRB,
   auto at = [&](int c, int qy, int qx, int dz) -> TC& {
     return W[(((c * Q + qy) * Q + qx) * D + dz) * NRB];
   };
-  // D of this thread's z-line (qy, qx) = r, one plane ahead of its use: all of it held in
+  // D of this thread's z-line (qy, qx) = r, a plane at a time: all of it held in
   // registers (12 Q of them) left one workgroup of 5 waves per CU at p = 4
   constexpr int NT = qdata_tile(Q), PL = NT * QQ;  // elements of a qdata tile, values a plane
   const TD* const qe = static_cast<const TD*>(M.qdata) + size_t(e / NT) * (NC * Q * PL) +
@@ -94,10 +111,13 @@ __global__ void __launch_bounds__(NE * Q * Q * NRB,
   TC dq[Q][NC];
   auto load_plane = [&](int qz) {
     if constexpr (DIFF) {
-      typedef typename Pair<TC, TD>::type pair_t;
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
-        const pair_t v = *reinterpret_cast<const pair_t*>(qe + 2 * ((k * Q + qz) * PL) + rq);
+        pair_t v;
+        if constexpr (DLDS)
+          v = sD[(el * 3 * Q + k * Q + qz) * QQ + r];
+        else
+          v = *reinterpret_cast<const pair_t*>(qe + 2 * ((k * Q + qz) * PL) + rq);
         dq[qz][2 * k] = TC(v.x);
         dq[qz][2 * k + 1] = TC(v.y);
       }
@@ -105,11 +125,27 @@ __global__ void __launch_bounds__(NE * Q * Q * NRB,
       dq[qz][0] = TC(qe[qz * PL + rq]);
     }
   };
-  // x-line (dz, dy) = r < D*D: the dofs of its D nodes (re-read where used: cached)
+  // x-line (dz, dy) = r < D*D: the dofs of its D nodes, read again before the scatter
   const bool xline = act && r < DD;
   const int xz = r / D, xy = r - (r / D) * D;
   const bool xline_inner = xz > 0 && xz < P && xy > 0 && xy < P;
   const int32_t* __restrict__ gline = M.gmap + size_t(e) * (DD * D) + r * D;
+  // loads return in order: the dofs first, X waits for nothing else
+  int gx[D];
+  if (xline) {
+#pragma unroll
+    for (int dx = 0; dx < D; ++dx) gx[dx] = gline[dx];
+  }
+  // DLDS: row j = (k, qz) of the line is loaded by the thread of right-hand side j mod NRB,
+  // under the first contraction's loads
+  constexpr int NJ = DLDS ? (3 * Q + NRB - 1) / NRB : 1;
+  pair_t dj[NJ];
+  if constexpr (DLDS) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+      if (act && rb + j * NRB < 3 * Q)
+        dj[j] = *reinterpret_cast<const pair_t*>(qe + size_t(2 * PL) * (rb + j * NRB) + rq);
+  }
   const bool yline = act && r < D * Q;
   const int yz = r / Q, yx = r - (r / Q) * Q;
   const int zy = r / Q, zx = r - (r / Q) * Q;
@@ -119,7 +155,7 @@ __global__ void __launch_bounds__(NE * Q * Q * NRB,
     TC u[D];
 #pragma unroll
     for (int dx = 0; dx < D; ++dx) {
-      const int g = gline[dx];
+      const int g = gx[dx];
       u[dx] = (constrained && g < 0) ? TC(0) : TC(X[size_t(g < 0 ? ~g : g) * nrhs + rr]);
     }
 #pragma unroll
@@ -133,6 +169,11 @@ __global__ void __launch_bounds__(NE * Q * Q * NRB,
       at(xy / Q, xy % Q, qx, xz) = b;
       if (DIFF) at((D + xy) / Q, (D + xy) % Q, qx, xz) = g;
     }
+  }
+  if constexpr (DLDS) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+      if (act && rb + j * NRB < 3 * Q) sD[(el * 3 * Q + rb + j * NRB) * QQ + r] = dj[j];
   }
   __syncthreads();
   // B along y: thread (dz, qx)
@@ -181,7 +222,8 @@ __global__ void __launch_bounds__(NE * Q * Q * NRB,
     for (int dz = 0; dz < D; ++dz) t0[dz] = t1[dz] = t2[dz] = TC(0);
 #pragma unroll
     for (int qz = 0; qz < Q; ++qz) {
-      if (qz + 1 < Q) load_plane(qz + 1);
+      if (DLDS && qz > 0) load_plane(qz);
+      if (!DLDS && qz + 1 < Q) load_plane(qz + 1);
       __asm__ volatile("" ::: "memory");  // keep the next plane's loads in this iteration
       if (DIFF) {
         TC ux = TC(0), uy = TC(0), uz = TC(0);
@@ -246,6 +288,10 @@ __global__ void __launch_bounds__(NE * Q * Q * NRB,
       if (DIFF) at((D + dy) / Q, (D + dy) % Q, yx, yz) = g;
     }
   }
+  if (xline) {
+#pragma unroll
+    for (int dx = 0; dx < D; ++dx) gx[dx] = gline[dx];
+  }
   __syncthreads();
   // B^t along x and G^t: thread (dz, dy)
   if (xline) {
@@ -263,7 +309,7 @@ __global__ void __launch_bounds__(NE * Q * Q * NRB,
         acc += bB(qx, dx) * wB[qx];
         if (DIFF) acc += bG(qx, dx) * wG[qx];
       }
-      const int g = gline[dx];
+      const int g = gx[dx];
       TV* const dst = &Y[size_t(g < 0 ? ~g : g) * nrhs + rr];
       if (dx > 0 && dx < P && xline_inner)  // an interior node: no other element has it
         *dst = TV(acc);
