@@ -140,7 +140,7 @@ __global__ void dg_face_qdata_kernel(const int32_t* __restrict__ faces,
 // Every interior face is evaluated from both sides (a quarter more arithmetic) so that each
 // element writes its own dofs once, with plain stores.  A kernel over the faces, after the
 // volume one, added 2 (p+1)^2 FP64 atomics per face, which go to memory one by one: 166 of
-// the 266 us at p = 4 on 40^3 elements; fused 138 us.
+// the 266 us at p = 4 on 40^3 elements; fused 131 us.
 template <int P>
 __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2))
     dg_apply_kernel(const int32_t* __restrict__ gmap, const int4* __restrict__ efaces,
@@ -183,17 +183,29 @@ __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2))
   auto stride_i = [](int f) { return f < 2 ? D : 1; };
   auto stride_j = [](int f) { return f < 4 ? DD : D; };
 
+  // Loads return in order: the element's block and its face records before the volume data,
+  // behind which x waited for all of it (p = 1, 1e6 elements 276 -> 256 us, p = 4, 64000:
+  // 138 -> 131); from p = 6 the volume data last, under the face stages (64.8 -> 61.2 at
+  // p = 6 on 20^3, 63.7 -> 62.3 at p = 7 on 17^3; p = 4 on 30^3 slower that way, 64.9 -> 68.9).
+  const int own = act ? gmap[size_t(e) * DDD] : 0;
+  int4 recs[RD];
+#pragma unroll
+  for (int k = 0; k < RD; ++k) {
+    const int l = r + k * QQ;
+    if (act && l < 6 * D) recs[k] = efaces[size_t(e) * 6 + l / D];
+  }
   // the volume data of this thread's z-line
   double dq[Q][3];
-  if (act) {
+  auto load_dq = [&]() {
+    if (!act) return;
     const double* const qe = qd + size_t(tile) * (3 * Q * NT) + tid;
 #pragma unroll
     for (int qz = 0; qz < Q; ++qz)
 #pragma unroll
       for (int c = 0; c < 3; ++c) dq[qz][c] = load_value<double, double>(qe + (c * Q + qz) * NT);
-  }
+  };
+  if (P < 6) load_dq();
   // the element's dofs (one contiguous block) into LDS
-  const int own = act ? gmap[size_t(e) * DDD] : 0;
   if (act)
     for (int i = r; i < DDD; i += QQ) X[i] = x[own + i];
   // the neighbours' face dofs of this thread's lines (f, j), in this element's frame
@@ -204,7 +216,7 @@ __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2))
 #pragma unroll
     for (int i = 0; i < D; ++i) nb[k][i] = 0.0;
     if (act && l < 6 * D) {
-      const int4 rec = efaces[size_t(e) * 6 + f];
+      const int4 rec = recs[k];
       if (rec.y >= 0) {
         const int g = (rec.z >> 1) & 7, o = rec.z >> 4;
         // (i, j) -> (u, v): u = i or j, reversed or not; so a line along i is a line there
@@ -218,6 +230,7 @@ __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2))
       }
     }
   }
+  if (P >= 6) load_dq();
   __syncthreads();
 
   // face lines (f, j)
