@@ -27,7 +27,7 @@ namespace {
 constexpr int kElasticValues = 11;
 
 template <int P, int Q>
-__global__ void __launch_bounds__(qdata_tile(Q) * Q * Q, P == 7 ? 2 : 1)
+__global__ void __launch_bounds__(qdata_tile(Q) * Q * Q, P == 3 ? 3 : P == 7 ? 2 : 1)
     elasticity_kernel(const int32_t* __restrict__ tile_off, const int32_t* __restrict__ tile_dofs,
                       const uint16_t* __restrict__ tile_slot, const double* __restrict__ tabB,
                       const double* __restrict__ tabG, const double* __restrict__ qd,
@@ -85,17 +85,44 @@ __global__ void __launch_bounds__(qdata_tile(Q) * Q * Q, P == 7 ? 2 : 1)
     for (int dx = 0; dx < D; ++dx) slot[dx] = sl[dx];
   }
 
+  // The tile's dofs, and all three components of x there, in one chain of latencies instead
+  // of one per component (g below is a third full while they wait): p = 4 on 30^3 elements
+  // 238 -> 211 us, p = 6 on 20^3 194 -> 173, p = 8 on 15^3 241 -> 210, p = 2 on 56^3 284 -> 269
+  constexpr int NG = (DDD + QQ - 1) / QQ;
+  int gd[NG];
+  double xg[3][NG];
+#pragma unroll
+  for (int k = 0; k < NG; ++k) gd[k] = tid + k * NE * QQ < nu ? tile_dofs[u0 + tid + k * NE * QQ] : 0;
+#pragma unroll
+  for (int comp = 0; comp < 3; ++comp)
+#pragma unroll
+    for (int k = 0; k < NG; ++k)
+      xg[comp][k] = (tid + k * NE * QQ < nu && !(constrained && gd[k] < 0))
+                        ? x[comp * nd + (gd[k] < 0 ? ~gd[k] : gd[k])]
+                        : 0.0;
+
   // g[c][qz][b]: reference derivative b of component c at the point (zx, zy, qz);
   // after the point stage, the coefficient of reference derivative b in output c
   double g[3][Q][3];
 
+  // D's planes: up to p = 5 one ahead of its use, the first under the last component (p = 1
+  // on 100^3 607 -> 542 us, p = 2 on 56^3 269 -> 263, p = 3 on 40^3, held to three waves, 259 ->
+  // 230; at p = 6, 8 the plane costs a wave: 173 -> 285 us, 210 -> 318)
+  constexpr bool AHEAD = P <= 5;
+  double next[kElasticValues];
+  auto load_plane = [&](int qz) {
+    const double* const qe = qd + size_t(tile) * kElasticValues * QQQ * NE + tid;
+#pragma unroll
+    for (int c = 0; c < kElasticValues; ++c)
+      next[c] = __builtin_nontemporal_load(qe + (c * Q + qz) * (NE * QQ));
+  };
+
 #pragma unroll
   for (int comp = 0; comp < 3; ++comp) {
-    const double* const xc = x + comp * nd;
-    for (int s = tid; s < nu; s += NE * QQ) {
-      const int gd = tile_dofs[u0 + s];
-      sX[s] = (constrained && gd < 0) ? 0.0 : xc[gd < 0 ? ~gd : gd];
-    }
+    if (AHEAD && comp == 2 && act) load_plane(0);
+#pragma unroll
+    for (int k = 0; k < NG; ++k)
+      if (tid + k * NE * QQ < nu) sX[tid + k * NE * QQ] = xg[comp][k];
     __syncthreads();
     if (xline) {
       double u[D];
@@ -171,17 +198,19 @@ __global__ void __launch_bounds__(qdata_tile(Q) * Q * Q, P == 7 ? 2 : 1)
 
   // point stage
   if (act) {
-    const double* qe = qd + size_t(tile) * kElasticValues * QQQ * NE + tid;
+    const double* const qe = qd + size_t(tile) * kElasticValues * QQQ * NE + tid;
 #pragma unroll
     for (int qz = 0; qz < Q; ++qz) {
       double K[3][3];
+      auto value = [&](int c) {
+        return AHEAD ? next[c] : __builtin_nontemporal_load(qe + (c * Q + qz) * (NE * QQ));
+      };
 #pragma unroll
       for (int b = 0; b < 3; ++b)
 #pragma unroll
-        for (int d = 0; d < 3; ++d)
-          K[b][d] = __builtin_nontemporal_load(qe + ((3 * b + d) * Q + qz) * (NE * QQ));
-      const double lw = __builtin_nontemporal_load(qe + (9 * Q + qz) * (NE * QQ));
-      const double mw = __builtin_nontemporal_load(qe + (10 * Q + qz) * (NE * QQ));
+        for (int d = 0; d < 3; ++d) K[b][d] = value(3 * b + d);
+      const double lw = value(9), mw = value(10);
+      if (AHEAD && qz + 1 < Q) load_plane(qz + 1);
       double F[3][3];  // F[c][d] = d u_c / d x_d
 #pragma unroll
       for (int c = 0; c < 3; ++c)
