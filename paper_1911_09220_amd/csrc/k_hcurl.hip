@@ -99,6 +99,46 @@ __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2), P >= 5 
   auto colG = [&](int d) { return tab(tabG + d); };
   auto colO = [&](int d) { return tab(tabO + d); };  // entry q at [q * DO]
 
+  // Up to p = 4 the slot and sign (~slot: -1) of the entries of this thread's x-lines are
+  // kept for all components, loaded under the gather, and D's planes are loaded one ahead of
+  // their use, the first under the last component: both take the latencies out of the
+  // stages (curl-curl p = 2 on 56^3 elements 166 -> 154 us, mass 152 -> 142, Maxwell p = 4 on
+  // 30^3 178 -> 168, p = 3 on 6^3 19.1 -> 16.3, p = 1 on 16^3 13.4 -> 12.3, on 100^3 497 -> 501).
+  // Above, the registers are full (p = 7 170 -> 173).
+  constexpr bool KEEP = P <= 4, AHEAD = KEEP;
+  int sl[3][DC];
+  auto load_slots = [&](auto Atag) {
+    constexpr int A = decltype(Atag)::value;
+    constexpr int n0 = A == 0 ? DO : DC, n1 = A == 1 ? DO : DC, n2 = A == 2 ? DO : DC;
+    if (act && r < n1 * n2) {
+#pragma unroll
+      for (int i0 = 0; i0 < n0; ++i0) {
+        const int j = A * CB + i0 + n0 * r;
+        const int s = slots[j];
+        sl[A][i0] = signs[j] < 0 ? ~s : s;
+      }
+    }
+  };
+  // entry i0 of the x-line: number j of the element
+  auto entry = [&](int A, int i0, int j) {
+    if constexpr (!KEEP) return double(signs[j]) * sX[slots[j]];
+    const int s = sl[A][i0];
+    return s < 0 ? -sX[~s] : sX[s];
+  };
+  auto add_entry = [&](int A, int i0, int j, double v) {
+    if constexpr (KEEP) {
+      const int s = sl[A][i0];
+      atomicAdd(&sX[s < 0 ? ~s : s], s < 0 ? -v : v);
+    } else {
+      atomicAdd(&sX[slots[j]], double(signs[j]) * v);
+    }
+  };
+  if constexpr (KEEP) {
+    load_slots(std::integral_constant<int, 0>{});
+    load_slots(std::integral_constant<int, 1>{});
+    load_slots(std::integral_constant<int, 2>{});
+  }
+
   // G: the tile's unique dofs, essential ones read as 0 when constrained
   for (int s0 = tid; s0 < nu; s0 += 4 * NE * QQ) {
     int gg[4];
@@ -140,8 +180,7 @@ __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2), P >= 5 
       double in[n0];
 #pragma unroll
       for (int i0 = 0; i0 < n0; ++i0) {
-        const int j = A * CB + i0 + n0 * (i1 + n1 * i2);
-        in[i0] = double(signs[j]) * sX[slots[j]];
+        in[i0] = entry(A, i0, A * CB + i0 + n0 * r);
       }
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
@@ -237,6 +276,14 @@ __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2), P >= 5 
   };
   forward(std::integral_constant<int, 0>{});
   forward(std::integral_constant<int, 1>{});
+  double dn[NCT];
+  auto load_plane = [&](int q) {
+    const double* const qe0 = qd + size_t(tile) * NCT * QQQ * NE + 2 * tid;
+#pragma unroll
+    for (int k = 0; k < NCT / 2; ++k)
+      load_pair<double, double>(qe0 + 2 * ((k * Q + q) * (NE * QQ)), dn[2 * k], dn[2 * k + 1]);
+  };
+  if (AHEAD && act) load_plane(0);
   forward(std::integral_constant<int, 2>{});
 
   // sX was last read by the x contraction of component 2, before the barrier that
@@ -249,12 +296,27 @@ __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2), P >= 5 
     const double* const qe0 = qd + size_t(tile) * NCT * QQQ * NE + 2 * tid;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
+      double dc[NCT];
+      if constexpr (AHEAD) {
+#pragma unroll
+        for (int k = 0; k < NCT; ++k) dc[k] = dn[k];
+        if (q + 1 < Q) load_plane(q + 1);
+      }
+      auto pairs = [&](int p0, double* d) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          if constexpr (AHEAD) {
+            d[2 * k] = dc[2 * (p0 + k)];
+            d[2 * k + 1] = dc[2 * (p0 + k) + 1];
+          } else {
+            load_pair<double, double>(qe0 + 2 * (((p0 + k) * Q + q) * (NE * QQ)), d[2 * k],
+                                      d[2 * k + 1]);
+          }
+        }
+      };
       if constexpr (MASS) {
         double d[6];
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-          load_pair<double, double>(qe0 + 2 * (((MP0 + k) * Q + q) * (NE * QQ)), d[2 * k],
-                                    d[2 * k + 1]);
+        pairs(MP0, d);
         const double a0 = uq[0][q], a1 = uq[1][q], a2 = uq[2][q];
         const double v0 = d[0] * a0 + d[1] * a1 + d[2] * a2;
         const double v1 = d[1] * a0 + d[3] * a1 + d[4] * a2;
@@ -266,10 +328,7 @@ __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2), P >= 5 
       }
       if constexpr (CURL) {
         double d[6];
-#pragma unroll
-        for (int k = 0; k < 3; ++k)
-          load_pair<double, double>(qe0 + 2 * (((CP0 + k) * Q + q) * (NE * QQ)), d[2 * k],
-                                    d[2 * k + 1]);
+        pairs(CP0, d);
         const double a0 = cq[0][q], a1 = cq[1][q], a2 = cq[2][q];
         const double v0 = d[0] * a0 + d[1] * a1 + d[2] * a2;
         const double v1 = d[1] * a0 + d[3] * a1 + d[4] * a2;
@@ -394,8 +453,7 @@ __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2), P >= 5 
             if constexpr (CURL) acc += cg[q * DC] * in[NYB - 1][q];
           }
         }
-        const int j = A * CB + i0 + n0 * (i1 + n1 * i2);
-        atomicAdd(&sX[slots[j]], double(signs[j]) * acc);
+        add_entry(A, i0, A * CB + i0 + n0 * r, acc);
       }
     }
   };
