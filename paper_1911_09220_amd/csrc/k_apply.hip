@@ -221,6 +221,30 @@ __global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, KIND != PAFEM_DI
 #pragma unroll
   for (int qz = 0; qz < (DIVV ? Q : 1); ++qz) sdiv[qz] = TC(0);
 
+  // Three input components: the dof ids are kept, and each component of x is loaded under the
+  // stages of the one before it, where the registers do not cost a wave.  Divergence p = 1 on
+  // 100^3 elements 396 -> 381 us, p = 3 on 40^3 157 -> 149, p = 6 on 20^3 128 -> 115, p = 8 on
+  // 15^3 150 -> 138 (p = 4 loses a wave, 127 -> 128: not used); vector diffusion p = 1 426 ->
+  // 391, p = 3 213 -> 201, p = 5 201 -> 195 (p = 6 loses a wave, 170 -> 287: not used); vector
+  // mass p = 1 202 -> 188, p = 4 on 30^3 93.5 -> 91.3 (p = 5 82 -> 89: not used).
+  constexpr bool GATHER3 = NV == 3 && (DIVV ? P != 4 : P <= (K0 == PAFEM_DIFFUSION ? 5 : 4));
+  constexpr int NG = GATHER3 ? (DDD + QQ - 1) / QQ : 1;
+  int gd[NG];
+  TC xn[NG];
+  auto load_next = [&](int comp) {
+#pragma unroll
+    for (int k = 0; k < NG; ++k)
+      xn[k] = (tid + k * NE * QQ < nu && !(constrained && gd[k] < 0))
+                  ? TC(x[comp * ystride + (gd[k] < 0 ? ~gd[k] : gd[k])])
+                  : TC(0);
+  };
+  if constexpr (GATHER3) {
+#pragma unroll
+    for (int k = 0; k < NG; ++k)
+      gd[k] = tid + k * NE * QQ < nu ? tile_dofs[u0 + tid + k * NE * QQ] : 0;
+    load_next(0);
+  }
+
   for (int comp = 0; comp < NV; ++comp) {
   const TV* const xv_in = x + comp * ystride;
   if (DIVV) load_dq(3 * comp);  // w kappa adj(J)[b][comp], b = 0..2
@@ -230,6 +254,14 @@ __global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, KIND != PAFEM_DI
   // in registers for the scatter
   constexpr bool ONEPASS = DDD <= 4 * QQ;
   int gkeep[4] = {0, 0, 0, 0};
+  if constexpr (GATHER3) {
+#pragma unroll
+    for (int k = 0; k < NG; ++k) {
+      if (ONEPASS) gkeep[k] = gd[k];
+      if (tid + k * NE * QQ < nu) sX[tid + k * NE * QQ] = xn[k];
+    }
+    if (comp + 1 < NV) load_next(comp + 1);
+  } else
   for (int s0 = tid; s0 < nu; s0 += 4 * NE * QQ) {
     int gg[4];
 #pragma unroll
