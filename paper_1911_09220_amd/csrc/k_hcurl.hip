@@ -103,9 +103,11 @@ __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2), P >= 5 
   // kept for all components, loaded under the gather, and D's planes are loaded one ahead of
   // their use, the first under the last component: both take the latencies out of the
   // stages (curl-curl p = 2 on 56^3 elements 166 -> 154 us, mass 152 -> 142, Maxwell p = 4 on
-  // 30^3 178 -> 168, p = 3 on 6^3 19.1 -> 16.3, p = 1 on 16^3 13.4 -> 12.3, on 100^3 497 -> 501).
-  // Above, the registers are full (p = 7 170 -> 173).
-  constexpr bool KEEP = P <= 4, AHEAD = KEEP;
+  // 30^3 178 -> 168, p = 1 on 16^3 13.4 -> 12.3, on 100^3 497 -> 501).  Maxwell at p = 3 loads
+  // only the first plane early (50^3 399 -> 388 us, 6^3 21.2 -> 17.5): all of them ahead cost
+  // a wave, 411 us.  Above p = 4 the registers are full (p = 7 170 -> 173).
+  constexpr bool KEEP = P <= 4;
+  constexpr int AHEAD = !KEEP ? 0 : KIND == PAFEM_HCURL_MAXWELL && P == 3 ? 1 : Q;
   int sl[3][DC];
   auto load_slots = [&](auto Atag) {
     constexpr int A = decltype(Atag)::value;
@@ -283,7 +285,7 @@ __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2), P >= 5 
     for (int k = 0; k < NCT / 2; ++k)
       load_pair<double, double>(qe0 + 2 * ((k * Q + q) * (NE * QQ)), dn[2 * k], dn[2 * k + 1]);
   };
-  if (AHEAD && act) load_plane(0);
+  if (AHEAD > 0 && act) load_plane(0);
   forward(std::integral_constant<int, 2>{});
 
   // sX was last read by the x contraction of component 2, before the barrier that
@@ -297,15 +299,15 @@ __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2), P >= 5 
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
       double dc[NCT];
-      if constexpr (AHEAD) {
+      if (q < AHEAD) {
 #pragma unroll
         for (int k = 0; k < NCT; ++k) dc[k] = dn[k];
-        if (q + 1 < Q) load_plane(q + 1);
+        if (q + 1 < AHEAD) load_plane(q + 1);
       }
       auto pairs = [&](int p0, double* d) {
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-          if constexpr (AHEAD) {
+          if (q < AHEAD) {
             d[2 * k] = dc[2 * (p0 + k)];
             d[2 * k + 1] = dc[2 * (p0 + k) + 1];
           } else {
