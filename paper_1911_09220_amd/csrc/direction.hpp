@@ -12,8 +12,19 @@ __device__ __forceinline__ void finish_done(CGState* st, int done) {
   __hip_atomic_store(&st->done, done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// done as this workgroup saw it, into LDS: valid for all threads after the next barrier, and
+// so the same for all of them.  The first workgroup of a launch may store done while others
+// start: read by every wave for itself, some waves of such a workgroup would leave and the rest
+// sum LDS slots that were never written.
+__device__ __forceinline__ void read_done(const CGState* st, int* stopped) {
+  if (threadIdx.x == 0)
+    *stopped = __hip_atomic_load(const_cast<int32_t*>(&st->done), __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // State after an update: convergence on rr, history, iteration count.  Same decision
-// in every workgroup, written by the first; returns true when the iteration stops.
+// in every workgroup that has not seen done yet, written by the first; returns true when the
+// iteration stops.
 __device__ __forceinline__ bool close_update(CGState* st, double rr, bool broken, double* hist) {
   const int done = (!isfinite(rr) || broken) ? 2 : rr <= st->tol2 ? 1 : 0;
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -30,15 +41,16 @@ __device__ __forceinline__ bool close_update(CGState* st, double rr, bool broken
 // the direction kernels leave it; false when the iteration has stopped.  `scratch`: 2 doubles
 // per wave.  Contains __syncthreads().
 __device__ __forceinline__ bool direction_beta(const Direction& d, double* scratch, double& beta) {
-  const int stopped = d.st->done;
+  __shared__ int stopped;
+  read_done(d.st, &stopped);
   const double rz_old = d.st->rz_old;
   double rz = 0.0, rr = 0.0;
   for (int i = threadIdx.x; i < d.nb; i += blockDim.x) {
     rz += d.partials[i];
     rr += d.partials[kCGBlocks + i];
   }
-  if (stopped) return false;
   block_sum2(rz, rr, scratch);
+  if (stopped) return false;
   beta = rz / rz_old;
   const bool stop = close_update(d.st, rr, !isfinite(beta), d.hist);
   if (blockIdx.x == 0 && threadIdx.x == 0) d.st->rz = rz;

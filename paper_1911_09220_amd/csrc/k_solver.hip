@@ -165,8 +165,9 @@ __device__ __forceinline__ double energy_share(const EnergyParts& ep, const doub
   return s;
 }
 __device__ __forceinline__ bool step_length(CGState* st, double share, double rz, double* scratch,
-                                            double& alpha) {
+                                            const int& stopped, double& alpha) {
   const double pq = block_sum(share, scratch);
+  if (stopped) return false;
   alpha = rz / pq;
   const bool ok = pq > 0.0 && isfinite(alpha);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -239,7 +240,8 @@ __global__ void __launch_bounds__(kCGThreads)
                      const double* __restrict__ d, const double* q,
                      const double* __restrict__ diag, double* q0, int64_t n) {
   __shared__ double scratch[2 * kCGThreads / kWave];
-  const int stopped = st->done;
+  __shared__ int stopped;
+  read_done(st, &stopped);
   const double rz0 = st->rz;
   const double share =
       energy_share(ep, has_ess ? partials + 2 * kCGBlocks : nullptr, gridDim.x);
@@ -254,9 +256,8 @@ __global__ void __launch_bounds__(kCGThreads)
     }
   };
   load(first_entry());
-  if (stopped) return;
   double alpha;
-  if (!step_length(st, share, rz0, scratch, alpha)) return;
+  if (!step_length(st, share, rz0, scratch, stopped, alpha)) return;
   double rz = 0.0, rr = 0.0;
   for (int64_t base = first_entry(); base < n; base += entry_step()) {
     if (base != first_entry()) load(base);
@@ -282,7 +283,8 @@ __global__ void __launch_bounds__(kCGThreads)
                         double* __restrict__ q, const uint8_t* __restrict__ bmask, double* hist,
                         int64_t n) {
   __shared__ double scratch[2 * kCGThreads / kWave];
-  const int stopped = st->done;
+  __shared__ int stopped;
+  read_done(st, &stopped);
   const double rz_old = st->rz_old;
   double rz = strided_share(partials, gridDim.x, 1);
   double rr = strided_share(partials + kCGBlocks, gridDim.x, 1);
@@ -297,8 +299,8 @@ __global__ void __launch_bounds__(kCGThreads)
     }
   };
   load(first_entry());
-  if (stopped) return;
   block_sum2(rz, rr, scratch);
+  if (stopped) return;
   const double beta = rz / rz_old;
   if (close_update(st, rr, !isfinite(beta), hist)) {
     if (blockIdx.x == 0 && threadIdx.x == 0) st->rz = rz;
@@ -370,12 +372,12 @@ __global__ void __launch_bounds__(kCGThreads)
                       const double* __restrict__ q, const double* __restrict__ diag,
                       const uint8_t* __restrict__ bmask, double* __restrict__ zj, int64_t n) {
   __shared__ double scratch[kCGThreads / kWave];
-  const int stopped = st->done;
+  __shared__ int stopped;
+  read_done(st, &stopped);
   const double rz0 = st->rz;
   const double share = energy_share(ep, bmask ? partials + 2 * kCGBlocks : nullptr, gridDim.x);
-  if (stopped) return;
   double alpha;
-  if (!step_length(st, share, rz0, scratch, alpha)) return;
+  if (!step_length(st, share, rz0, scratch, stopped, alpha)) return;
   double rr = 0.0;
   GRID_LOOP(i, n) {
     x[i] += alpha * p[i];
@@ -394,8 +396,10 @@ __global__ void __launch_bounds__(kCGThreads)
                     const double* __restrict__ z, const double* __restrict__ zold, double* hist,
                     int64_t n) {
   __shared__ double scratch[2 * kCGThreads / kWave];
-  if (state_done(st)) return;
+  __shared__ int stopped;
+  read_done(st, &stopped);
   const double rr = block_sum(strided_share(partials + kCGBlocks, gridDim.x, 1), scratch);
+  if (stopped) return;
   if (close_update(st, rr, false, hist)) return;
   double rz = 0.0, rzo = 0.0;
   GRID_LOOP(i, n) {
@@ -413,10 +417,12 @@ __global__ void __launch_bounds__(kCGThreads)
                          double* __restrict__ p, double* __restrict__ q,
                          const uint8_t* __restrict__ bmask, int64_t n) {
   __shared__ double scratch[2 * kCGThreads / kWave];
-  if (state_done(st)) return;
+  __shared__ int stopped;
+  read_done(st, &stopped);
   double rz = strided_share(partials, gridDim.x, 1);
   double rzo = strided_share(partials + 3 * kCGBlocks, gridDim.x, 1);
   block_sum2(rz, rzo, scratch);
+  if (stopped) return;
   const double beta = (rz - rzo) / st->rz_old;
   const bool ok = rz > 0.0 && isfinite(beta);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -494,7 +500,8 @@ __global__ void __launch_bounds__(kCGThreads)
                      const float* __restrict__ d, const float* __restrict__ q,
                      const float* __restrict__ dinv, float* __restrict__ q0, int64_t n) {
   __shared__ double scratch[2 * kCGThreads / kWave];
-  const int stopped = st->done;
+  __shared__ int stopped;
+  read_done(st, &stopped);
   const double rz0 = st->rz;
   const double share =
       energy_share(ep, has_ess ? partials + 2 * kCGBlocks : nullptr, gridDim.x);
@@ -510,9 +517,8 @@ __global__ void __launch_bounds__(kCGThreads)
     }
   };
   load(first_entry());
-  if (stopped) return;
   double alpha;
-  if (!step_length(st, share, rz0, scratch, alpha)) return;
+  if (!step_length(st, share, rz0, scratch, stopped, alpha)) return;
   const double xstep = s * alpha;
   double rz = 0.0, rr = 0.0;
   for (int64_t base = first_entry(); base < n; base += entry_step()) {
@@ -538,7 +544,8 @@ __global__ void __launch_bounds__(kCGThreads)
                         const float* __restrict__ dinv, const float* d, float* dnew,
                         float* __restrict__ q, const uint8_t* __restrict__ ess, int64_t n) {
   __shared__ double scratch[2 * kCGThreads / kWave];
-  const int stopped = st->done;
+  __shared__ int stopped;
+  read_done(st, &stopped);
   const double rz_old = st->rz_old;
   double beta = st->beta;
   double rz = strided_share(partials, gridDim.x, 1);
@@ -555,9 +562,9 @@ __global__ void __launch_bounds__(kCGThreads)
     }
   };
   load(first_entry());
+  block_sum2(rz, rr, scratch);
   if (stopped) return;
   if (!replaced) {
-    block_sum2(rz, rr, scratch);
     beta = rz / rz_old;
     const bool stop = close_update(st, rr, !isfinite(beta), nullptr);
     if (blockIdx.x == 0 && threadIdx.x == 0) st->rz = rz;
