@@ -113,7 +113,7 @@ void Batch::build_descriptors(const void* const* x, void* const* y) {
   host.assign(ops.size(), BatchMesh{});
   for (const Group& g : groups) {
     const int ne_tile = batch_tile_elems(g.cand);
-    int block = 0;
+    int64_t tile = 0;
     for (int k = g.first; k < g.first + g.count; ++k) {
       const Op* o = ops[order[k]];
       const DevSpace& sp = o->space->dev;
@@ -125,19 +125,19 @@ void Batch::build_descriptors(const void* const* x, void* const* y) {
       M.y = y[order[k]];
       M.ne = int32_t(sp.ne);
       M.ndofs = int32_t(sp.ndofs);
-      M.block_begin = block;
+      M.tile_begin = int32_t(tile);
       M.constrained = (o->flags & PAFEM_OP_CONSTRAINED) ? 1 : 0;
-      block += int((sp.ne + ne_tile - 1) / ne_tile) * batch_chunks(g.cand, nrhs);
+      tile += (sp.ne + ne_tile - 1) / ne_tile;
     }
   }
 }
 
-int Batch::group_blocks(const Group& g) const {
+int64_t Batch::group_tiles(const Group& g) const {
   const int ne_tile = batch_tile_elems(g.cand);
-  int blocks = 0;
+  int64_t tiles = 0;
   for (int k = g.first; k < g.first + g.count; ++k)
-    blocks += int((ops[order[k]]->space->ne + ne_tile - 1) / ne_tile) * batch_chunks(g.cand, nrhs);
-  return blocks;
+    tiles += (ops[order[k]]->space->ne + ne_tile - 1) / ne_tile;
+  return tiles;
 }
 
 void Batch::upload(hipStream_t st) {
@@ -156,7 +156,7 @@ void Batch::launch_group(const Group& g, hipStream_t st) const {
   const void* tabB = vdtype == PAFEM_F64 ? static_cast<const void*>(sp.tables + off)
                                          : static_cast<const void*>(sp.tables32 + off);
   if (!launch_batch_apply(g.p, g.cand, vdtype, qdtype, kind, d_meshes + g.first, g.count,
-                          group_blocks(g), tabB, nrhs, st))
+                          group_tiles(g), tabB, nrhs, st))
     throw Error(PAFEM_EUNSUPPORTED, "batched kernel not built for order " + std::to_string(g.p));
 }
 

@@ -17,7 +17,7 @@ struct BatchMesh {
   const void* x;         // [ndofs][nrhs]
   void* y;               // [ndofs][nrhs]
   int32_t ne, ndofs;
-  int32_t block_begin;   // first workgroup of this mesh within its order's launch
+  int32_t tile_begin;    // first tile of this mesh among its order's
   int32_t constrained;
 };
 
@@ -27,20 +27,24 @@ constexpr int kBatchCandidates = 6;
 constexpr int kBatchMfmaCandidate = 5;
 int batch_tile_elems(int cand);
 int batch_tile_rhs(int cand);
-// workgroups per tile: one per chunk of right-hand sides (the matrix-core variant walks
-// them itself)
-inline int batch_chunks(int cand, int nrhs) {
-  return cand == kBatchMfmaCandidate ? 1 : nrhs / batch_tile_rhs(cand);
+// Chunks of right-hand sides in one launch, one workgroup of `threads` for each tile and chunk:
+// all of them, or as even a share as keeps the launch under the 2^32 threads that a grid's
+// first dimension may have (1e6 elements at p = 1 reach them at 478 right-hand sides)
+inline int batch_launch_chunks(int64_t tiles, int threads, int chunks) {
+  const int64_t most = int64_t(0xffffffff) / (tiles * threads);
+  if (most < 1) return 1;  // tiles alone are too many: the launch is refused
+  const int64_t launches = (chunks + most - 1) / most;
+  return int((chunks + launches - 1) / launches);
 }
 // Launches the multi-rhs apply of one order group; false if the (order,
 // candidate, dtype) combination is not built.
 // tabB: the order's 1D B table followed by its G table, in the vector dtype
 bool launch_batch_apply(int p, int cand, int vdtype, int qdtype, int kind,
-                        const BatchMesh* meshes, int nmesh, int nblocks, const void* tabB,
+                        const BatchMesh* meshes, int nmesh, int64_t ntiles, const void* tabB,
                         int nrhs, hipStream_t st);
 void launch_batch_init(int vdtype, const BatchMesh* meshes, int nmesh, int nrhs, hipStream_t st);
 // the matrix-core variant (FP64, orders 1..4, nrhs a multiple of 16); false otherwise
-bool launch_batch_apply_mfma(int p, int kind, const BatchMesh* meshes, int nmesh, int nblocks,
+bool launch_batch_apply_mfma(int p, int kind, const BatchMesh* meshes, int nmesh, int ntiles,
                              const double* tabB, int nrhs, hipStream_t st);
 
 }  // namespace pafem

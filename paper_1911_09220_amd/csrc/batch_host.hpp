@@ -39,7 +39,7 @@ class Batch {
   };
   void build_descriptors(const void* const* x, void* const* y);
   void upload(hipStream_t st);
-  int group_blocks(const Group& g) const;
+  int64_t group_tiles(const Group& g) const;
   void launch_group(const Group& g, hipStream_t st) const;
   void launch_all(hipStream_t st) const;
   void prepare(const void* const* x, void* const* y, hipStream_t st);

@@ -59,7 +59,8 @@ __global__ void __launch_bounds__(
                    ((KIND == PAFEM_DIFFUSION ? 3 : 1) * (P + 1) * NRB * int(sizeof(TC)) +
                     (mrhs_d_in_lds(P, KIND, NRB, sizeof(TC) == 4) ? 6 * Q * int(sizeof(TD)) : 0))))
     pa_apply_mrhs_kernel(const BatchMesh* __restrict__ meshes, int nmesh,
-                         const TC* __restrict__ tabB, const TC* __restrict__ tabG, int nrhs) {
+                         const TC* __restrict__ tabB, const TC* __restrict__ tabG, int nrhs,
+                         int nchunk, int first_rhs) {
   constexpr int D = P + 1, DD = D * D, QQ = Q * Q;
   constexpr bool DIFF = (KIND == PAFEM_DIFFUSION);
   constexpr int NC = DIFF ? 6 : 1;
@@ -72,16 +73,16 @@ __global__ void __launch_bounds__(
   __shared__ TC sW[NE * ELEM * NRB];
   __shared__ pair_t sD[DLDS ? NE * 3 * Q * QQ : 1];  // [el][k, qz][line]
 
-  // which mesh, which tile of it and which chunk of right-hand sides: consecutive
-  // workgroups of one die take the chunks of a tile and then its neighbour, so D, the dof
+  // which mesh, which tile of it and which of the launch's nchunk chunks of right-hand sides
+  // (the first begins at first_rhs): consecutive workgroups of one die take the chunks of a tile and then its neighbour, so D, the dof
   // map and the shared dofs' lines stay in that die's L2
   int m = 0;
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  while (m + 1 < nmesh && meshes[m + 1].block_begin <= blk) ++m;
+  const int t = blk / nchunk;
+  while (m + 1 < nmesh && meshes[m + 1].tile_begin <= t) ++m;
   const BatchMesh& M = meshes[m];
-  const int nchunk = nrhs / NRB;
-  const int tile = (blk - M.block_begin) / nchunk;
-  const int r0 = (blk - M.block_begin - tile * nchunk) * NRB;
+  const int tile = t - M.tile_begin;
+  const int r0 = first_rhs + (blk - t * nchunk) * NRB;
 
   const int constrained = M.constrained;
   auto bB = [&](int q, int d) -> TC { return tabB[q * D + d]; };
@@ -345,49 +346,52 @@ __global__ void __launch_bounds__(256)
 }
 
 template <int P, int NE, int NRB, typename TV, typename TD, typename TC>
-void launch_cfg(const BatchMesh* meshes, int nmesh, int nblocks, int kind, const void* tab,
+void launch_cfg(const BatchMesh* meshes, int nmesh, int64_t ntiles, int kind, const void* tab,
                 int nrhs, hipStream_t st) {
-  constexpr int Q = P + 2;
+  constexpr int Q = P + 2, T = NE * Q * Q * NRB;
+  const int chunks = nrhs / NRB, per = batch_launch_chunks(ntiles, T, chunks);
   const TC* tabB = static_cast<const TC*>(tab);
   const TC* tabG = tabB + Q * (P + 1);
-  if (kind == PAFEM_DIFFUSION)
-    hipLaunchKernelGGL((pa_apply_mrhs_kernel<P, Q, NE, NRB, PAFEM_DIFFUSION, TV, TD, TC>),
-                       dim3(nblocks), dim3(NE * Q * Q * NRB), 0, st, meshes, nmesh, tabB, tabG,
-                       nrhs);
-  else
-    hipLaunchKernelGGL((pa_apply_mrhs_kernel<P, Q, NE, NRB, PAFEM_MASS, TV, TD, TC>),
-                       dim3(nblocks), dim3(NE * Q * Q * NRB), 0, st, meshes, nmesh, tabB, tabG,
-                       nrhs);
+  for (int c = 0; c < chunks; c += per) {
+    const int nc = chunks - c < per ? chunks - c : per;
+    const dim3 grid(unsigned(ntiles * nc));
+    if (kind == PAFEM_DIFFUSION)
+      hipLaunchKernelGGL((pa_apply_mrhs_kernel<P, Q, NE, NRB, PAFEM_DIFFUSION, TV, TD, TC>), grid,
+                         dim3(T), 0, st, meshes, nmesh, tabB, tabG, nrhs, nc, c * NRB);
+    else
+      hipLaunchKernelGGL((pa_apply_mrhs_kernel<P, Q, NE, NRB, PAFEM_MASS, TV, TD, TC>), grid,
+                         dim3(T), 0, st, meshes, nmesh, tabB, tabG, nrhs, nc, c * NRB);
+  }
 }
 
 // Candidate tiles per order (elements x right-hand sides per workgroup), limited
 // by 1024 threads per workgroup and the LDS of the FP64 diffusion variant.
 template <int P, typename TV, typename TD, typename TC>
-bool launch_tile(int cand, const BatchMesh* meshes, int nmesh, int nblocks, int kind,
+bool launch_tile(int cand, const BatchMesh* meshes, int nmesh, int64_t ntiles, int kind,
                  const void* tab, int nrhs, hipStream_t st) {
   if (cand == 0) {
-    launch_cfg<P, 1, 4, TV, TD, TC>(meshes, nmesh, nblocks, kind, tab, nrhs, st);
+    launch_cfg<P, 1, 4, TV, TD, TC>(meshes, nmesh, ntiles, kind, tab, nrhs, st);
     return true;
   }
   if (cand == 4) {
-    launch_cfg<P, 1, 2, TV, TD, TC>(meshes, nmesh, nblocks, kind, tab, nrhs, st);
+    launch_cfg<P, 1, 2, TV, TD, TC>(meshes, nmesh, ntiles, kind, tab, nrhs, st);
     return true;
   }
   if constexpr (P <= 5) {
     if (cand == 1) {
-      launch_cfg<P, 1, 8, TV, TD, TC>(meshes, nmesh, nblocks, kind, tab, nrhs, st);
+      launch_cfg<P, 1, 8, TV, TD, TC>(meshes, nmesh, ntiles, kind, tab, nrhs, st);
       return true;
     }
   }
   if constexpr (P <= 3) {
     if (cand == 2) {
-      launch_cfg<P, 1, 16, TV, TD, TC>(meshes, nmesh, nblocks, kind, tab, nrhs, st);
+      launch_cfg<P, 1, 16, TV, TD, TC>(meshes, nmesh, ntiles, kind, tab, nrhs, st);
       return true;
     }
   }
   if constexpr (P <= 3) {
     if (cand == 3) {
-      launch_cfg<P, 2, 8, TV, TD, TC>(meshes, nmesh, nblocks, kind, tab, nrhs, st);
+      launch_cfg<P, 2, 8, TV, TD, TC>(meshes, nmesh, ntiles, kind, tab, nrhs, st);
       return true;
     }
   }
@@ -415,21 +419,21 @@ int batch_tile_rhs(int cand) {
 }
 
 bool launch_batch_apply(int p, int cand, int vdtype, int qdtype, int kind,
-                        const BatchMesh* meshes, int nmesh, int nblocks, const void* tab,
+                        const BatchMesh* meshes, int nmesh, int64_t ntiles, const void* tab,
                         int nrhs, hipStream_t st) {
   if (cand == kBatchMfmaCandidate) {
     if (vdtype != PAFEM_F64 || qdtype != PAFEM_F64 || nrhs % 16) return false;
-    return launch_batch_apply_mfma(p, kind, meshes, nmesh, nblocks,
+    return launch_batch_apply_mfma(p, kind, meshes, nmesh, int(ntiles),
                                    static_cast<const double*>(tab), nrhs, st);
   }
   bool ok = false;
 #define PAFEM_BATCH_ORDER(PP)                                                                   \
   case PP:                                                                                      \
     if (vdtype == PAFEM_F64 && qdtype == PAFEM_F64)                                             \
-      ok = launch_tile<PP, double, double, double>(cand, meshes, nmesh, nblocks, kind, tab,     \
+      ok = launch_tile<PP, double, double, double>(cand, meshes, nmesh, ntiles, kind, tab,     \
                                                    nrhs, st);                                   \
     else if (vdtype == PAFEM_F32 && qdtype == PAFEM_F32)                                        \
-      ok = launch_tile<PP, float, float, float>(cand, meshes, nmesh, nblocks, kind, tab, nrhs,  \
+      ok = launch_tile<PP, float, float, float>(cand, meshes, nmesh, ntiles, kind, tab, nrhs,  \
                                                 st);                                            \
     break;
   switch (p) {

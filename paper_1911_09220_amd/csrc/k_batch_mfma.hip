@@ -51,9 +51,9 @@ __global__ void __launch_bounds__(256)
 
   int m = 0;
   const int blk = blockIdx.x;
-  while (m + 1 < nmesh && meshes[m + 1].block_begin <= blk) ++m;
+  while (m + 1 < nmesh && meshes[m + 1].tile_begin <= blk) ++m;
   const BatchMesh& M = meshes[m];
-  const int e = blk - M.block_begin;  // one element per workgroup
+  const int e = blk - M.tile_begin;  // one element per workgroup
   const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
   const int lr = lane % 16, lg = lane / 16;  // operand column (rhs) / row group
   const int32_t* __restrict__ gmap = M.gmap + size_t(e) * D * D * D;
@@ -267,16 +267,16 @@ __global__ void __launch_bounds__(256)
 
 }  // namespace
 
-bool launch_batch_apply_mfma(int p, int kind, const BatchMesh* meshes, int nmesh, int nblocks,
+bool launch_batch_apply_mfma(int p, int kind, const BatchMesh* meshes, int nmesh, int ntiles,
                              const double* tabB, int nrhs, hipStream_t st) {
   const double* tabG = tabB + (p + 2) * (p + 1);
 #define PAFEM_MFMA_ORDER(PP)                                                                  \
   case PP:                                                                                    \
     if (kind == PAFEM_DIFFUSION)                                                              \
-      hipLaunchKernelGGL((pa_apply_mrhs_mfma_kernel<PP, PAFEM_DIFFUSION>), dim3(nblocks),     \
+      hipLaunchKernelGGL((pa_apply_mrhs_mfma_kernel<PP, PAFEM_DIFFUSION>), dim3(ntiles),     \
                          dim3(256), 0, st, meshes, nmesh, tabB, tabG, nrhs);                  \
     else                                                                                      \
-      hipLaunchKernelGGL((pa_apply_mrhs_mfma_kernel<PP, PAFEM_MASS>), dim3(nblocks),          \
+      hipLaunchKernelGGL((pa_apply_mrhs_mfma_kernel<PP, PAFEM_MASS>), dim3(ntiles),          \
                          dim3(256), 0, st, meshes, nmesh, tabB, tabG, nrhs);                  \
     return true;
   switch (p) {
