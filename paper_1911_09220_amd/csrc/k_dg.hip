@@ -8,6 +8,8 @@
 // w (beta . N) is formed (the neighbour's points reached through the face's orientation)
 // and contracted back onto the element's face dofs.  Boundary faces keep the outflow part
 // only (zero inflow data).
+#include <limits>
+
 #include "device.hpp"
 #include "launch.hpp"
 
@@ -259,6 +261,10 @@ __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2))
   // weights of the lines (f, q), outward from this element; the face's own frame is its
   // "-" element's
   double w[RQ][Q];
+  // Outflow where w > above.  Where the velocity is tangential (w = 0) both sides take the
+  // "+" element's value, whose lines therefore compare with the largest negative number: an
+  // infinity or NaN of the "-" element does not cross.
+  double above[RQ];
 #pragma unroll
   for (int k = 0; k < RQ; ++k) {
     const int l = r + k * QQ, f = l / Q, q = l - f * Q;
@@ -266,6 +272,7 @@ __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2))
       const int4 rec = efaces[size_t(e) * 6 + f];
       const double* const wf = fq + size_t(rec.x) * QQ;
       const bool plus = rec.z & 1;
+      above[k] = plus ? -std::numeric_limits<double>::denorm_min() : 0.0;
 #pragma unroll
       for (int t = 0; t < Q; ++t) {
         const double v = wf[plus ? face_perm(rec.z >> 4, q, t, Q) : q + Q * t];
@@ -295,7 +302,7 @@ __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2))
           va += rb[j] * a[j];
           vb += rb[j] * b[j];
         }
-        const double F = w[k][t] * (w[k][t] > 0.0 ? va : vb);
+        const double F = w[k][t] * (w[k][t] > above[k] ? va : vb);
 #pragma unroll
         for (int j = 0; j < D; ++j) o[j] += rb[j] * F;
       }
