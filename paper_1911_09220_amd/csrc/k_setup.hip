@@ -164,20 +164,45 @@ __global__ void evec_gather_kernel(const int32_t* __restrict__ toff,
 }
 
 // y = x on the essential dofs (constrained), 0 on the others; blockIdx.y: component, at
-// stride n.  One launch for all dofs and components, four dofs per thread (a launch for
-// whole groups of four and one for the rest, per component, took 14 us before a 110 us
-// elasticity apply at 3 x 531k dofs, now 6; where n was a multiple of four, and the second
-// launch absent, a small scalar init took 2.3 us against 2.7).
-template <typename T>
+// stride n.  One launch for all dofs and components, four dofs per thread, NP of them
+// neighbours with one load of their masks and one store (NP > 1: 16 bytes, for which x, y and
+// every component have to be aligned; the thread that finds fewer than NP left takes them one
+// by one).  All masks are loaded before the first is looked at.  45000 dofs 2.8 -> 2.4 us, 3.9M
+// 8.7 -> 7.8, 29M 69 -> 57 (one dof at a time, 8-byte stores -> this).
+template <typename T, int NP>
 __global__ void __launch_bounds__(256)
     scatter_init_kernel(const uint8_t* __restrict__ bmask, const T* __restrict__ x,
                         int constrained, T* __restrict__ y, int64_t n) {
+  typedef T pack __attribute__((ext_vector_type(NP)));
+  typedef uint8_t mask __attribute__((ext_vector_type(NP)));
   const int64_t off = int64_t(blockIdx.y) * n;
-  const int64_t g0 = int64_t(blockIdx.x) * (4 * 256) + threadIdx.x;
+  const int64_t g0 = int64_t(blockIdx.x) * (4 * 256) + NP * threadIdx.x;
+  constexpr int K = 4 / NP;
+  mask m[K];
+  pack v[K];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    const int64_t g = g0 + k * 256;
-    if (g < n) y[off + g] = (constrained && bmask[g]) ? x[off + g] : T(0);
+  for (int k = 0; k < K; ++k) {
+    const int64_t g = g0 + k * (256 * NP);
+    m[k] = uint8_t(0);
+    if (constrained && g + NP <= n) m[k] = *reinterpret_cast<const mask*>(bmask + g);
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    bool any = false;
+#pragma unroll
+    for (int j = 0; j < NP; ++j) any = any || m[k][j];
+    v[k] = T(0);
+    if (any) v[k] = *reinterpret_cast<const pack*>(x + off + g0 + k * (256 * NP));
+  }
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int64_t g = g0 + k * (256 * NP);
+#pragma unroll
+    for (int j = 0; j < NP; ++j) v[k][j] = m[k][j] ? v[k][j] : T(0);
+    if (g + NP <= n)
+      *reinterpret_cast<pack*>(y + off + g) = v[k];
+    else
+      for (int64_t i = g; i < n; ++i) y[off + i] = (constrained && bmask[i]) ? x[off + i] : T(0);
   }
 }
 
@@ -264,9 +289,17 @@ template <typename T>
 void scatter_init(const DevSpace& sp, const T* x, bool constrained, T* y, hipStream_t st,
                   int ncomp, bool skip_private) {
   const int64_t n = sp.ndofs, nl = sp.nshared;
-  if (!skip_private)
-    hipLaunchKernelGGL(scatter_init_kernel<T>, dim3(unsigned((n + 1023) / 1024), ncomp), dim3(256),
-                       0, st, sp.bmask, x, int(constrained), y, n);
+  const dim3 grid(unsigned((n + 1023) / 1024), ncomp);
+  constexpr int NP = 16 / sizeof(T);
+  auto aligned = [](const void* p, uintptr_t a) { return reinterpret_cast<uintptr_t>(p) % a == 0; };
+  const bool packs =
+      aligned(x, 16) && aligned(y, 16) && aligned(sp.bmask, NP) && (ncomp == 1 || n % NP == 0);
+  if (!skip_private && packs)
+    hipLaunchKernelGGL((scatter_init_kernel<T, NP>), grid, dim3(256), 0, st, sp.bmask, x,
+                       int(constrained), y, n);
+  else if (!skip_private)
+    hipLaunchKernelGGL((scatter_init_kernel<T, 1>), grid, dim3(256), 0, st, sp.bmask, x,
+                       int(constrained), y, n);
   else if (nl > 0)
     hipLaunchKernelGGL(scatter_init_list_kernel<T>, dim3(unsigned((nl + 255) / 256), ncomp),
                        dim3(256), 0, st, sp.shared, nl, x, int(constrained), y, n);
