@@ -98,8 +98,11 @@ __global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, KIND != PAFEM_DI
   // 42.4 / 41.1 / 39.2 / 48.2 -> 40.9 / 37.0 / 34.4 / 33.9 / 40.9 us with the init of the
   // other dofs alone), and the convection (p = 5..8 2-5%).  At p <= 2 few lines are a
   // tile's own (no difference); the diffusion at p = 5..7 and the divergence were 3-14%
-  // slower (their registers are at the occupancy limit), the H(curl) one equal.
-  constexpr bool PRIV = sizeof(TV) == 8 && has_private(K0, P);
+  // slower (their registers are at the occupancy limit), the H(curl) one equal.  The gradient's
+  // components (p >= 5), whose init clears every dof all the same, store them up to p = 7 (1e7
+  // dofs 862 / 956 / 924 -> 838 / 938 / 903 us, 1.3M 136.9 / 132.6 / 128.7 -> 135.3 / 133.1 /
+  // 129.4) and not at p = 8 (1.4M 175 -> 182, 1e7 equal).
+  constexpr bool PRIV = sizeof(TV) == 8 && has_private(K0, P) && !(GRADC && P == 8);
   static_assert(!((CONV || GRADV || DIVV) && DOT), "the convection, gradient and divergence operators have no energy");
   static_assert(!((GRADV || DIVV) && EVEC), "the gradient and divergence operators use the atomic scatter");
   static_assert(NOUT * D <= NCC * Q, "back x-line arrays must fit the element region");
