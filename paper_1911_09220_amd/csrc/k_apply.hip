@@ -94,10 +94,12 @@ __global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, KIND != PAFEM_DI
   constexpr int NCC = GRAD ? 3 : 1;  // arrays after the y-lines (one per derivative)
   constexpr int NOUT = GRADV ? 3 : 1;  // output components
   // Tiles store their private dofs and add only the others atomically: the mass action at
-  // p >= 3, whose scatter is a third of its time (p = 4 / 5 / 6 / 7 / 8 at ~1.7M dofs 44.4 /
+  // p >= 4, whose scatter is a third of its time (p = 4 / 5 / 6 / 7 / 8 at ~1.7M dofs 44.4 /
   // 42.4 / 41.1 / 39.2 / 48.2 -> 40.9 / 37.0 / 34.4 / 33.9 / 40.9 us with the init of the
-  // other dofs alone), and the convection (p = 5..8 2-5%).  At p <= 2 few lines are a
-  // tile's own (no difference); the diffusion at p = 5..7 and the divergence were 3-14%
+  // other dofs alone), and the convection at p >= 5 (2-5%).  Below, few lines are a tile's own
+  // (added -> stored: mass p = 3 on 72^3 elements 241 -> 254 us, on 36^3 37.9 -> 39.6,
+  // convection p = 3 308 -> 317, p = 4 on 54^3 231 -> 232; p <= 2 no difference); the diffusion
+  // at p = 5..7 and the divergence were 3-14%
   // slower (their registers are at the occupancy limit), the H(curl) one equal.  The gradient's
   // components (p >= 5), whose init clears every dof all the same, store them up to p = 7 (1e7
   // dofs 862 / 956 / 924 -> 838 / 938 / 903 us, 1.3M 136.9 / 132.6 / 128.7 -> 135.3 / 133.1 /

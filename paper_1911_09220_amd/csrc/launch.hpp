@@ -31,9 +31,9 @@ void launch_scatter_init(const DevSpace& sp, const double* x, bool constrained, 
 void launch_scatter_init(const DevSpace& sp, const float* x, bool constrained, float* y,
                          hipStream_t st);
 // whether the FP64 fused apply of this kind (without kVectorKind) and order stores its tiles'
-// private dofs instead of adding them
+// private dofs instead of adding them (the measurements stand with PRIV in k_apply.hip)
 constexpr bool has_private(int kind, int p) {
-  return p >= 3 && (kind == PAFEM_MASS || kind == PAFEM_CONVECTION);
+  return (kind == PAFEM_MASS && p >= 4) || (kind == PAFEM_CONVECTION && p >= 5);
 }
 
 // ---- apply (k_apply.hip) ----
