@@ -8,6 +8,7 @@ namespace pafem {
 
 constexpr int kWave = 64;
 constexpr int kNumXcd = 8;  // MI355X: 8 accelerator complex dies, one L2 each
+constexpr int kNumCu = 256; // compute units
 
 // Workgroups are dispatched round-robin over the XCDs (block b runs on XCD b % 8).
 // Remap so that each XCD works on one contiguous range of tiles: neighbouring

@@ -35,7 +35,8 @@ __host__ __device__ constexpr int eps3(int c, int b, int a) {
 // the k-th axis (k = 0, 1) other than a
 __host__ __device__ constexpr int other_axis(int a, int k) { return k < a ? k : k + 1; }
 
-template <int P, int KIND, bool DOT>
+// EARLY: whether the loads may be kept and issued ahead (below)
+template <int P, int KIND, bool DOT, bool EARLY>
 __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2), P >= 5 ? 2 : 1)
     nd_apply_kernel(const int32_t* __restrict__ tile_off, const int32_t* __restrict__ tile_dofs,
                     const uint16_t* __restrict__ tile_slot, const int8_t* __restrict__ esign,
@@ -102,11 +103,15 @@ __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2), P >= 5 
   // Up to p = 4 the slot and sign (~slot: -1) of the entries of this thread's x-lines are
   // kept for all components, loaded under the gather, and D's planes are loaded one ahead of
   // their use, the first under the last component: both take the latencies out of the
-  // stages (curl-curl p = 2 on 56^3 elements 166 -> 154 us, mass 152 -> 142, Maxwell p = 4 on
-  // 30^3 178 -> 168, p = 1 on 16^3 13.4 -> 12.3, on 100^3 497 -> 501).  Maxwell at p = 3 loads
-  // only the first plane early (50^3 399 -> 388 us, 6^3 21.2 -> 17.5): all of them ahead cost
-  // a wave, 411 us.  Above p = 4 the registers are full (p = 7 170 -> 173).
-  constexpr bool KEEP = P <= 4;
+  // stages (curl-curl p = 2 on 56^3 elements 166 -> 154 us, mass 152 -> 142, mass p = 3 on 50^3
+  // 263 -> 256, Maxwell p = 4 on 38^3 357 -> 333).  Maxwell at p = 1 and 2 gains on small grids
+  // (24^3 13.2 -> 9.5 us, 12^3 10.2 -> 9.7) and is equal on large ones (150^3 1737 -> 1738, 75^3
+  // 579 -> 580).  Maxwell at p = 3 loads only the first plane early (50^3 399 -> 383 us, 6^3
+  // 21.2 -> 17.5): all of them ahead cost a wave, 411 us.  Above p = 4 the registers are full
+  // (p = 7 170 -> 173).
+  // Without EARLY each is loaded where it is used: the shorter chain of a workgroup that has a
+  // compute unit to itself (small_grid).
+  constexpr bool KEEP = EARLY && P <= 4;
   constexpr int AHEAD = !KEEP ? 0 : KIND == PAFEM_HCURL_MAXWELL && P == 3 ? 1 : Q;
   int sl[3][DC];
   auto load_slots = [&](auto Atag) {
@@ -476,6 +481,16 @@ __global__ void __launch_bounds__(qdata_tile(P + 2) * (P + 2) * (P + 2), P >= 5 
   }
 }
 
+// Grids of at most one workgroup per compute unit, where there is no other wave to hide the
+// loads' issue behind: mass and curl-curl at p = 3, 4 are faster without them ahead.  Kernel,
+// ahead -> not: mass p = 4 on 31 tiles 12.4 -> 11.6 us, 143: 13.2 -> 12.6, 247: 13.7 -> 13.0, but
+// 483: 17.8 -> 18.2; p = 3 on 134 tiles 10.1 -> 9.8, 220: 10.7 -> 10.2, 410: 12.7 -> 13.0;
+// curl-curl p = 4 on 74 tiles 16.2 -> 15.6, p = 3 on 220 13.3 -> 12.9, on 410 15.7 -> 16.1.
+// (p <= 2 and Maxwell are faster with them at every size.)
+constexpr bool small_grid_kind(int P, int KIND) {
+  return (P == 3 || P == 4) && KIND != PAFEM_HCURL_MAXWELL;
+}
+
 template <int P, int KIND, bool DOT>
 void launch_nd_one(const DevSpace& sp, bool constrained, const double* qd, const double* x,
                    double* y, double* dotp, hipStream_t st) {
@@ -485,9 +500,15 @@ void launch_nd_one(const DevSpace& sp, bool constrained, const double* qd, const
   const double* tb = sp.tables + table_offset_doubles(Q, P + 1, sp.ng) + 2 * Q;
   const double* tg = tb + Q * (P + 1);
   const double* to = sp.tables_open + nd_open_offset(Q, P);
-  hipLaunchKernelGGL((nd_apply_kernel<P, KIND, DOT>), dim3(nblk), dim3(NE * Q * Q), 0, st,
-                     sp.tile_off, sp.tile_dofs, sp.tile_slot, sp.sign, tb, tg, to, qd, x, y, dotp,
-                     int(sp.ne), int(constrained));
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(nblk), dim3(NE * Q * Q), 0, st, sp.tile_off, sp.tile_dofs,
+                       sp.tile_slot, sp.sign, tb, tg, to, qd, x, y, dotp, int(sp.ne),
+                       int(constrained));
+  };
+  if constexpr (small_grid_kind(P, KIND)) {
+    if (nblk <= kNumCu) return launch(nd_apply_kernel<P, KIND, DOT, false>);
+  }
+  launch(nd_apply_kernel<P, KIND, DOT, true>);
 }
 
 template <int P>
