@@ -595,11 +595,13 @@ pafem_status pafem_fcg_solve(pafem_op op, pafem_net net, const float* feats, con
 
 /* Solver iterations (pafem_pcg_solve batches, pafem_pmg_fcg_solve pairs of
  * iterations) are captured once per solve into a HIP graph (kernels only) and
- * replayed on the caller's stream, where that pays: at most 64 kernels, replayed
- * 16 times or more.  mode 0 launches every kernel directly
+ * replayed on the caller's stream, where that pays: 8 to 64 kernels, and iterations
+ * allowed (max_iter) for 16 replays or more.  mode 0 launches every kernel directly
  * instead; process-wide, returns the previous mode.  Results are the same up to
  * the order of atomic sums. */
 int32_t pafem_set_graph_mode(int32_t mode);
+/* Graphs replayed by all solves of this process so far. */
+int64_t pafem_graph_replays(void);
 
 /* ---------------------------------------------------- order multigrid --- */
 /* Matrix-free preconditioning of PA operators by multigrid in the polynomial

@@ -128,6 +128,10 @@ std::atomic<int>& graph_mode_flag() {
   static std::atomic<int> flag{1};
   return flag;
 }
+std::atomic<int64_t>& graph_replay_count() {
+  static std::atomic<int64_t> count{0};
+  return count;
+}
 }
 
 extern "C" {
@@ -135,6 +139,8 @@ extern "C" {
 const char* pafem_last_error(void) { return g_last_error.c_str(); }
 
 int32_t pafem_version(void) { return 274; }
+
+int64_t pafem_graph_replays(void) { return graph_replay_count().load(); }
 
 int32_t pafem_set_graph_mode(int32_t mode) {
   return graph_mode_flag().exchange(mode != 0 ? 1 : 0);
@@ -710,6 +716,11 @@ pafem_status pafem_pcg_solve(pafem_op op, const double* diag, const double* b, d
           launch_cg_direction(state, partials, r, dg, dk, d, qi, ess, hist, n, s2);
       }
     };
+    // kernels of a full batch
+    auto batch_kernels = [&]() {
+      if (direction_built && host.ess == 0.0) return 2 * check + 1;
+      return check * (apply_kernels(o, !evec) + fold_kernels(nap) + 2);
+    };
     CapturedGraph graph;
     int launched = 0;
     while (true) {
@@ -719,7 +730,7 @@ pafem_status pafem_pcg_solve(pafem_op op, const double* diag, const double* b, d
       if (host.done || launched >= opts->max_iter) break;
       const int batch = std::min(check, opts->max_iter - launched);
       if (graphs_enabled() && batch == check && check >= 2 &&
-          graph_pays(3 * check, opts->max_iter / check)) {
+          graph_pays(batch_kernels(), opts->max_iter / check)) {
         if (!graph.ready()) graph.capture([&](hipStream_t cs) { iterations(cs, check); });
         graph.launch(st);
       } else {

@@ -46,6 +46,11 @@ pafem_status guarded(F&& f) {
 // Workspace bytes of one operator application (element vector of the
 // deterministic scatter; also the diagonal's element vector).
 size_t op_work_bytes(const Op& op);
+// kernels of one apply_op of a symmetric operator: the apply, and the y-init of the atomic scatter
+// (unless y is ready) or the gather of the element-vector one
+inline int apply_kernels(const Op& op, bool y_ready) {
+  return (op.flags & PAFEM_OP_SCATTER_EVEC) || !y_ready ? 2 : 1;
+}
 // y = A x on the op's stream; `work` holds op_work_bytes(op).
 // y_ready: y already holds the apply init (x on essential dofs when constrained, else 0)
 void apply_op(const Op& op, const void* x, void* y, void* work, hipStream_t st,

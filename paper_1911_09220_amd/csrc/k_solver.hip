@@ -671,7 +671,7 @@ namespace {
   check_launch(#kernel)
 
 EnergyParts energy_parts(double* epart, int nepart, hipStream_t s) {
-  if (nepart <= kFoldAbove) return {epart, nepart, 1};
+  if (fold_kernels(nepart) == 0) return {epart, nepart, 1};
   hipLaunchKernelGGL(fold_kernel, dim3(kCGBlocks), dim3(256), 0, s, epart, nepart);
   check_launch("fold_kernel");
   return {epart, kCGBlocks, 8};

@@ -195,6 +195,14 @@ VBufs vcycle_bufs(const PMG& g, const VLayout& L, char* w) {
   return B;
 }
 
+// Below another level the coarse right-hand side is a restriction, 0 on the essential dofs, and
+// the applies may form their direction.
+bool coarse_takes_direction(const PMG& g) {
+  const Op& op = *g.ops[size_t(g.L - 1)];
+  return g.L > 1 && !(op.flags & PAFEM_OP_SCATTER_EVEC) &&
+         apply_takes_direction(op.space->dev, op.kind, op.qdtype);
+}
+
 // Jacobi-PCG from zero with a fixed iteration count (stops early only on an exact
 // zero residual or a breakdown): r, d, q are the level's r, d, y
 void coarse_pcg(const PMG& g, const double* b, double* x, VBufs& B, hipStream_t st) {
@@ -210,10 +218,7 @@ void coarse_pcg(const PMG& g, const double* b, double* x, VBufs& B, hipStream_t 
   double* const yi = evec ? nullptr : v.y;  // the apply's y-init, written with the direction
   launch_cg_init(B.state, B.partials, b, nullptr, diag, x, v.r, v.d, yi, ess, 1, 0.0, iters + 1,
                  B.hist, n, st);
-  // Below another level b is a restriction, 0 on the essential dofs: the applies may form
-  // their direction (second buffer: the scatter's workspace).
-  const bool fused =
-      l > 0 && !evec && apply_takes_direction(op.space->dev, op.kind, op.qdtype);
+  const bool fused = coarse_takes_direction(g);  // second buffer: the scatter's workspace
   double* const dbuf[2] = {v.d, static_cast<double*>(B.opwork)};
   for (int k = 0; k < iters; ++k) {
     double* const dk = fused ? dbuf[k & 1] : v.d;
@@ -251,6 +256,33 @@ void vcycle(const PMG& g, int l, const double* b, double* x, VBufs& B, hipStream
   launch_prolongate(cs, fs, g.interp[size_t(l)], c.x, x, true, st);
   chebyshev(op, diag, g.lmax[size_t(l)], g.o.lo, g.o.hi, g.o.degree, b, x, false, v.r, v.d, v.y,
             B.opwork, st);
+}
+
+// kernels that chebyshev, vcycle and an FCG iteration around it launch
+int chebyshev_kernels(const Op& op, int degree, bool zero_guess) {
+  if (degree <= 0) return zero_guess ? 1 : 0;
+  return (zero_guess ? 0 : apply_kernels(op, false)) + 1 +
+         (degree - 1) * (apply_kernels(op, false) + 1);
+}
+int vcycle_kernels(const PMG& g) {
+  int n = 0;
+  for (int l = 0; l + 1 < g.L; ++l) {  // smoothing, residual, restriction (2), prolongation
+    const Op& op = *g.ops[size_t(l)];
+    n += chebyshev_kernels(op, g.o.degree, true) + apply_kernels(op, false) + 3 +
+         chebyshev_kernels(op, g.o.degree, false);
+  }
+  const Op& c = *g.ops[size_t(g.L - 1)];
+  const int iters = std::max(0, g.o.coarse_iters);
+  const bool evec = c.flags & PAFEM_OP_SCATTER_EVEC;
+  n += 2 + iters * (apply_kernels(c, !evec) + fold_kernels(pa_apply_blocks(c.space->dev)) + 1);
+  if (!coarse_takes_direction(g)) n += std::max(0, iters - 1);
+  return n;
+}
+int fcg_iteration_kernels(const PMG& g) {
+  const Op& op = *g.ops[0];
+  const bool evec = op.flags & PAFEM_OP_SCATTER_EVEC;
+  return apply_kernels(op, !evec) + fold_kernels(pa_apply_blocks(op.space->dev)) + 3 +
+         vcycle_kernels(g);
 }
 
 struct FLayout {
@@ -511,11 +543,8 @@ pafem_status pafem_pmg_fcg_solve(pafem_pmg pmg, const double* b, double* x, void
       launch_fcg_direction(state, partials, zn, p, qi, ess, n, s2);
     };
     int check = std::max(1, opts->check_every);
-    // a pair of iterations: per level 4 degree + 4 kernels, the coarse PCG 3 an iteration, and
-    // 4 of the outer iteration
-    const int pair_kernels =
-        2 * ((g.L - 1) * (4 * std::max(0, g.o.degree) + 4) + 3 * std::max(0, g.o.coarse_iters) + 4);
-    const bool graphs = graphs_enabled() && graph_pays(pair_kernels, opts->max_iter / 2);
+    const bool graphs =
+        graphs_enabled() && graph_pays(2 * fcg_iteration_kernels(g), opts->max_iter / 2);
     if (graphs) check += check & 1;  // whole pairs of iterations per host check
     CapturedGraph pair;               // two iterations, z -> zold -> z
     int launched = 0;

@@ -41,6 +41,7 @@ struct EnergyParts {
   int n, stride;
 };
 constexpr int kFoldAbove = 32768;
+inline int fold_kernels(int nepart) { return nepart > kFoldAbove ? 1 : 0; }
 
 // The direction step of an iteration as part of the apply that follows it (FP64 and FP32
 // diffusion): the kernel sums rz and rr of the last update (partials, nb of each), decides

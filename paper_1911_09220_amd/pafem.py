@@ -85,6 +85,7 @@ def _load():
         "pafem_last_error": (C.c_char_p, []),
         "pafem_version": (I32, []),
         "pafem_set_graph_mode": (I32, [I32]),
+        "pafem_graph_replays": (I64, []),
         "pafem_mesh_create_hex": (I32, [I64, P, I64, P, I32, P, C.POINTER(P)]),
         "pafem_mesh_create_quad": (I32, [I64, P, I64, P, C.POINTER(P)]),
         "pafem_mesh_destroy": (None, [P]),
@@ -208,6 +209,11 @@ def pafem_set_graph_mode(mode):
     """1: replay solver iterations from HIP graphs (default); 0: direct launches.
     Returns the previous mode."""
     return lib.pafem_set_graph_mode(int(mode))
+
+
+def pafem_graph_replays():
+    """Graphs replayed by all solves of this process so far."""
+    return lib.pafem_graph_replays()
 
 
 def pafem_mesh_create_hex(vertices, hexes, geom_order=1, geom_nodes=None):
