@@ -27,14 +27,14 @@ constexpr int kBatchCandidates = 6;
 constexpr int kBatchMfmaCandidate = 5;
 int batch_tile_elems(int cand);
 int batch_tile_rhs(int cand);
-// Chunks of right-hand sides in one launch, one workgroup of `threads` for each tile and chunk:
+// Groups of right-hand sides in one launch, one workgroup of `threads` for each tile and group:
 // all of them, or as even a share as keeps the launch under the 2^32 threads that a grid's
 // first dimension may have (1e6 elements at p = 1 reach them at 478 right-hand sides)
-inline int batch_launch_chunks(int64_t tiles, int threads, int chunks) {
+inline int batch_launch_groups(int64_t tiles, int threads, int groups) {
   const int64_t most = int64_t(0xffffffff) / (tiles * threads);
   if (most < 1) return 1;  // tiles alone are too many: the launch is refused
-  const int64_t launches = (chunks + most - 1) / most;
-  return int((chunks + launches - 1) / launches);
+  const int64_t launches = (groups + most - 1) / most;
+  return int((groups + launches - 1) / launches);
 }
 // Launches the multi-rhs apply of one order group; false if the (order,
 // candidate, dtype) combination is not built.

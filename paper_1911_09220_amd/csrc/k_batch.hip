@@ -9,9 +9,9 @@
 // atomics, broadcast D loads, conflict-free LDS).  Table entries are the same for
 // every lane and come from scalar loads; the quadrature data D goes through LDS or
 // is loaded one plane ahead of its use.  One workgroup per tile and chunk of NRB
-// right-hand sides; the chunks of a tile follow each other on one die, whose L2 keeps D and
-// the dof map.  All meshes of one order share one grouped launch: a workgroup finds its
-// mesh from a prefix table of workgroup counts.
+// right-hand sides (small tiles: per tile and several chunks, mrhs_walks); the chunks of a tile
+// follow each other on one die, whose L2 keeps D and the dof map.  All meshes of one order share
+// one grouped launch: a workgroup finds its mesh from a prefix table of tile counts.
 //
 // Bound by latency at the waves that the registers and LDS leave, and by the atomics (an
 // interior node's sum is stored, no other element has it; the others are added).  Loads
@@ -21,6 +21,9 @@
 // registers across a loop over the chunks (180 at p = 4: one workgroup of 5 waves per CU) ->
 // now: p = 1 (64^3 elements) 557 -> 369 us, p = 2 (40^3) 368 -> 257, p = 3 (24^3) 263 -> 156,
 // p = 4 (20^3) 442 -> 222, p = 5 (15^3) 280 -> 158, p = 6 (12^3) 207 -> 138.
+#include <algorithm>
+#include <type_traits>
+
 #include "batch.hpp"
 #include "device.hpp"
 
@@ -43,24 +46,51 @@ constexpr int mrhs_waves(int P, int threads, int lds) {
 
 // Whether the elements' D goes through LDS: loaded once for the tile, under the latency of X,
 // where the streamed variant reads every plane in each right-hand side's thread.  16
-// right-hand sides, streamed -> LDS: p = 1 (tile 16) 489 -> 404 us, p = 2 (16) 342 -> 278,
-// p = 4 (4) 250 -> 241; FP32 p = 4 (8) 161 -> 140.  Streamed stays at p = 6 (the planes take
-// the LDS of a third workgroup), and for tiles of 2 and 4 in FP64 at odd orders (p = 3 229
-// against 244 us, p = 5 175 against 191).
-constexpr bool mrhs_d_in_lds(int P, int KIND, int NRB, bool f32) {
-  return KIND == PAFEM_DIFFUSION && P <= 5 && (NRB >= 8 || f32 || P % 2 == 0);
+// right-hand sides, streamed -> LDS: p = 1 (tile 16, 64^3 elements) 424 -> 354 us, p = 2 (16,
+// 40^3) 297 -> 237, p = 3 (16, 24^3) 156 -> 139, p = 4 (4, 20^3) 203 -> 193, p = 5 (8, 15^3) 137.5 ->
+// 135; FP32 p = 4 (8) 127 -> 107, p = 5 (8) 95 -> 90.  Tiles of 2 and 4 gain less, as they read D
+// fewer times: p = 2 790 -> 737 (2) and 372 -> 340 (4), p = 5 (4) 153 -> 146, but p = 3 301 -> 309 (2)
+// and 204 -> 211 (4), p = 5 (2) 207 -> 213, and p = 1 on 56^3 with two right-hand sides 120 -> 129.
+// At p = 6 the planes take the LDS of a third workgroup.
+constexpr bool mrhs_d_in_lds(int P, int KIND, int NRB, bool f32, bool walk) {
+  const bool streamed = (P == 1 && NRB <= 4 && !walk) || ((P == 3 || P == 5) && NRB <= 4);
+  return KIND == PAFEM_DIFFUSION && P <= 5 && (f32 || !streamed);
 }
 
-template <int P, int Q, int NE, int NRB, int KIND, typename TV, typename TD, typename TC>
+// Whether workgroups walk several chunks of right-hand sides, D staying in LDS: tiles of 2 and 4
+// at p = 1, 2 and those of 2 at p = 3 in FP32, which are what right-hand sides that 8 does not
+// divide get.  Their workgroups are one wave, and with one per chunk the starts of workgroups
+// bound the launch.  One workgroup per chunk -> walking: p = 1 on 56^3 elements, 10 right-hand
+// sides 679 -> 502 us (FP32 863 -> 501), 14: 909 -> 691 (986 -> 616); on 100^3, 20: 3613 -> 3027
+// (3378 -> 2494); p = 2 on 28^3, 10: 200 -> 147 (222 -> 166); on 50^3, 54: 5260 -> 4042 (6866 ->
+// 4617); p = 3 on 33^3 in FP32, 14: 826 -> 688, but 775 -> 950 in FP64 (D streamed).  Tiles of 2
+// that walk go in launch order, not in die order: p = 1 on 100^3 in FP32, 6: 1841 -> 1624, 54:
+// 12923 -> 11630, p = 2 on 50^3, 6: 577 -> 517 (tiles of 4 the other way: p = 1 on 100^3 in FP32,
+// 20: 2494 -> 2915).
+constexpr bool mrhs_walks(int P, int NRB, bool f32) {
+  return (P <= 2 && NRB <= 4) || (P == 3 && NRB == 2 && f32);
+}
+
+// The right-hand sides of a launch that does not simply take one workgroup per tile and chunk:
+// ngroup groups of `walk` chunks, from first_rhs up to end_rhs.  A type of its own, as one more
+// argument in every launch took the scalar registers of an eighth wave at p = 4 in FP32 (16
+// right-hand sides on 25^3 elements 217 -> 230 us).
+struct RhsPart {
+  int ngroup, walk, first_rhs, end_rhs;
+};
+struct NoPart {};
+
+template <int P, int Q, int NE, int NRB, int KIND, bool PART, typename TV, typename TD, typename TC>
 __global__ void __launch_bounds__(
     NE * Q * Q * NRB,
     mrhs_waves(P, NE * Q * Q * NRB,
                NE * Q * Q *
                    ((KIND == PAFEM_DIFFUSION ? 3 : 1) * (P + 1) * NRB * int(sizeof(TC)) +
-                    (mrhs_d_in_lds(P, KIND, NRB, sizeof(TC) == 4) ? 6 * Q * int(sizeof(TD)) : 0))))
+                    (mrhs_d_in_lds(P, KIND, NRB, sizeof(TC) == 4, PART) ? 6 * Q * int(sizeof(TD))
+                                                                       : 0))))
     pa_apply_mrhs_kernel(const BatchMesh* __restrict__ meshes, int nmesh,
                          const TC* __restrict__ tabB, const TC* __restrict__ tabG, int nrhs,
-                         int nchunk, int first_rhs) {
+                         std::conditional_t<PART, RhsPart, NoPart> part) {
   constexpr int D = P + 1, DD = D * D, QQ = Q * Q;
   constexpr bool DIFF = (KIND == PAFEM_DIFFUSION);
   constexpr int NC = DIFF ? 6 : 1;
@@ -68,21 +98,28 @@ __global__ void __launch_bounds__(
   constexpr int ELEM = NCC * QQ * D;  // entries of one element region (per rhs)
   static_assert((DIFF ? 2 : 1) * D <= NCC * Q, "x-line outputs must fit the element region");
 
-  constexpr bool DLDS = mrhs_d_in_lds(P, KIND, NRB, sizeof(TC) == 4);
+  constexpr bool DLDS = mrhs_d_in_lds(P, KIND, NRB, sizeof(TC) == 4, PART);
   typedef typename Pair<TC, TD>::type pair_t;
   __shared__ TC sW[NE * ELEM * NRB];
   __shared__ pair_t sD[DLDS ? NE * 3 * Q * QQ : 1];  // [el][k, qz][line]
 
-  // which mesh, which tile of it and which of the launch's nchunk chunks of right-hand sides
-  // (the first begins at first_rhs): consecutive workgroups of one die take the chunks of a tile and then its neighbour, so D, the dof
-  // map and the shared dofs' lines stay in that die's L2
+  // which mesh, which tile of it and which right-hand sides.  In die order: consecutive
+  // workgroups of one die take the chunks of a tile and then its neighbour, so D, the dof map
+  // and the shared dofs' lines stay in that die's L2
+  constexpr bool WALK = PART && mrhs_walks(P, NRB, sizeof(TC) == 4);
   int m = 0;
-  const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  const int t = blk / nchunk;
+  const int blk = WALK && NRB == 2 ? int(blockIdx.x) : xcd_remap(blockIdx.x, gridDim.x);
+  int ngroup = nrhs / NRB;
+  if constexpr (PART) ngroup = part.ngroup;
+  const int t = blk / ngroup;
   while (m + 1 < nmesh && meshes[m + 1].tile_begin <= t) ++m;
   const BatchMesh& M = meshes[m];
   const int tile = t - M.tile_begin;
-  const int r0 = first_rhs + (blk - t * nchunk) * NRB;
+  int r0 = (blk - t * ngroup) * NRB, r1 = 0;
+  if constexpr (PART) {
+    r0 = part.first_rhs + r0 * (WALK ? part.walk : 1);
+    r1 = WALK ? min(r0 + part.walk * NRB, part.end_rhs) : 0;
+  }
 
   const int constrained = M.constrained;
   auto bB = [&](int q, int d) -> TC { return tabB[q * D + d]; };
@@ -131,6 +168,8 @@ __global__ void __launch_bounds__(
   const int xz = r / D, xy = r - (r / D) * D;
   const bool xline_inner = xz > 0 && xz < P && xy > 0 && xy < P;
   const int32_t* __restrict__ gline = M.gmap + size_t(e) * (DD * D) + r * D;
+  bool first = true;
+  do {
   // loads return in order: the dofs first, X waits for nothing else
   int gx[D];
   if (xline) {
@@ -144,7 +183,7 @@ __global__ void __launch_bounds__(
   if constexpr (DLDS) {
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
-      if (act && rb + j * NRB < 3 * Q)
+      if (act && first && rb + j * NRB < 3 * Q)
         dj[j] = *reinterpret_cast<const pair_t*>(qe + size_t(2 * PL) * (rb + j * NRB) + rq);
   }
   const bool yline = act && r < D * Q;
@@ -174,7 +213,7 @@ __global__ void __launch_bounds__(
   if constexpr (DLDS) {
 #pragma unroll
     for (int j = 0; j < NJ; ++j)
-      if (act && rb + j * NRB < 3 * Q) sD[(el * 3 * Q + rb + j * NRB) * QQ + r] = dj[j];
+      if (act && first && rb + j * NRB < 3 * Q) sD[(el * 3 * Q + rb + j * NRB) * QQ + r] = dj[j];
   }
   __syncthreads();
   // B along y: thread (dz, qx)
@@ -318,6 +357,12 @@ __global__ void __launch_bounds__(
         unsafeAtomicAdd(dst, TV(acc));
     }
   }
+  if constexpr (WALK) {
+    first = false;
+    r0 += NRB;
+    if (r0 < r1) __syncthreads();  // the next chunk overwrites the element regions
+  }
+  } while (WALK && r0 < r1);
 }
 
 // Y = X on essential dofs (constrained) and 0 elsewhere, for every mesh of the
@@ -345,22 +390,43 @@ __global__ void __launch_bounds__(256)
   }
 }
 
+// Walking workgroups take all right-hand sides of a tile from this many tiles on; fewer tiles are
+// split into groups of chunks that make up for it (54 right-hand sides, all at once -> grouped:
+// p = 2 on 8^3 elements 67 -> 30 us, on 12^3 86 -> 74, p = 1 on 8^3 54 -> 26; on 16^3, 4096 tiles,
+// 138 and 77 where 8 groups took 144 and 78)
+constexpr int64_t kWalkTiles = 4096;
+
 template <int P, int NE, int NRB, typename TV, typename TD, typename TC>
 void launch_cfg(const BatchMesh* meshes, int nmesh, int64_t ntiles, int kind, const void* tab,
                 int nrhs, hipStream_t st) {
   constexpr int Q = P + 2, T = NE * Q * Q * NRB;
-  const int chunks = nrhs / NRB, per = batch_launch_chunks(ntiles, T, chunks);
+  const int chunks = nrhs / NRB;
+  // groups of chunks, one workgroup each: as even as possible
+  int groups = chunks;
+  if (mrhs_walks(P, NRB, sizeof(TC) == 4))
+    groups = int(std::min<int64_t>(chunks, (kWalkTiles + ntiles - 1) / ntiles));
+  const int walk = (chunks + groups - 1) / groups;
+  groups = (chunks + walk - 1) / walk;
+  const int per = batch_launch_groups(ntiles, T, groups);
   const TC* tabB = static_cast<const TC*>(tab);
   const TC* tabG = tabB + Q * (P + 1);
-  for (int c = 0; c < chunks; c += per) {
-    const int nc = chunks - c < per ? chunks - c : per;
-    const dim3 grid(unsigned(ntiles * nc));
-    if (kind == PAFEM_DIFFUSION)
-      hipLaunchKernelGGL((pa_apply_mrhs_kernel<P, Q, NE, NRB, PAFEM_DIFFUSION, TV, TD, TC>), grid,
-                         dim3(T), 0, st, meshes, nmesh, tabB, tabG, nrhs, nc, c * NRB);
+  for (int g = 0; g < groups; g += per) {
+    const int ng = std::min(per, groups - g);
+    const dim3 grid(unsigned(ntiles * ng));
+    auto launch = [&](auto kernel, auto part) {
+      hipLaunchKernelGGL(kernel, grid, dim3(T), 0, st, meshes, nmesh, tabB, tabG, nrhs, part);
+    };
+    auto launch_kind = [&](auto part) {
+      constexpr bool PART = !std::is_same<decltype(part), NoPart>::value;
+      if (kind == PAFEM_DIFFUSION)
+        launch(pa_apply_mrhs_kernel<P, Q, NE, NRB, PAFEM_DIFFUSION, PART, TV, TD, TC>, part);
+      else
+        launch(pa_apply_mrhs_kernel<P, Q, NE, NRB, PAFEM_MASS, PART, TV, TD, TC>, part);
+    };
+    if (walk > 1 || ng < chunks)
+      launch_kind(RhsPart{ng, walk, g * walk * NRB, nrhs});
     else
-      hipLaunchKernelGGL((pa_apply_mrhs_kernel<P, Q, NE, NRB, PAFEM_MASS, TV, TD, TC>), grid,
-                         dim3(T), 0, st, meshes, nmesh, tabB, tabG, nrhs, nc, c * NRB);
+      launch_kind(NoPart{});
   }
 }
 
