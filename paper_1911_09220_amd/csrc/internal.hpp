@@ -137,7 +137,7 @@ struct DevSpace {
   const float* tables32 = nullptr;     // the same tables rounded to FP32 (FP32 kernels)
   int32_t* status = nullptr;           // [64] small device status words
   const int32_t* elem_orig = nullptr;  // [ne] caller element id of each device element
-  const int32_t* tile_off = nullptr;   // [ntiles+1] offsets into tile_dofs
+  const int32_t* tile_off = nullptr;   // [ntiles+1] offsets into tile_dofs (H1, ND; L2: no tile lists)
   // unique dofs of each apply tile (~g if essential): first its tile_priv[tile] private
   // dofs (of this tile alone, in lines of kLineDofs such dofs), then the shared ones
   const int32_t* tile_dofs = nullptr;
@@ -247,6 +247,9 @@ inline int nd_dofs_per_elem(int p) { return 3 * p * (p + 1) * (p + 1); }
 Space* build_l2_space(const Mesh* mesh, int order, int flags);
 void space_dof_coords(const Space& s, double* xyz);
 constexpr int kLineDofs = 16;  // FP64 values of a 128-byte cache line
+// the lowest order at which an operator stores its tiles' private dofs (has_private); hexahedral
+// H1 spaces from it on list them, in all others every dof counts as shared
+constexpr int kPrivateOrder = 4;
 constexpr int kSpaceSegments = 20;
 // words of the per-element owner bitmask (bit i of element k: node i is the first
 // occurrence of its dof in device element order)

@@ -33,7 +33,7 @@ void launch_scatter_init(const DevSpace& sp, const float* x, bool constrained, f
 // whether the FP64 fused apply of this kind (without kVectorKind) and order stores its tiles'
 // private dofs instead of adding them (the measurements stand with PRIV in k_apply.hip)
 constexpr bool has_private(int kind, int p) {
-  return (kind == PAFEM_MASS && p >= 4) || (kind == PAFEM_CONVECTION && p >= 5);
+  return (kind == PAFEM_MASS && p >= kPrivateOrder) || (kind == PAFEM_CONVECTION && p >= 5);
 }
 
 // ---- apply (k_apply.hip) ----

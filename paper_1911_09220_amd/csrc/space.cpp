@@ -186,6 +186,10 @@ void finish_space(Space* s, const Mesh& m, int flags) {
   // apply tiles: tile_ne consecutive device elements share one list of unique dofs
   s->tile_ne = s->dim == 2 ? qdata_tile_2d(p + 2) : qdata_tile(p + 2);
   const int64_t ntiles = (ne + s->tile_ne - 1) / s->tile_ne;
+  s->tables = build_tables(p, s->ng);
+  for (int64_t d = 0; d < ndofs; ++d)
+    if (s->bmask[size_t(d)]) s->bdr.push_back(int32_t(d));
+  if (s->family == kFamilyL2) return;  // an element's dofs are one block: no kernel reads lists
   s->tile_off.assign(size_t(ntiles) + 1, 0);
   s->tile_slot.assign(size_t(ntiles) * s->tile_ne * dpe, 0);
   s->tile_dofs.reserve(size_t(ne) * dpe / 2);
@@ -193,9 +197,10 @@ void finish_space(Space* s, const Mesh& m, int flags) {
   // A line with both stored and atomically added entries moves between the dies' L2s: with
   // every dof of one tile stored the diffusion apply at p = 3 (3.9M dofs) took 228 instead
   // of 196 us, with whole lines 193.
+  const bool with_private = s->family == kFamilyH1 && s->dim == 3 && p >= kPrivateOrder;
   std::vector<int32_t> last(size_t(ndofs), -1);
-  std::vector<uint8_t> touched(size_t(ndofs), 0);  // 0, 1, 2 = more than one
-  for (int64_t k = 0; k < ne; ++k) {
+  std::vector<uint8_t> touched(size_t(ndofs), with_private ? 0 : 2);  // 0, 1, 2 = more than one
+  for (int64_t k = 0; with_private && k < ne; ++k) {
     const int32_t t = int32_t(k / s->tile_ne);
     const int32_t* g = s->gmap.data() + size_t(s->dev_order[size_t(k)]) * dpe;
     for (int i = 0; i < dpe; ++i) {
@@ -206,7 +211,7 @@ void finish_space(Space* s, const Mesh& m, int flags) {
       }
     }
   }
-  for (int64_t a = 0; a < ndofs; a += kLineDofs) {
+  for (int64_t a = 0; with_private && a < ndofs; a += kLineDofs) {
     const int64_t b = std::min(ndofs, a + kLineDofs);
     bool one = true;
     for (int64_t d = a; d < b; ++d)
@@ -246,11 +251,9 @@ void finish_space(Space* s, const Mesh& m, int flags) {
     s->tile_priv.push_back(int32_t(priv.size()));
     s->tile_off[size_t(t) + 1] = int32_t(s->tile_dofs.size());
   }
+  if (!with_private) return;
   for (int64_t d = 0; d < ndofs; ++d)
     if (touched[size_t(d)] == 2) s->shared.push_back(s->bmask[size_t(d)] ? ~int32_t(d) : int32_t(d));
-  for (int64_t d = 0; d < ndofs; ++d)
-    if (s->bmask[size_t(d)]) s->bdr.push_back(int32_t(d));
-  s->tables = build_tables(p, s->ng);
 }
 
 // lexicographic corner c = cx + 2 cy -> slot in the counter-clockwise quad order
