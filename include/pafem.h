@@ -122,7 +122,7 @@ typedef int32_t pafem_status;
  * the face's "-" element), then per face one 8-byte slot holding its "-" and "+"
  * elements' indices (caller order, int32 each; 0 for the "+" side of a boundary face);
  * coeff of pafem_qdata_assemble: device beta[3].
- * Unconstrained, atomic scatter, FP64, not symmetric (no diagonal or CG). */
+ * Unconstrained, every dof stored once, FP64, not symmetric (no diagonal or CG). */
 #define PAFEM_DG_CONVECTION 10
 
 /* Space families (pafem_space_family). */

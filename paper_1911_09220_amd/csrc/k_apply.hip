@@ -13,18 +13,18 @@
 // intermediate value passes through LDS once.  Per element:
 //   G    gather the tile's unique dofs once into LDS (essential dofs read as 0 when
 //        constrained); a thread owning the x-line (dz, dy) picks its D values
-//        through the tile slot map.  The index lists are read once per apply and
-//        loaded non-temporally; at p <= 4 every thread keeps the dof ids it gathered
-//        for the scatter instead of reading the list again
+//        through the tile slot map.  The index lists are loaded non-temporally; at p <= 4
+//        the kinds of one component keep the dof ids they gathered for the scatter instead
+//        of reading the list again
 //   B    x-lines (dz, dy) -> y-lines (dz, qx) -> z-lines (qy, qx)
 //   D    pointwise on the z-line: 1 value (mass) or a symmetric 3x3 (diffusion) per
 //        point, streamed from HBM with non-temporal loads issued before the gather
 //        (at some orders only the first planes, the rest one z-iteration ahead)
 //   B^t  z-lines (in registers) -> y-lines -> x-lines
 //   G^t  either: sum the element outputs per unique dof of the tile in LDS, then per
-//        unique dof a plain store if no other tile has the dof, else one hardware FP
-//        atomic into y (pre-set on such dofs by an init kernel); or a plain store of the
-//        element vector for the deterministic transposed gather.
+//        unique dof one hardware FP atomic into y (pre-set by an init kernel), or where
+//        the kind stores its tiles' private dofs (PRIV below) a plain store of those; or
+//        a plain store of the element vector for the deterministic transposed gather.
 // With DOT, each workgroup also writes the sum of its elements' energies
 // u_E . (A_E u_E) (u_E the gathered input, essential entries 0 when constrained) to
 // dotp[blockIdx.x], taken at the quadrature points as the sum of (B G u) . D (B G u):
@@ -256,13 +256,12 @@ __global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, KIND != PAFEM_DI
   // G: gather the tile's unique dofs; four per thread per step keep several
   // gathers in flight
   // at p <= 4 a tile's unique dofs fit one pass of four per thread: the dof ids stay
-  // in registers for the scatter
+  // in registers for the scatter (one component; three read the list again there)
   constexpr bool ONEPASS = DDD <= 4 * QQ;
   int gkeep[4] = {0, 0, 0, 0};
   if constexpr (GATHER3) {
 #pragma unroll
     for (int k = 0; k < NG; ++k) {
-      if (ONEPASS) gkeep[k] = gd[k];
       if (tid + k * NE * QQ < nu) sX[tid + k * NE * QQ] = xn[k];
     }
     if (comp + 1 < NV) load_next(comp + 1);

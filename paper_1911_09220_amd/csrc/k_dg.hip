@@ -64,8 +64,8 @@ __device__ inline void geom_basis(int NG, int j, double x, double& val, double& 
 
 // w_s w_t scale (beta . N) at the Q x Q Gauss points of every face, N = T_b x T_c
 // oriented outward from the face's first element (the interior face's "-" side); after
-// them, one 8-byte slot per face with its two elements' caller indices (the dof blocks
-// a kernel over the faces reads and writes)
+// them, one 8-byte slot per face with its two elements' caller indices, part of the data's
+// published layout (pafem.h; the apply takes its neighbours from the space)
 __global__ void dg_face_qdata_kernel(const int32_t* __restrict__ faces,
                                      const int32_t* __restrict__ bfaces, int64_t nf, int64_t nb,
                                      const int32_t* __restrict__ orig,
