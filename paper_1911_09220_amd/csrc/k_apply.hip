@@ -50,9 +50,12 @@ constexpr int elems_per_block() {
 
 struct NoDirection {};
 
+// The launch bounds ask for the waves per SIMD that the registers can give without spilling in a
+// loop.  Recomputed geometry at p = 4 needs 162 to 169 of them as the compiler happens to order
+// the scatter; 168 are three waves (54^3 elements: two waves 404 us, three 339).
 template <int P, int Q, int KIND, bool EVEC, bool DOT, bool DIR, typename TV, typename TD,
           typename TC>
-__global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, KIND != PAFEM_DIFFUSION ? 1 : sizeof(TC) == 4 ? (P == 6 ? 5 : 1) : (P == 4 || P == 5) ? 4 : P == 2 ? 5 : P >= 6 ? 3 : 1)
+__global__ void __launch_bounds__(elems_per_block<Q>() * Q * Q, (KIND == PAFEM_DIFFUSION_GEOM && P == 4) ? 3 : KIND != PAFEM_DIFFUSION ? 1 : sizeof(TC) == 4 ? (P == 6 ? 5 : 1) : (P == 4 || P == 5) ? 4 : P == 2 ? 5 : P >= 6 ? 3 : 1)
     pa_apply_kernel(const int32_t* __restrict__ tile_off, const int32_t* __restrict__ tile_dofs,
                     const uint16_t* __restrict__ tile_slot, const TC* __restrict__ tabB,
                     const TC* __restrict__ tabG, const TD* __restrict__ qd,
