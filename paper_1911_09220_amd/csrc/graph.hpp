@@ -22,12 +22,13 @@ inline bool graphs_enabled() { return graph_mode_flag().load(std::memory_order_r
 // most.  The graphs live for one solve, capture and instantiation cost about 2 us a kernel, and
 // a replay's own launch as much as several kernels'.  Jacobi-PCG, direct -> graph: batches of 5
 // kernels (two iterations) 0.87 -> 1.10 ms a solve of 16 replays and 3.22 -> 3.80 of 64 (4913
-// dofs), of 6 (0.5M dofs) 2.34 -> 2.56 and 8.96 -> 9.54; 9 kernels 1.57 -> 1.49 and 5.97 -> 5.36, 17 kernels 2.42 -> 2.31 and 9.28 -> 8.53, 41
-// kernels 4.88 -> 4.76 and 19.5 -> 18.2; 8 kernels (element-vector scatter) 1.37 -> 1.24 and
-// 5.22 -> 4.35; on 0.5M dofs, where the device is the slower side, equal to 2 % from 9 kernels
-// on.  Pairs of multigrid FCG iterations of 38 to 58 kernels, replayed 6 to 13 times, 0.96 to
-// 1.07 times as fast; of about 90 kernels (p = 3) 18.5 -> 19.0 ms; 200 CG iterations in 2D as
-// one graph of 600 kernels, replayed once, 9.6 -> 10.9 ms.
+// dofs), of 6 (0.5M dofs) 2.34 -> 2.56 and 8.96 -> 9.54; 9 kernels 1.57 -> 1.49 and 5.97 ->
+// 5.36, 17 kernels 2.42 -> 2.31 and 9.28 -> 8.53, 41 kernels 4.88 -> 4.76 and 19.5 -> 18.2; 8
+// kernels (element-vector scatter) 1.37 -> 1.24 and 5.22 -> 4.35; on 0.5M dofs, where the
+// device is the slower side, equal to 2 % from 9 kernels on.  Pairs of multigrid FCG iterations
+// of 38 to 58 kernels, replayed 6 to 13 times, 0.96 to 1.07 times as fast; of about 90 kernels
+// (p = 3) 18.5 -> 19.0 ms; 200 CG iterations in 2D as one graph of 600 kernels, replayed once,
+// 9.6 -> 10.9 ms.
 inline bool graph_pays(int kernels, int replays) {
   return kernels >= 8 && kernels <= 64 && replays >= 16;
 }
