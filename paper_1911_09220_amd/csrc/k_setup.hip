@@ -288,21 +288,30 @@ namespace {
 template <typename T>
 void scatter_init(const DevSpace& sp, const T* x, bool constrained, T* y, hipStream_t st,
                   int ncomp, bool skip_private) {
-  const int64_t n = sp.ndofs, nl = sp.nshared;
-  const dim3 grid(unsigned((n + 1023) / 1024), ncomp);
+  if (skip_private) {
+    const int64_t nl = sp.nshared;
+    if (nl > 0)
+      hipLaunchKernelGGL(scatter_init_list_kernel<T>, dim3(unsigned((nl + 255) / 256), ncomp),
+                         dim3(256), 0, st, sp.shared, nl, x, int(constrained), y,
+                         int64_t(sp.ndofs));
+    HIP_LAUNCH_CHECK();
+    return;
+  }
+  // Without constraints the components are one run of zeros, and neither x nor the masks are
+  // read (three components of 118k dofs, an odd stride: 2.9 -> 2.6 us, as a plain fill).
+  const int nc = constrained ? ncomp : 1;
+  const int64_t n = constrained ? sp.ndofs : ncomp * sp.ndofs;
+  const dim3 grid(unsigned((n + 1023) / 1024), nc);
   constexpr int NP = 16 / sizeof(T);
   auto aligned = [](const void* p, uintptr_t a) { return reinterpret_cast<uintptr_t>(p) % a == 0; };
-  const bool packs =
-      aligned(x, 16) && aligned(y, 16) && aligned(sp.bmask, NP) && (ncomp == 1 || n % NP == 0);
-  if (!skip_private && packs)
+  const bool packs = aligned(y, 16) && (!constrained || (aligned(x, 16) && aligned(sp.bmask, NP) &&
+                                                         (nc == 1 || n % NP == 0)));
+  if (packs)
     hipLaunchKernelGGL((scatter_init_kernel<T, NP>), grid, dim3(256), 0, st, sp.bmask, x,
                        int(constrained), y, n);
-  else if (!skip_private)
+  else
     hipLaunchKernelGGL((scatter_init_kernel<T, 1>), grid, dim3(256), 0, st, sp.bmask, x,
                        int(constrained), y, n);
-  else if (nl > 0)
-    hipLaunchKernelGGL(scatter_init_list_kernel<T>, dim3(unsigned((nl + 255) / 256), ncomp),
-                       dim3(256), 0, st, sp.shared, nl, x, int(constrained), y, n);
   HIP_LAUNCH_CHECK();
 }
 }  // namespace
